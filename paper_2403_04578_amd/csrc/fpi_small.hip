@@ -6,25 +6,28 @@
 // owns 16 column slots.  Per sweep it
 //   1. forms the current injection conj(S./V) = conj(S) V / |V|^2 (Eq. (3)) of the
 //      slot's buses straight into its MFMA B operand (never stored to memory),
-//   2. multiplies by Z as one real product [Zr -Zi; Zi Zr] [Ir; Ii] on the
-//      16x16x4 FP64 matrix cores, with Z streamed from L2 in fragment order,
+//   2. multiplies by Z on the 16x16x4 FP64 matrix cores, the complex product as three
+//      real ones, with Z streamed from L2 in fragment order,
 //   3. adds w, measures max_i |V'_i - V_i| per column with lane shuffles, and
 //   4. retires converged columns (writes V, sweep count and status) and refills
 //      their slots from a global atomic column queue, so the 16-wide MFMA tiles
 //      stay full while columns finish after different numbers of sweeps.
 //
-// Register layout.  The real-block operator is arranged in 16-row tiles of 8
-// buses: tile rows 0-7 hold the real parts, 8-15 the imaginary parts.  The FP64
-// MFMA leaves tile row g + 4r of output column j in lane 16g + j, register r, so
-// a lane holds Re/Im of buses 8mt+g and 8mt+g+4 of its column.  The K index of
-// the B operand uses the same order, and for k-step 4mt + r lane 16g + j must
-// supply B[16mt + 4r + g][j], which is exactly the value it holds in register r
-// of tile mt: the injection never leaves the lane.
+// Register layout.  A tile is 16 buses; the real and imaginary parts of Z are separate
+// operands.  The FP64 MFMA leaves tile row g + 4r of output column j in lane 16g + j,
+// register r, for each of the three products, so a lane combines Re and Im of buses
+// 16t + g + 4r of its column by itself.  For k-step 4t + r lane 16g + j must supply
+// I[16t + 4r + g][j], which is exactly the bus it holds in register r of tile t: the
+// epilogue lane writes the operand entry that the same lane position reads.
+#include <cmath>
+#include <cstring>
+
 #include "tpf_internal.h"
 
 namespace tpf {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
 template <typename IO>
 __device__ __forceinline__ void ld_c(const IO *p, double &re, double &im) {
@@ -38,117 +41,185 @@ __device__ __forceinline__ void st_c(IO *p, double re, double im) {
     p[1] = (IO)im;
 }
 
-// One workgroup of NW waves owns 16 column slots; wave w computes the output row
-// tiles t = w' + NW q (w' its rotated role) of all 16 columns.  Per lane and
-// owned tile q: v[q] = {Re V(8t+g), Re V(8t+g+4), Im V(8t+g), Im V(8t+g+4)} of the
-// slot's column, s[q] the loads in the same order.  The injections conj(S./V)
-// (B operand) of all buses live in LDS as Ib[16*MT rows][16 columns]; the lane
-// that holds tile-row g + 4r of tile t writes row 16t + g + 4r, and k-step kt
-// reads row 4kt + g, so both access patterns are contiguous 512-byte spans.
+// One workgroup of NW waves owns 16 column slots; wave w computes the 16-bus tiles
+// t = w' + NW q (w' its rotated role) of all 16 columns.  Per lane and owned tile the slot's
+// voltages and loads of buses 16t + g + 4r, r = 0..3, in registers; the injections
+// conj(S./V) of all buses live in LDS as Ib[bus][16 columns] complex values: the lane that
+// holds bus 16t + g + 4r of column j writes row 16t + 4r + g, and k-step kt reads rows
+// 4kt .. 4kt + 3, so both access patterns are contiguous 1 KB spans.
 template <int TPW>
 struct SlotState {
-    d4 v[TPW], s[TPW];
+    d4 vr[TPW], vi[TPW], sr[TPW], si[TPW];
 };
 
-// Writes the injection conj(S./V) of the lane's two buses 8t+g and 8t+g+4; for ZIP loads
-// (Eq. (2)) alpha_P conj(S./V) + alpha_I conj(S) + alpha_Z conj(S) V, with the shares
-// staged in LDS as zl[3][8 MT] (alpha_P, alpha_I, alpha_Z).
-template <bool ZIP>
-__device__ __forceinline__ void put_injection(double *Ib, int t, int lane, const d4 &vv, const d4 &ss,
-                                              const double *zl, int MT) {
+// 1 / x for a finite positive x: the hardware estimate and two Newton steps (within an ulp).
+// The compiler's division spends eleven vector instructions where this takes five, and
+// vector instructions take their issue slots from the FP64 matrix products (see below).
+__device__ __forceinline__ double reciprocal(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
+}
+
+// a + b of the rounded terms, whatever products they came from: the third product's operand
+// has to be the sum of the values the other two use.
+__device__ __forceinline__ double plain_sum(double a, double b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
+// Injections in LDS: complex values, and with SUM their Re + Im as a plane of its own.
+template <bool SUM>
+struct Inj {
+    d2 *c;      // [rows][16]
+    double *s;  // [rows][16] (SUM)
+};
+
+// Writes the injection conj(S./V) of the lane's four buses of tile t (rows below `rows`); for
+// ZIP loads (Eq. (2)) alpha_P conj(S./V) + alpha_I conj(S) + alpha_Z conj(S) V, with the
+// shares staged in LDS as zl[3][16 MT] (alpha_P, alpha_I, alpha_Z).
+template <bool SUM, bool ZIP>
+__device__ __forceinline__ void put_injection(const Inj<SUM> &I, int t, int lane, const d4 &vr, const d4 &vi,
+                                              const d4 &sr, const d4 &si, const double *zl, int MT, int rows) {
     const int g = lane >> 4;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const double vr = vv[h], vi = vv[h + 2], sr = ss[h], si = ss[h + 2];
-        const double inv = 1.0 / (vr * vr + vi * vi);
-        double ir = (sr * vr + si * vi) * inv, ii = (sr * vi - si * vr) * inv;  // conj(S/V)
+    for (int r = 0; r < 4; ++r) {
+        const int b = 16 * t + 4 * r + g;
+        const double inv = reciprocal(vr[r] * vr[r] + vi[r] * vi[r]);
+        const double pr = sr[r] * vr[r] + si[r] * vi[r], pi = sr[r] * vi[r] - si[r] * vr[r];  // conj(S) V
+        double ir = pr * inv, ii = pi * inv;                                                  // conj(S/V)
         if constexpr (ZIP) {
-            const int b = 8 * t + g + 4 * h;
-            const double ap = zl[b], ai = zl[8 * MT + b], az = zl[16 * MT + b];
-            ir = ap * ir + ai * sr + az * (sr * vr + si * vi);
-            ii = ap * ii - ai * si + az * (sr * vi - si * vr);
+            const double ap = zl[b], ai = zl[16 * MT + b], az = zl[32 * MT + b];
+            ir = ap * ir + ai * sr[r] + az * pr;
+            ii = ap * ii - ai * si[r] + az * pi;
         }
-        Ib[256 * t + 64 * h + lane] = ir;        // Re, row 16t+g+4h
-        Ib[256 * t + 64 * (h + 2) + lane] = ii;  // Im, row 16t+g+8+4h
+        if (b < rows) {
+            I.c[64 * (4 * t + r) + lane] = d2{ir, ii};
+            if constexpr (SUM) I.s[64 * (4 * t + r) + lane] = plain_sum(ir, ii);
+        }
     }
 }
 
-// acc[q] += A(tile t_q, k-step kt) * B(k-step kt) over all k-steps, NV owned tiles.
-// A fragments stream from L2 through a 4-deep register ring (loads issued three
-// k-steps ahead of their MFMA); KT = 4 MT is a multiple of 4.  Aw points at this
-// wave role's fragments, laid out [KT + pad][TPW][64].
-template <int TPW, int NV>
-__device__ __forceinline__ void sweep_product(d4 (&acc)[TPW], const double *__restrict__ Aw, const double *Ib,
-                                              int MT, int lane) {
-    const int KT = 4 * MT;
-    constexpr int ST = TPW * 64;  // doubles per k-step
-    // Uniform (scalar) fragment pointers, lane offset added last: the loads use a
-    // scalar base and a 32-bit lane offset instead of per-lane 64-bit addresses.
-    double r0[NV], r1[NV], r2[NV], r3[NV];
+typedef int i4 __attribute__((ext_vector_type(4)));
+
+// The complex product Z I, as three real products instead of four:
+//     m1 = Zr Ir, m2 = Zi Ii, m3 = (Zr + Zi)(Ir + Ii);  Re = m1 - m2, Im = m3 - m1 - m2.
+// The sweep is bound by the FP64 units (64 cycles per 16x16x4 product, and the vector
+// instructions beside it do not overlap with the matrix ones: their busy shares add up to
+// the same 85 % in every form of this kernel), so a quarter fewer products is a quarter
+// less time there.  Every term stays in FP64, and |Z I| is small against |V| ~ 1, whose
+// rounding hides the one extra subtraction.  Fragments of Z (Re and Im of a lane's entry as
+// one 16-byte load) stream from L2 through a 4-deep register ring, issued three k-steps
+// ahead of their products.
+//
+// NV tiles into slots Q0 .. Q0 + NV - 1 over the k-steps [k0, k1); the first one's fragments
+// [KT + pad][64] start at fragment group `a0` (of 64) of the buffer, the others `stride`
+// groups further each.
+template <int TPW, int Q0, int NV, bool SUM>
+__device__ __forceinline__ void sweep_product(d4 (&m1)[TPW], d4 (&m2)[TPW], d4 (&m3)[TPW],
+                                              __amdgpu_buffer_rsrc_t A, int a0, int stride, const Inj<SUM> &I, int k0,
+                                              int k1, int lane) {
+    d2 r0[NV], r1[NV], r2[NV], r3[NV];
+    const int voff = lane * 16;
+    // buffer loads: the k-step is a scalar offset, no vector address arithmetic
+    auto fetch = [&](d2(&r)[NV], int kt) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        r0[q] = Aw[q * 64 + lane];
-        r1[q] = Aw[ST + q * 64 + lane];
-        r2[q] = Aw[2 * ST + q * 64 + lane];
-    }
+        for (int q = 0; q < NV; ++q)
+            r[q] = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(A, voff, (a0 + q * stride + kt) * 1024, 0));
+    };
+    const d2 *Bl = I.c + lane;
+    const double *Sl = I.s + lane;
+    d2 nb = Bl[k0 * 64];  // the next k-step's injections, read ahead of its products
+    double ns = 0.0;
+    if constexpr (SUM) ns = Sl[k0 * 64];
+    auto step = [&](const d2(&r)[NV], int kt) __attribute__((always_inline)) {
+        const d2 b = nb;
+        double bs = ns;
+        nb = Bl[(kt + 1) * 64];  // one row group past the last is read, not used
+        if constexpr (SUM)
+            ns = Sl[(kt + 1) * 64];
+        else
+            bs = b.x + b.y;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            const double as = r[q].x + r[q].y;
+            m1[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[q].x, b.x, m1[Q0 + q], 0, 0, 0);
+            m2[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[q].y, b.y, m2[Q0 + q], 0, 0, 0);
+            m3[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(as, bs, m3[Q0 + q], 0, 0, 0);
+        }
+    };
+    fetch(r0, k0);
+    fetch(r1, k0 + 1);
+    fetch(r2, k0 + 2);
+    int kt = k0;
 #pragma unroll 1
-    for (int kt = 0; kt < KT; kt += 4) {
-        const double *A3 = Aw + (size_t)(kt + 3) * ST;
-#pragma unroll
-        for (int q = 0; q < NV; ++q) r3[q] = A3[q * 64 + lane];
-        const double b0 = Ib[kt * 64 + lane];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r0[q], b0, acc[q], 0, 0, 0);
-        {  // the fragment array is padded with zero k-steps: no bounds branch
-            const double *A4 = Aw + (size_t)(kt + 4) * ST;
-#pragma unroll
-            for (int q = 0; q < NV; ++q) r0[q] = A4[q * 64 + lane];
-        }
-        const double b1 = Ib[(kt + 1) * 64 + lane];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r1[q], b1, acc[q], 0, 0, 0);
-        {
-            const double *A5 = Aw + (size_t)(kt + 5) * ST;
-#pragma unroll
-            for (int q = 0; q < NV; ++q) r1[q] = A5[q * 64 + lane];
-        }
-        const double b2 = Ib[(kt + 2) * 64 + lane];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r2[q], b2, acc[q], 0, 0, 0);
-        {
-            const double *A6 = Aw + (size_t)(kt + 6) * ST;
-#pragma unroll
-            for (int q = 0; q < NV; ++q) r2[q] = A6[q * 64 + lane];
-        }
-        const double b3 = Ib[(kt + 3) * 64 + lane];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r3[q], b3, acc[q], 0, 0, 0);
+    for (; kt + 4 <= k1; kt += 4) {  // a tile's fragments are padded with zero k-steps: no bounds branch
+        fetch(r3, kt + 3);
+        step(r0, kt);
+        fetch(r0, kt + 4);
+        step(r1, kt + 1);
+        fetch(r1, kt + 5);
+        step(r2, kt + 2);
+        fetch(r2, kt + 6);
+        step(r3, kt + 3);
     }
+    if (kt < k1) step(r0, kt);
+    if (kt + 1 < k1) step(r1, kt + 1);
+    if (kt + 2 < k1) step(r2, kt + 2);
 }
 
-template <int TPW, int NW, bool ZIP, typename IO>
-__global__ __launch_bounds__(NW * 64) void fpi_f64_kernel(
+// Waves w and w + 4 of a workgroup share a SIMD, so the tiles left over by whole rounds of
+// four, MT % 4 = r of them, would leave 4 - r SIMDs idle for a tile's time.  With SHARE their
+// k-steps are shared out among wave roles 4 .. 7: roles 4 .. 3 + r own one such tile each and
+// do its first r / 4, the other 4 - r do the rest and hand their partial sums over in LDS.
+//
+// The injections are kept in `bufs` copies used in turn: with two (and no shared tiles), a
+// wave that ends its part of the product writes the next injections at once, without
+// waiting for the others.
+//
+// `thr` is the bit pattern of the smallest double whose square root is not below the
+// tolerance: non-negative doubles order like their bit patterns, so the stopping rule and
+// the column maxima (|dV|^2 by LDS atomics) are integer work.
+template <int TPW, int NW, bool SHARE, bool ZIP, typename IO>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(TPW == 1 ? 4 : 2))) void fpi_f64_kernel(
     const IO *__restrict__ S, IO *__restrict__ Vout, int32_t *__restrict__ iters_out,
     int8_t *__restrict__ status_out, const IO *__restrict__ V0, const double *__restrict__ A,
-    const double *__restrict__ wv, int n, int MT, long long tau, double tol, int max_iter,
+    const double *__restrict__ wv, int n, int MT, long long tau, unsigned long long thr, int max_iter, int bufs,
     unsigned long long *__restrict__ queue, const double *__restrict__ aP, const double *__restrict__ aI,
     const double *__restrict__ aZ) {
-    extern __shared__ double lds[];
-    double *Ib = lds;                                 // [16*MT][16]
-    double *part = lds + 256 * MT;                    // [NW][16] partial max |dV|^2
-    int *flag = reinterpret_cast<int *>(part + NW * 16);  // [NW][16] partial non-finite / guard flags
-    unsigned long long *qb = reinterpret_cast<unsigned long long *>(flag + NW * 16);
-    double *wl = reinterpret_cast<double *>(qb + 2);   // [2][8*MT] w staged once
-    double *zl = wl + 16 * MT;                         // [3][8*MT] ZIP shares (ZIP only)
+    constexpr bool SUM = TPW == 1;
+    extern __shared__ __align__(16) double lds[];
+    const int KT = (n + 3) / 4, rows = 4 * KT;
+    d2 *Ibuf = reinterpret_cast<d2 *>(lds);                      // [bufs][rows][16]
+    double *Isum = reinterpret_cast<double *>(Ibuf + (size_t)bufs * rows * 16);  // [bufs][rows][16] (SUM)
+    d2 *wl = reinterpret_cast<d2 *>(Isum + (SUM ? (size_t)bufs * rows * 16 : 0));  // [16 MT] w staged once
+    unsigned long long *mx = reinterpret_cast<unsigned long long *>(wl + 16 * MT);  // [3][16] max |dV|^2 in turn
+    unsigned long long *qb = mx + 48;
+    int *flag = reinterpret_cast<int *>(qb + 2);                 // [16] start voltages refused
+    d2 *hand = reinterpret_cast<d2 *>(flag + 16);                // [3][4][64] partial sums handed over (extra > 0)
+    const int extra = SHARE ? MT & 3 : 0;                        // tiles whose k-steps are shared out
+    double *zl = reinterpret_cast<double *>(hand + (extra ? 768 : 0));  // [3][16 MT] ZIP shares (ZIP only)
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
     const int g = lane >> 4, j = lane & 15;
-    const int tw = (wave + blockIdx.x) % NW;  // rotated role: balances tiles over SIMDs
-    const int nv = (MT - tw + NW - 1) / NW;   // tiles owned by this wave (0..TPW)
-    const double *Aw = A + (size_t)tw * (4 * MT + kFragPadSteps) * TPW * 64;
+    // tiles tw + NW q: the first `nf` (TPW or TPW - 1) over all k-steps, and for owners of a
+    // shared tile one more over the first `ks`
+    const int tw = wave;
+    const int whole = MT - extra;
+    const int nf = (whole - tw + NW - 1) / NW;
+    const bool owner = extra > 0 && tw >= 4 && tw < 4 + extra, helper = extra > 0 && tw >= 4 + extra;
+    const int nv = nf + (owner ? 1 : 0);
+    const int ks = (extra * KT + 3) / 4;
+    const int tstride = KT + kFragPadSteps;  // fragment groups of a tile
+    const __amdgpu_buffer_rsrc_t Az =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(A), 0, MT * tstride * 1024, 0x00027000);
+    // tile of slot q (whole tiles go round the roles; the shared ones come last)
+    auto tile_of = [&](int q) { return q < nf ? tw + NW * q : whole + tw - 4; };
 
     SlotState<TPW> st;
+    Inj<SUM> I{Ibuf, Isum};
+    int turn = 0;  // mx[turn]: this sweep's column maxima
     long long col = -1;
     int it = 0;
     bool exhausted = false;
@@ -156,42 +227,44 @@ __global__ __launch_bounds__(NW * 64) void fpi_f64_kernel(
     // Loads column c into the lanes of the slots with `take` (c < 0: empty slot),
     // writes their injections, and applies the warm-start guard across the workgroup.
     auto load_slots = [&](bool take, long long c) {
-        int ok = 1;
+        int bad = 0;
         const bool real = take && c >= 0;
+        if (take) {
 #pragma unroll
-        for (int q = 0; q < TPW; ++q) {
-            const int t = tw + NW * q;
-            if (q < nv && take) {
+            for (int q = 0; q < TPW; ++q) {
+                if (q < nv) {
+                    const int b0 = 16 * tile_of(q) + g;
+                    const IO *Sp = S + 2 * (c * n + b0), *Vp = V0 + 2 * (c * n + b0);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int b = 8 * t + g + 4 * h;
-                    double sr = 0.0, si = 0.0, vr = 1.0, vi = 0.0;
-                    if (real && b < n) {
-                        ld_c(S + 2 * (c * n + b), sr, si);
-                        if (V0) {
-                            ld_c(V0 + 2 * (c * n + b), vr, vi);
-                            const double m2 = vr * vr + vi * vi;
-                            ok &= (m2 >= 0.25 && m2 <= 2.25) ? 1 : 0;
+                    for (int r = 0; r < 4; ++r) {
+                        double sr = 0.0, si = 0.0, vr = 1.0, vi = 0.0;
+                        if (real && b0 + 4 * r < n) {
+                            ld_c(Sp + 8 * r, sr, si);
+                            if (V0) {
+                                ld_c(Vp + 8 * r, vr, vi);
+                                const double m2 = vr * vr + vi * vi;
+                                bad |= (m2 >= 0.25 && m2 <= 2.25) ? 0 : 1;
+                            }
                         }
+                        st.sr[q][r] = sr;
+                        st.si[q][r] = si;
+                        st.vr[q][r] = vr;
+                        st.vi[q][r] = vi;
                     }
-                    st.s[q][h] = sr;
-                    st.s[q][h + 2] = si;
-                    st.v[q][h] = vr;
-                    st.v[q][h + 2] = vi;
                 }
             }
         }
         if (V0) {  // uniform: a warm start is kept only if every bus of the column passes
-            ok &= __shfl_xor(ok, 16);
-            ok &= __shfl_xor(ok, 32);
-            if (g == 0) flag[wave * 16 + j] = ok;
+            if (threadIdx.x < 16) flag[threadIdx.x] = 0;
             __syncthreads();
-            int all = 1;
-            for (int w = 0; w < NW; ++w) all &= flag[w * 16 + j];
+            if (bad) flag[j] = 1;
             __syncthreads();
-            if (real && !all) {
+            if (real && flag[j]) {
 #pragma unroll
-                for (int q = 0; q < TPW; ++q) st.v[q] = d4{1.0, 1.0, 0.0, 0.0};
+                for (int q = 0; q < TPW; ++q) {
+                    st.vr[q] = d4{1.0, 1.0, 1.0, 1.0};
+                    st.vi[q] = d4{0.0, 0.0, 0.0, 0.0};
+                }
             }
         }
         if (take) {
@@ -199,93 +272,124 @@ __global__ __launch_bounds__(NW * 64) void fpi_f64_kernel(
             it = 0;
 #pragma unroll
             for (int q = 0; q < TPW; ++q)
-                if (q < nv) put_injection<ZIP>(Ib, tw + NW * q, lane, st.v[q], st.s[q], zl, MT);
+                if (q < nv)
+                    put_injection<SUM, ZIP>(I, tile_of(q), lane, st.vr[q], st.vi[q], st.sr[q], st.si[q], zl, MT, rows);
         }
     };
 
-    for (int e = threadIdx.x; e < 16 * MT; e += NW * 64) wl[e] = wv[e];
+    for (int e = threadIdx.x; e < 16 * MT; e += NW * 64) wl[e] = d2{wv[e], wv[16 * MT + e]};
+    if (threadIdx.x < 48) mx[threadIdx.x] = 0ull;
     if constexpr (ZIP) {  // padding buses: no load, share 0
-        for (int e = threadIdx.x; e < 8 * MT; e += NW * 64) {
+        for (int e = threadIdx.x; e < 16 * MT; e += NW * 64) {
             zl[e] = e < n ? aP[e] : 0.0;
-            zl[8 * MT + e] = e < n ? aI[e] : 0.0;
-            zl[16 * MT + e] = e < n && aZ ? aZ[e] : 0.0;
+            zl[16 * MT + e] = e < n ? aI[e] : 0.0;
+            zl[32 * MT + e] = e < n && aZ ? aZ[e] : 0.0;
         }
+        __syncthreads();
     }
-    // Initial fill: 16 consecutive queue entries per workgroup.
-    if (threadIdx.x == 0) *qb = atomicAdd(queue, 16ull);
-    __syncthreads();
+    // Initial fill: 16 consecutive columns per workgroup; the queue deals out those past
+    // the first 16 gridDim.x (it is not touched when there are none).
+    const unsigned long long dealt = 16ull * gridDim.x;
     {
-        const unsigned long long base = *qb;
-        if (base + 16 >= (unsigned long long)tau) exhausted = true;
-        const long long c = (long long)base + j;
+        const long long base = 16ll * blockIdx.x;
+        if (dealt >= (unsigned long long)tau) exhausted = true;
+        const long long c = base + j;
         load_slots(true, c < tau ? c : -1);
     }
     __syncthreads();
 
     while (__ballot(col >= 0)) {
-        // ---- product [Zr -Zi; Zi Zr] [Ir; Ii] for the owned row tiles
-        d4 acc[TPW];
+        // ---- complex product Z I for the owned tiles
+        d4 m1[TPW], m2[TPW], m3[TPW];
 #pragma unroll
-        for (int q = 0; q < TPW; ++q) acc[q] = d4{0.0, 0.0, 0.0, 0.0};
-        switch (nv) {
-#define TPF_NV(k) \
-    case k: if constexpr (k <= TPW) sweep_product<TPW, k>(acc, Aw, Ib, MT, lane); break;
-            TPF_NV(1) TPF_NV(2) TPF_NV(3) TPF_NV(4) TPF_NV(5) TPF_NV(6)
-#undef TPF_NV
-            default: break;
+        for (int q = 0; q < TPW; ++q) m1[q] = m2[q] = m3[q] = d4{0.0, 0.0, 0.0, 0.0};
+        if constexpr (!SHARE) {
+            if (nf == TPW)
+                sweep_product<TPW, 0, TPW>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
+            else if constexpr (TPW > 1)
+                sweep_product<TPW, 0, TPW - 1>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
+        } else {
+            if constexpr (TPW > 1)
+                sweep_product<TPW, 0, TPW - 1>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
+            // the last slot: a whole tile, an owner's part of a shared one, or a helper's parts.
+            // extra = 3: role 7 does the rest of each of the three tiles; 2: roles 6 and 7 of one
+            // each; 1: roles 5, 6 and 7 a third of it each
+            const int h = tw - 4 - extra, third = (KT - ks + 2) / 3;
+            const int e1 = helper ? (extra == 3 ? 3 : h + 1) : nv == TPW ? 1 : 0;
+            for (int e = helper && extra != 3 ? h : 0; e < e1; ++e) {
+                const int t = helper ? whole + (extra == 1 ? 0 : e) : tile_of(TPW - 1);
+                const int k0 = !helper ? 0 : extra == 1 ? min(KT, ks + e * third) : ks;
+                const int k1 = owner ? ks : helper && extra == 1 ? min(KT, k0 + third) : KT;
+                m1[TPW - 1] = m2[TPW - 1] = m3[TPW - 1] = d4{0.0, 0.0, 0.0, 0.0};
+                sweep_product<TPW, TPW - 1, 1>(m1, m2, m3, Az, t * tstride, 0, I, k0, k1, lane);
+                if (helper) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        hand[256 * e + 64 * r + lane] = d2{m1[TPW - 1][r] - m2[TPW - 1][r],
+                                                           m3[TPW - 1][r] - m1[TPW - 1][r] - m2[TPW - 1][r]};
+                }
+            }
         }
-        __syncthreads();  // every wave has read Ib
-        // ---- epilogue: V' = acc + w, partial max |V' - V|^2, next injections
-        double dmax = 0.0;
-        int bad = 0;
+        if (bufs == 1) {
+            __syncthreads();  // every wave has read the injections; partial sums visible
+        } else {
+            I.s = I.c == Ibuf ? Isum + 16 * rows : Isum;
+            I.c = I.c == Ibuf ? Ibuf + 16 * rows : Ibuf;
+        }
+        // ---- epilogue: V' = Z I + w, partial max |V' - V|^2, next injections
+        double dmax = 0.0, poison = 0.0;
 #pragma unroll
         for (int q = 0; q < TPW; ++q) {
             if (q < nv) {
-                const int t = tw + NW * q;
-                const int b0 = 8 * t + g;
-                const double w0r = wl[b0], w1r = wl[b0 + 4];
-                const double w0i = wl[8 * MT + b0], w1i = wl[8 * MT + b0 + 4];
-                const double n0r = acc[q][0] + w0r, n1r = acc[q][1] + w1r;
-                const double n0i = acc[q][2] + w0i, n1i = acc[q][3] + w1i;
-                const double d0r = n0r - st.v[q][0], d0i = n0i - st.v[q][2];
-                const double d1r = n1r - st.v[q][1], d1i = n1i - st.v[q][3];
-                const double e0 = d0r * d0r + d0i * d0i, e1 = d1r * d1r + d1i * d1i;
-                bad |= !(e0 < HUGE_VAL) | !(e1 < HUGE_VAL);
-                dmax = e0 > dmax ? e0 : dmax;
-                dmax = e1 > dmax ? e1 : dmax;
-                st.v[q] = d4{n0r, n1r, n0i, n1i};
-                put_injection<ZIP>(Ib, t, lane, st.v[q], st.s[q], zl, MT);
+                const int t = tile_of(q);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const d2 w = wl[16 * t + g + 4 * r];
+                    double pr = m1[q][r] - m2[q][r], pi = m3[q][r] - m1[q][r] - m2[q][r];
+                    if (SHARE && q == TPW - 1 && owner) {
+                        const int e1 = extra == 1 ? 3 : tw - 3;
+                        for (int e = extra == 1 ? 0 : tw - 4; e < e1; ++e) {
+                            const d2 p = hand[256 * e + 64 * r + lane];
+                            pr += p.x;
+                            pi += p.y;
+                        }
+                    }
+                    const double nr = pr + w.x, ni = pi + w.y;
+                    const double dr = nr - st.vr[q][r], di = ni - st.vi[q][r];
+                    const double e = dr * dr + di * di;
+                    poison = __builtin_fma(e, 0.0, poison);  // NaN once a step is not finite
+                    dmax = fmax(dmax, e);
+                    st.vr[q][r] = nr;
+                    st.vi[q][r] = ni;
+                }
+                put_injection<SUM, ZIP>(I, t, lane, st.vr[q], st.vi[q], st.sr[q], st.si[q], zl, MT, rows);
             }
         }
-        dmax = fmax(dmax, __shfl_xor(dmax, 16));
-        dmax = fmax(dmax, __shfl_xor(dmax, 32));
-        bad |= __shfl_xor(bad, 16);
-        bad |= __shfl_xor(bad, 32);
-        if (g == 0) {
-            part[wave * 16 + j] = dmax;
-            flag[wave * 16 + j] = bad;
-        }
+        // three sets of maxima in turn: this sweep's, the next one's (a wave may already
+        // write it while another still reads these), and the last one's, cleared below
+        unsigned long long *m = mx + 16 * turn;
+        if (nv > 0) atomicMax(m + j, poison == 0.0 ? (unsigned long long)__double_as_longlong(dmax) : ~0ull);
         __syncthreads();
-        dmax = 0.0;
-        bad = 0;
-        for (int w = 0; w < NW; ++w) {
-            dmax = fmax(dmax, part[w * 16 + j]);
-            bad |= flag[w * 16 + j];
-        }
+        const unsigned long long dm2 = m[j];
+        turn = turn == 2 ? 0 : turn + 1;
+        if (threadIdx.x < 16) mx[16 * (turn == 2 ? 0 : turn + 1) + threadIdx.x] = 0ull;
         ++it;
-        const bool conv = !bad && sqrt(dmax) < tol;
+        const bool bad = dm2 == ~0ull, conv = dm2 < thr;
         const bool done = col >= 0 && (bad || conv || it >= max_iter);
         const unsigned long long dm = __ballot(done && g == 0);  // same in every wave
         if (dm) {
+            const int cnt = __popcll(dm);
+            if (threadIdx.x == 0)
+                *qb = exhausted ? (unsigned long long)tau : dealt + atomicAdd(queue, (unsigned long long)cnt);
             if (done) {
 #pragma unroll
                 for (int q = 0; q < TPW; ++q) {
                     if (q < nv) {
+                        const int b0 = 16 * tile_of(q) + g;
+                        IO *Vp = Vout + 2 * (col * n + b0);
 #pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            const int b = 8 * (tw + NW * q) + g + 4 * h;
-                            if (b < n) st_c(Vout + 2 * (col * n + b), st.v[q][h], st.v[q][h + 2]);
-                        }
+                        for (int r = 0; r < 4; ++r)
+                            if (b0 + 4 * r < n) st_c(Vp + 8 * r, st.vr[q][r], st.vi[q][r]);
                     }
                 }
                 if (wave == 0 && g == 0) {
@@ -293,8 +397,6 @@ __global__ __launch_bounds__(NW * 64) void fpi_f64_kernel(
                     status_out[col] = bad ? TPF_ST_NONFINITE : (conv ? TPF_ST_CONVERGED : TPF_ST_MAX_ITER);
                 }
             }
-            const int cnt = __popcll(dm);
-            if (threadIdx.x == 0) *qb = exhausted ? (unsigned long long)tau : atomicAdd(queue, (unsigned long long)cnt);
             __syncthreads();
             const unsigned long long base = *qb;
             if (base + cnt >= (unsigned long long)tau) exhausted = true;
@@ -346,43 +448,84 @@ static int num_cus() {
     return cached[dev];
 }
 
-template <int TPW, int NW, bool ZIP, typename IO>
+// Bit pattern of the smallest double x >= 0 with sqrt(x) >= tol, so that x < it exactly when
+// sqrt(x) < tol (for tol = inf every finite x; sqrt is monotone and correctly rounded).
+static unsigned long long square_bound(double tol) {
+    double x = tol * tol;
+    while (std::sqrt(x) >= tol && x > 0.0) x = std::nextafter(x, 0.0);
+    while (std::sqrt(x) < tol) x = std::nextafter(x, HUGE_VAL);
+    unsigned long long bits;
+    std::memcpy(&bits, &x, 8);
+    return bits;
+}
+
+template <int TPW, int NW, bool SHARE, bool ZIP, typename IO>
 static int launch_rows_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                           int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
                           unsigned long long *queue, hipStream_t stream) {
-    const int MT = dn.MT;
-    const size_t lds = (size_t)256 * MT * sizeof(double) + (size_t)NW * 16 * (sizeof(double) + sizeof(int)) + 16 +
-                       (size_t)(ZIP ? 40 : 16) * MT * sizeof(double);
-    auto kern = fpi_f64_kernel<TPW, NW, ZIP, IO>;
+    const int n = net.n, MT = dn.MT64;
+    const size_t ib = (size_t)(n + 3) / 4 * 4 * (TPW == 1 ? 384 : 256);  // one copy of the injections
+    size_t rest = (size_t)16 * MT * 16 + 48 * 8 + 16 + 64 + (SHARE ? 768 * 16 : 0) + (size_t)(ZIP ? 48 : 0) * MT * 8;
+    auto kern = fpi_f64_kernel<TPW, NW, SHARE, ZIP, IO>;
+    rest = std::max(rest, (size_t)1024);  // the product reads one row group past the last
+    // Two copies of the injections where they do not cost a resident workgroup (half of the
+    // barriers against fewer workgroups to fill the waits of the others).
+    auto resident = [&](int bufs) {
+        const size_t lds = bufs * ib + rest;
+        int per_cu = 0;
+        if (lds > (size_t)160 * 1024 ||
+            hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, NW * 64, lds) != hipSuccess)
+            per_cu = 0;
+        return per_cu;
+    };
+    const int one = resident(1), two = SHARE ? 0 : resident(2);
+    const int bufs = two > 0 && two >= one ? 2 : 1;
+    const size_t lds = bufs * ib + rest;
     if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return fail(TPF_ERR_DEVICE, "hipFuncSetAttribute failed");
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, NW * 64, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
+    const int per_cu = std::max(1, bufs == 2 ? two : one);
     const long long blocks = std::min<long long>((long long)num_cus() * per_cu, (tau + 15) / 16);
+    if (16 * blocks < tau) {  // the columns past the first fill come from the queue
+        const int rc = launch_zero_u64(queue, 1, stream);
+        if (rc != TPF_OK) return rc;
+    }
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NW * 64), lds, stream, (const IO *)S, (IO *)V, iters,
-                       status, (const IO *)V0, dn.A64, dn.w64, net.n, MT, (long long)tau, tol, max_iter, queue,
+                       status, (const IO *)V0, dn.A64, dn.w64, n, MT, (long long)tau, square_bound(tol), max_iter, bufs, queue,
                        (const double *)dn.aP, (const double *)dn.aI, (const double *)dn.aZ);
     return TPF_OK;
 }
 
-template <int TPW, int NW, typename IO>
+template <int TPW, int NW, bool SHARE, typename IO>
 static int launch_rows(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                        int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
                        unsigned long long *queue, hipStream_t stream) {
     if (dn.aP)
-        return launch_rows_as<TPW, NW, true, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue, stream);
-    return launch_rows_as<TPW, NW, false, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue, stream);
+        return launch_rows_as<TPW, NW, SHARE, true, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue,
+                                                        stream);
+    return launch_rows_as<TPW, NW, SHARE, false, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue,
+                                                     stream);
 }
+
+// Leftover tiles are shared out among the waves wherever there are some, as long as a wave
+// owns at most two (with three the registers are full).  Against whole tiles: 145 against
+// 164 us for 43,200 columns of 86 buses (6 tiles), 1,168 against 1,236 us for 100,000 of 149
+// (10 tiles), 1,046 against 1,126 us for 50,000 of 209 (14 tiles); no difference for the
+// 99-bus year (7 tiles, one idle wave of eight).
+static bool shares_tiles(int MT) { return MT > 4 && MT <= 16 && MT % 4 != 0; }
 
 template <typename IO>
 static int dispatch_rows(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                          int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
                          unsigned long long *queue, hipStream_t stream) {
-#define TPF_GO(T, W)                                                                                      \
-    if (dn.TPW == T && dn.NW == W)                                                                        \
-        return launch_rows<T, W, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue, stream);
-    TPF_GO(1, 4) TPF_GO(1, 8) TPF_GO(2, 8) TPF_GO(3, 8) TPF_GO(4, 8) TPF_GO(5, 8)
+    int NW = 0, TPW = 0;
+    f64_config(dn.MT64, NW, TPW);
+    const bool share = shares_tiles(dn.MT64);
+#define TPF_GO(T, W, SH)                                                                                       \
+    if (TPW == T && NW == W && share == SH)                                                                    \
+        return launch_rows<T, W, SH, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue, stream);
+    TPF_GO(1, 1, false) TPF_GO(1, 2, false) TPF_GO(1, 3, false) TPF_GO(1, 4, false) TPF_GO(1, 8, false)
+    TPF_GO(2, 8, false) TPF_GO(3, 8, false) TPF_GO(1, 8, true) TPF_GO(2, 8, true)
 #undef TPF_GO
     return fail(TPF_ERR_UNSUPPORTED, "register-resident sweep kernel: no instance for this network size");
 }

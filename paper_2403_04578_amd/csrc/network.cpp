@@ -70,11 +70,10 @@ static void lu_solve(const std::vector<cd> &lu, const std::vector<int> &piv, int
     }
 }
 
-// Row/column position of (PQ bus q, part) inside the real-block operator used by
-// the small-network kernels: each 16-row tile holds 8 buses, real parts in rows
-// 0-7 and imaginary parts in rows 8-15, so that the FP64 MFMA output layout
-// (lane group g holds tile rows g, g+4, g+8, g+12) keeps Re and Im of a bus in
-// one lane.
+// Row position of (PQ bus q, part) inside the real-block operator of the large-network
+// FP64 product: each 16-row tile holds 8 buses, real parts in rows 0-7 and imaginary
+// parts in rows 8-15, so that the FP64 MFMA output layout (lane group g holds tile rows
+// g, g+4, g+8, g+12) keeps Re and Im of a bus in one lane.
 static inline int blk_pos(int q, int part) { return 16 * (q / 8) + 8 * part + (q % 8); }
 
 // Order of the FP32-family kernels: Re/Im of a bus on adjacent tile rows so that
@@ -112,39 +111,26 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
     };
     // ---- small-network FP64 fragments
     if (n <= 8 * kMaxSmallTiles) {
-        const int MT = (n + 7) / 8, M = 16 * MT, KT = 4 * MT;
-        dn.MT = MT;
-        std::vector<double> Ab((size_t)M * M, 0.0);  // real-block operator, permuted rows/cols
-        for (int i = 0; i < n; ++i)
-            for (int k = 0; k < n; ++k) {
-                const cd z = net.Z[(size_t)i * n + k];
-                Ab[(size_t)blk_pos(i, 0) * M + blk_pos(k, 0)] = z.real();
-                Ab[(size_t)blk_pos(i, 0) * M + blk_pos(k, 1)] = -z.imag();
-                Ab[(size_t)blk_pos(i, 1) * M + blk_pos(k, 0)] = z.imag();
-                Ab[(size_t)blk_pos(i, 1) * M + blk_pos(k, 1)] = z.real();
-            }
-        // 16x16x4 FP64 MFMA A operand: lane 16*kk + ii holds A[16*mt + ii][4*kt + kk].  Grouped
-        // by the wave role that multiplies tile mt (mt % NW), so that one wave's fragments
-        // of a k-step are contiguous.
-        int NW = 0, TPW = 0;
-        rows_config(MT, NW, TPW);
-        dn.NW = NW;
-        dn.TPW = TPW;
+        const int MT = (n + 15) / 16, KT = (n + 3) / 4;
+        dn.MT64 = MT;
+        // 16x16x4 FP64 MFMA A operand: lane 16*kk + ii holds Z[16*mt + ii][4*kt + kk], its real
+        // and imaginary parts side by side.
         const int KP = KT + kFragPadSteps;
-        std::vector<double> frag((size_t)NW * KP * TPW * 64, 0.0);
-        for (int tw = 0; tw < NW; ++tw)
+        std::vector<double> frag((size_t)MT * KP * 128, 0.0);
+        for (int mt = 0; mt < MT; ++mt)
             for (int kt = 0; kt < KT; ++kt)
-                for (int q = 0; q < TPW; ++q) {
-                    const int mt = tw + NW * q;
-                    if (mt >= MT) continue;
-                    for (int l = 0; l < 64; ++l)
-                        frag[(((size_t)tw * KP + kt) * TPW + q) * 64 + l] =
-                            Ab[(size_t)(16 * mt + (l % 16)) * M + 4 * kt + l / 16];
+                for (int l = 0; l < 64; ++l) {
+                    const int i = 16 * mt + l % 16, k = 4 * kt + l / 16;
+                    if (i >= n || k >= n) continue;
+                    const cd z = net.Z[(size_t)i * n + k];
+                    double *f = &frag[(((size_t)mt * KP + kt) * 64 + l) * 2];
+                    f[0] = z.real();
+                    f[1] = z.imag();
                 }
-        std::vector<double> wv(2 * 8 * MT);
-        for (int q = 0; q < 8 * MT; ++q) {
+        std::vector<double> wv(2 * 16 * MT);
+        for (int q = 0; q < 16 * MT; ++q) {
             wv[q] = q < n ? net.w[q].real() : 1.0;
-            wv[8 * MT + q] = q < n ? net.w[q].imag() : 0.0;
+            wv[16 * MT + q] = q < n ? net.w[q].imag() : 0.0;
         }
         if (!dalloc((void **)&dn.A64, frag.size() * 8) || !dalloc((void **)&dn.w64, wv.size() * 8))
             return fail(TPF_ERR_OOM, "device allocation failed (network staging)");
@@ -153,7 +139,12 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
     }
     // ---- FP32-family fragments (FP32 and mixed modes)
     if (n <= 8 * 16) {
-        const int MT = dn.MT, M = 16 * MT, KT = 4 * MT, NW = dn.NW, TPW = dn.TPW;
+        const int MT = (n + 7) / 8, M = 16 * MT, KT = 4 * MT;
+        int NW = 0, TPW = 0;
+        rows_config(MT, NW, TPW);
+        dn.MT = MT;
+        dn.NW = NW;
+        dn.TPW = TPW;
         const int KTL = (MT + 1) / 2, KL = 32 * KTL;
         dn.KTL = KTL;
         std::vector<double> Ab((size_t)M * KL, 0.0);
@@ -194,10 +185,15 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
                         }
                 }
             }
-        if (!dalloc((void **)&dn.A32, f32.size() * 4) || !dalloc((void **)&dn.Abf, nl * 2) ||
+        std::vector<double> wv(2 * 8 * MT);
+        for (int q = 0; q < 8 * MT; ++q) {
+            wv[q] = q < n ? net.w[q].real() : 1.0;
+            wv[8 * MT + q] = q < n ? net.w[q].imag() : 0.0;
+        }
+        if (!dalloc((void **)&dn.w32, wv.size() * 8) || !dalloc((void **)&dn.A32, f32.size() * 4) || !dalloc((void **)&dn.Abf, nl * 2) ||
             !dalloc((void **)&dn.Ah, nl * 2) || !dalloc((void **)&dn.Al, nl * 2))
             return fail(TPF_ERR_OOM, "device allocation failed (network staging)");
-        if (!h2d(dn.A32, f32.data(), f32.size() * 4) || !h2d(dn.Abf, fbf.data(), nl * 2) ||
+        if (!h2d(dn.w32, wv.data(), wv.size() * 8) || !h2d(dn.A32, f32.data(), f32.size() * 4) || !h2d(dn.Abf, fbf.data(), nl * 2) ||
             !h2d(dn.Ah, fh.data(), nl * 2) || !h2d(dn.Al, fl.data(), nl * 2))
             return fail(TPF_ERR_DEVICE, "host-to-device copy failed (network staging)");
     }

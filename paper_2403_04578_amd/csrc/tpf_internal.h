@@ -16,12 +16,17 @@ namespace tpf {
 
 using cd = std::complex<double>;
 
-// Register-resident sweep kernels keep one 16-row MFMA tile per 8 PQ buses in
-// registers; MT = ceil(n / 8) tiles, n <= 8 * kMaxSmallTiles.
+// Register-resident sweep kernels: n <= 8 * kMaxSmallTiles.
 constexpr int kMaxSmallTiles = 40;
 
-// Workgroup shape of the register-resident kernels for MT row tiles: NW waves,
-// each owning at most TPW tiles (tile t belongs to wave role t % NW).
+// FP64: MT = ceil(n / 16) tiles of 16 buses over NW waves, at most TPW each; no more waves
+// than tiles, so that small networks pay for fewer waves at their barriers.
+inline void f64_config(int MT, int &NW, int &TPW) {
+    NW = MT <= 4 ? MT : 8;
+    TPW = (MT + NW - 1) / NW;
+}
+// FP32 and mixed: one 16-row MFMA tile per 8 PQ buses, MT = ceil(n / 8) row tiles, NW
+// waves, each owning at most TPW tiles (tile t belongs to wave role t % NW).
 inline void rows_config(int MT, int &NW, int &TPW) {
     NW = MT <= 4 ? 4 : 8;
     TPW = (MT + NW - 1) / NW;
@@ -38,15 +43,17 @@ constexpr int kFragPadSteps = 4;
 // Device copies of a network, made on first use on each device.
 struct DeviceNet {
     int device = -1;
-    int MT = 0;                  // 16-row tiles of the real-block operator (small-n kernels)
-    int NW = 0, TPW = 0;         // workgroup shape (rows_config)
-    double *A64 = nullptr;       // FP64 MFMA A fragments, [NW roles][4*MT+pad k-steps][TPW tiles][64 lanes]
-    double *w64 = nullptr;       // [2][8*MT]: Re w then Im w per bus (padding buses: 1, 0)
+    int MT = 0;                  // 16-row tiles of the real-block operator (FP32-family kernels)
+    int NW = 0, TPW = 0;         // their workgroup shape (rows_config)
+    int MT64 = 0;                // 16-bus tiles of the FP64 kernel
+    double *A64 = nullptr;       // FP64 MFMA A fragments of Z, [tiles][ceil(n/4)+pad k-steps][64 lanes][Re, Im]
+    double *w64 = nullptr;       // [2][16 MT64]: Re w then Im w per bus (padding buses: 1, 0)
     // FP32-family kernels (FP32 and mixed modes), n <= 128.  Rows/cols use the order
     // of the FP32/BF16/FP16 MFMA output (lane group g holds tile rows 4g..4g+3):
     // row 16 t + 2 (q % 8) + part for PQ bus q = 8 t + (q % 8).
     int KTL = 0;                 // 32-wide k-steps of the 16-bit products (K padded to 32 KTL)
     int sZ = 0;                  // power-of-two scale of Z in the FP16 operands
+    double *w32 = nullptr;       // [2][8*MT]: Re w then Im w per bus (padding buses: 1, 0)
     float *A32 = nullptr;        // FP32 fragments, [NW][4*MT+pad][TPW][64]
     uint16_t *Abf = nullptr;     // BF16 fragments, [NW][TPW][KTL][64][8]
     uint16_t *Ah = nullptr;      // FP16 fragments of Z 2^sZ, [NW][TPW][KTL][64][8]
