@@ -1,60 +1,28 @@
-// Sweep path for networks too large for the register-resident kernels (the dense
+// FP32 and mixed sweeps of networks too large for the register-resident kernels (the dense
 // operator no longer fits one workgroup): every sweep of Algorithm 1 runs as
 //   inject  I = conj(S./V) for the active columns (Eq. (3)), written as the B operand
 //           [active][K] with K = interleaved Re/Im per bus;
-//   gemm    V' = Z I + w on MFMA (64 x 64 output tiles, K staged through LDS), whose
-//           epilogue updates the state in place and reduces max |V' - V| per column
-//           with atomics;
-//   finish  chunks of 256 active columns: sweep count, stopping rule, retirement to the
+//   gemm    U' = Z I on MFMA (K staged through LDS), whose epilogue updates the state, the
+//           FP32 drop U = V - w, in place and reduces max |U' - U| per column with atomics;
+//   finish  chunks of active columns: sweep count, stopping rule, retirement to the
 //           output, compaction of the active list for the next sweep and the next
 //           sweep's injection (the first sweep's comes from its own kernel).
-// FP64 mode keeps the state V in FP64; FP32 mode keeps the FP32 drop U = V - w.  Every
-// sweep is queued without waiting on the device: the active counts stay there.
-#include "tpf_internal.h"
-
-#include <algorithm>
+// Every sweep is queued without waiting on the device: the active counts stay there.
+#include "large_common.h"
 
 namespace tpf {
 
-typedef double d4x __attribute__((ext_vector_type(4)));
 typedef float f4x __attribute__((ext_vector_type(4)));
 
 namespace {
 
-template <typename T>
-struct Acc;
-template <>
-struct Acc<double> {
-    typedef d4x v4;
-    __device__ static v4 mma(double a, double b, v4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-    // FP64 16x16x4 output: lane group g holds tile rows g + 4 r
-    __device__ static int row(int g, int r) { return g + 4 * r; }
-};
-template <>
-struct Acc<float> {
-    typedef f4x v4;
-    __device__ static v4 mma(float a, float b, v4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    // FP32 16x16x4 output: lane group g holds tile rows 4 g + r
-    __device__ static int row(int g, int r) { return 4 * g + r; }
-};
-
-// Row r of the operator (output order) -> (bus, part).  FP64: 16-row tiles of 8 buses,
-// Re in rows 0-7, Im in rows 8-15 (so a lane holds both parts of a bus); FP32:
-// interleaved Re/Im.  The K order is always interleaved.
-template <typename T>
-__device__ __forceinline__ void row_bus(int r, int &bus, int &part) {
-    if constexpr (sizeof(T) == 8) {
-        bus = 8 * (r >> 4) + (r & 7);
-        part = (r >> 3) & 1;
-    } else {
-        bus = r >> 1;
-        part = r & 1;
-    }
+__device__ __forceinline__ f4x mma32(float a, float b, const f4x &c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// State x[col][2 n]: FP64 mode holds V, FP32 mode holds U = V - w.
-template <typename T, typename IO>
-__global__ void init_kernel(const IO *__restrict__ V0, const double *__restrict__ w, int n, long long tau, T *x,
+// State x[col][2 n] = U = V - w.
+template <typename IO>
+__global__ void init_kernel(const IO *__restrict__ V0, const double *__restrict__ w, int n, long long tau, float *x,
                             int32_t *iters, long long *act, int *na, unsigned long long *dmax) {
     const long long c = blockIdx.x * 4LL + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -70,13 +38,8 @@ __global__ void init_kernel(const IO *__restrict__ V0, const double *__restrict_
     for (int b = lane; b < n; b += 64) {
         double vr = 1.0, vi = 0.0;
         if (ok) vr = (double)V0[2 * (c * n + b)], vi = (double)V0[2 * (c * n + b) + 1];
-        if constexpr (sizeof(T) == 8) {
-            x[2 * (c * n + b)] = vr;
-            x[2 * (c * n + b) + 1] = vi;
-        } else {
-            x[2 * (c * n + b)] = (T)(vr - w[2 * b]);
-            x[2 * (c * n + b) + 1] = (T)(vi - w[2 * b + 1]);
-        }
+        x[2 * (c * n + b)] = (float)(vr - w[2 * b]);
+        x[2 * (c * n + b) + 1] = (float)(vi - w[2 * b + 1]);
     }
     if (lane == 0) {
         iters[c] = 0;
@@ -86,24 +49,18 @@ __global__ void init_kernel(const IO *__restrict__ V0, const double *__restrict_
     }
 }
 
-// ZIP shares of Eq. (2) per PQ bus: all NULL for constant-power loads; aZ NULL when no
-// bus has a constant-impedance share.
-struct ZipShares {
-    const double *aP, *aI, *aZ;
-};
-
 // I = conj(S./V), or for ZIP loads alpha_P conj(S./V) + alpha_I conj(S) + alpha_Z conj(S) V
 // (the constant-impedance current, carried in the injection: the same fixed point as
 // eliminating diag(alpha_Z s*) into Y_dd), at bus b of column c; zero on the K padding.
-template <typename T, typename IO>
-__device__ __forceinline__ void injection_at(const IO *__restrict__ S, const T *__restrict__ x,
+template <typename IO>
+__device__ __forceinline__ void injection_at(const IO *__restrict__ S, const float *__restrict__ x,
                                              const double *__restrict__ w, int n, long long c, int b,
-                                             const ZipShares zs, T &ir, T &ii) {
+                                             const ZipShares zs, float &ir, float &ii) {
     ir = 0, ii = 0;
     if (b >= n) return;
     const double sr = (double)S[2 * (c * n + b)], si = (double)S[2 * (c * n + b) + 1];
     double vr = (double)x[2 * (c * n + b)], vi = (double)x[2 * (c * n + b) + 1];
-    if constexpr (sizeof(T) == 4) vr += w[2 * b], vi += w[2 * b + 1];
+    vr += w[2 * b], vi += w[2 * b + 1];
     const double inv = 1.0 / (vr * vr + vi * vi);
     double jr = (sr * vr + si * vi) * inv, ji = (sr * vi - si * vr) * inv;
     if (zs.aP) {
@@ -116,41 +73,38 @@ __device__ __forceinline__ void injection_at(const IO *__restrict__ S, const T *
             ji += az * (sr * vi - si * vr);
         }
     }
-    ir = (T)jr;
-    ii = (T)ji;
+    ir = (float)jr;
+    ii = (float)ji;
 }
 
 // The first sweep's B operand [rows][KP]: row a = injection of column act[a] (zero past na).
-template <typename T, typename IO>
-__global__ void inject_kernel(const IO *__restrict__ S, const T *__restrict__ x, const double *__restrict__ w, int n,
+template <typename IO>
+__global__ void inject_kernel(const IO *__restrict__ S, const float *__restrict__ x, const double *__restrict__ w, int n,
                               int KP, const long long *__restrict__ act, const int *__restrict__ na, int rows,
-                              const ZipShares zs, T *__restrict__ B) {
+                              const ZipShares zs, float *__restrict__ B) {
     const long long total = (long long)rows * KP;
     const int nact = *na;
     for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total / 2;
          e += (long long)gridDim.x * blockDim.x) {
         const long long a = e / (KP / 2);
         const int b = (int)(e - a * (KP / 2));
-        T ir = 0, ii = 0;
-        if (a < nact) injection_at<T, IO>(S, x, w, n, act[a], b, zs, ir, ii);
+        float ir = 0, ii = 0;
+        if (a < nact) injection_at<IO>(S, x, w, n, act[a], b, zs, ir, ii);
         B[a * KP + 2 * b] = ir;
         B[a * KP + 2 * b + 1] = ii;
     }
 }
 
 // C tile [64 rows][64 active columns] = A[rows][K] B[cols][K]^T; epilogue on the state.
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_kernel(const T *__restrict__ A, int KP, const T *__restrict__ B,
+__global__ __launch_bounds__(256) void gemm_kernel(const float *__restrict__ A, int KP, const float *__restrict__ B,
                                                    const long long *__restrict__ act, const int *__restrict__ na,
                                                    int row_blocks, const double *__restrict__ w, int n,
-                                                   T *__restrict__ x, unsigned long long *__restrict__ dmax,
+                                                   float *__restrict__ x, unsigned long long *__restrict__ dmax,
                                                    int *__restrict__ badf) {
-    using Ops = Acc<T>;
-    typedef typename Ops::v4 v4;
     const int nact = *na;
     const int ct = (nact + 63) / 64;
-    __shared__ T As[2][64][17];  // two buffers: the next k-slab lands while this one is used
-    __shared__ T Bs[2][64][17];
+    __shared__ float As[2][64][17];  // two buffers: the next k-slab lands while this one is used
+    __shared__ float Bs[2][64][17];
     __shared__ double red[2][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, j = lane & 15;
@@ -159,18 +113,18 @@ __global__ __launch_bounds__(256) void gemm_kernel(const T *__restrict__ A, int 
     // With A small enough to stay in L2 the row blocks of a column tile run back to back
     // (its B slab is fetched from HBM about once); otherwise column tiles run fastest and
     // the resident blocks share A's row block.
-    const bool rows_fast = (size_t)row_blocks * 64 * KP * sizeof(T) <= ((size_t)2 << 20);
+    const bool rows_fast = (size_t)row_blocks * 64 * KP * sizeof(float) <= ((size_t)2 << 20);
     for (int t = blockIdx.x; t < ct * row_blocks; t += gridDim.x) {
         const int c0 = (rows_fast ? t / row_blocks : t % ct) * 64;
         const int r0 = (rows_fast ? t % row_blocks : t / ct) * 64;
-        v4 acc[2][2];
+        f4x acc[2][2];
         for (int a = 0; a < 2; ++a)
-            for (int b = 0; b < 2; ++b) acc[a][b] = v4{0, 0, 0, 0};
+            for (int b = 0; b < 2; ++b) acc[a][b] = f4x{0, 0, 0, 0};
         const int rr = tid >> 2, kk = (tid & 3) * 4;
-        const T *Ap = A + (size_t)(r0 + rr) * KP + kk, *Bp = B + (size_t)(c0 + rr) * KP + kk;
+        const float *Ap = A + (size_t)(r0 + rr) * KP + kk, *Bp = B + (size_t)(c0 + rr) * KP + kk;
         // the next k-slab is fetched into registers while the current one is multiplied
-        T pa0 = Ap[0], pa1 = Ap[1], pa2 = Ap[2], pa3 = Ap[3];
-        T pb0 = Bp[0], pb1 = Bp[1], pb2 = Bp[2], pb3 = Bp[3];
+        float pa0 = Ap[0], pa1 = Ap[1], pa2 = Ap[2], pa3 = Ap[3];
+        float pb0 = Bp[0], pb1 = Bp[1], pb2 = Bp[2], pb3 = Bp[3];
         As[0][rr][kk] = pa0, As[0][rr][kk + 1] = pa1, As[0][rr][kk + 2] = pa2, As[0][rr][kk + 3] = pa3;
         Bs[0][rr][kk] = pb0, Bs[0][rr][kk + 1] = pb1, Bs[0][rr][kk + 2] = pb2, Bs[0][rr][kk + 3] = pb3;
         __syncthreads();
@@ -184,7 +138,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(const T *__restrict__ A, int 
             }
     #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
-                T af[2], bf[2];
+                float af[2], bf[2];
     #pragma unroll
                 for (int a = 0; a < 2; ++a) af[a] = As[buf][wr + 16 * a + j][4 * ks + g];
     #pragma unroll
@@ -192,18 +146,17 @@ __global__ __launch_bounds__(256) void gemm_kernel(const T *__restrict__ A, int 
     #pragma unroll
                 for (int a = 0; a < 2; ++a)
     #pragma unroll
-                    for (int b = 0; b < 2; ++b) acc[a][b] = Ops::mma(af[a], bf[b], acc[a][b]);
+                    for (int b = 0; b < 2; ++b) acc[a][b] = mma32(af[a], bf[b], acc[a][b]);
             }
             if (more) {  // the other buffer: its last readers passed the previous barrier
-                T *as = &As[buf ^ 1][rr][kk], *bs = &Bs[buf ^ 1][rr][kk];
+                float *as = &As[buf ^ 1][rr][kk], *bs = &Bs[buf ^ 1][rr][kk];
                 as[0] = pa0, as[1] = pa1, as[2] = pa2, as[3] = pa3;
                 bs[0] = pb0, bs[1] = pb1, bs[2] = pb2, bs[3] = pb3;
             }
             __syncthreads();
             buf ^= 1;
         }
-        // epilogue: each lane holds both parts of two buses (FP64 layout) or of two buses
-        // (FP32 interleaved layout: rows 4g..4g+3 = Re/Im of two buses) of column j
+        // epilogue: lane group g holds rows 4g..4g+3 = Re/Im of two buses of column j
     #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const int ac = c0 + wc + 16 * b + j;
@@ -216,20 +169,16 @@ __global__ __launch_bounds__(256) void gemm_kernel(const T *__restrict__ A, int 
                 const int tile0 = r0 + wr + 16 * a;
     #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    // the two registers holding Re and Im of one bus
-                    const int rre = sizeof(T) == 8 ? h : 2 * h, rim = sizeof(T) == 8 ? h + 2 : 2 * h + 1;
-                    int bus, part;
-                    row_bus<T>(tile0 + Ops::row(g, rre), bus, part);
+                    const int bus = (tile0 + 4 * g + 2 * h) >> 1;
                     if (live && bus < n) {
-                        const double nr = (double)acc[a][b][rre] + (sizeof(T) == 8 ? w[2 * bus] : 0.0);
-                        const double ni = (double)acc[a][b][rim] + (sizeof(T) == 8 ? w[2 * bus + 1] : 0.0);
-                        T *xp = x + 2 * (c * n + bus);
+                        const double nr = (double)acc[a][b][2 * h], ni = (double)acc[a][b][2 * h + 1];
+                        float *xp = x + 2 * (c * n + bus);
                         const double dr = nr - (double)xp[0], di = ni - (double)xp[1];
                         const double e2 = dr * dr + di * di;
                         bad |= !(e2 < HUGE_VAL);
                         emax = e2 > emax ? e2 : emax;
-                        xp[0] = (T)nr;
-                        xp[1] = (T)ni;
+                        xp[0] = (float)nr;
+                        xp[1] = (float)ni;
                     }
                 }
             }
@@ -250,31 +199,6 @@ __global__ __launch_bounds__(256) void gemm_kernel(const T *__restrict__ A, int 
     }
 }
 
-// Tells the host that queues the sweeps that none is left to do (a store to pinned host
-// memory, visible to the host without any wait on the device).
-__device__ __forceinline__ void post_done(int *done_flag, int seq) {
-    if (done_flag) __hip_atomic_store(done_flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-// Places of the staying columns of a chunk in the next list: a rank from the
-// block's ballots and one atomic per chunk (a counter shared by every column of the sweep
-// would serialise a million atomics).  Returns the slot, or -1 when `stay` is false.
-__device__ __forceinline__ int chunk_slot(bool stay, int *counter, int *wsum, int *base) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const unsigned long long m = __ballot(stay);
-    const int rank = __popcll(m & ((1ull << lane) - 1ull));
-    if (lane == 0) wsum[wave] = __popcll(m);
-    __syncthreads();
-    if (tid == 0) {
-        const int tot = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        *base = tot ? atomicAdd(counter, tot) : 0;
-    }
-    __syncthreads();
-    int off = *base;
-    for (int w = 0; w < wave; ++w) off += wsum[w];
-    return stay ? off + rank : -1;
-}
-
 // Chunks of cpb active columns (a power of two, 4 to 256: fewer for wider networks, so
 // that the per-column work of the second phase spreads over enough wavefronts): one
 // thread per column for the convergence test (Eq. (3))
@@ -282,13 +206,13 @@ __device__ __forceinline__ int chunk_slot(bool stay, int *counter, int *wsum, in
 // for the outputs of a retired one or the next sweep's B row (injection) of a staying
 // one.  `cnt_next` was cleared a sweep earlier; `cnt_clear` (the count two sweeps back,
 // read by no kernel still to run) is cleared for the sweep after next.
-template <typename T, typename IO>
+template <typename IO>
 __global__ __launch_bounds__(256) void finish_kernel(
     const long long *__restrict__ act, const int *__restrict__ cnt, int *cnt_clear, const IO *__restrict__ S,
-    const T *__restrict__ x, const double *__restrict__ w, int n, int KP, const ZipShares zs, double tol,
+    const float *__restrict__ x, const double *__restrict__ w, int n, int KP, const ZipShares zs, double tol,
     int max_iter, unsigned long long *__restrict__ dmax,
     const int *__restrict__ badf, int32_t *iters, int8_t *status, IO *__restrict__ V,
-    long long *__restrict__ act_next, int *cnt_next, T *__restrict__ B, int *done_flag, int seq, int cpb) {
+    long long *__restrict__ act_next, int *cnt_next, float *__restrict__ B, int *done_flag, int seq, int cpb) {
     __shared__ long long col_s[256];
     __shared__ int slot_s[256];
     __shared__ int wsum[4], base_s;
@@ -326,15 +250,15 @@ __global__ __launch_bounds__(256) void finish_kernel(
             if (sl < 0) {
                 for (int b = lane; b < n; b += 64) {
                     double vr = (double)x[2 * (cc * n + b)], vi = (double)x[2 * (cc * n + b) + 1];
-                    if constexpr (sizeof(T) == 4) vr += w[2 * b], vi += w[2 * b + 1];
+                    vr += w[2 * b], vi += w[2 * b + 1];
                     V[2 * (cc * n + b)] = (IO)vr;
                     V[2 * (cc * n + b) + 1] = (IO)vi;
                 }
             } else {
-                T *Br = B + (long long)sl * KP;
+                float *Br = B + (long long)sl * KP;
                 for (int b = lane; b < KP / 2; b += 64) {
-                    T ir, ii;
-                    injection_at<T, IO>(S, x, w, n, cc, b, zs, ir, ii);
+                    float ir, ii;
+                    injection_at<IO>(S, x, w, n, cc, b, zs, ir, ii);
                     Br[2 * b] = ir;
                     Br[2 * b + 1] = ii;
                 }
@@ -761,13 +685,6 @@ __global__ __launch_bounds__(256) void finish_mixed_kernel(
 
 }  // namespace
 
-// Whether a sweep of solve `seq` already found every column retired: the sweeps queued
-// after it would all exit at once, so the host queues no more.  A read of pinned host
-// memory; it never waits for the device.
-static bool all_retired(const DeviceNet &dn, int seq) {
-    return dn.done_host && __atomic_load_n(dn.done_host, __ATOMIC_ACQUIRE) == seq;
-}
-
 // Columns per finish chunk: about 16,384 buses' worth, a power of two in [4, 256] (one
 // atomic per chunk keeps a million-column sweep from serialising on the list counter,
 // and small chunks keep a few wide columns spread over many wavefronts).
@@ -777,36 +694,16 @@ static int finish_chunk(int n) {
     return c;
 }
 
-// Fixed grids of the queued sweeps: enough blocks to fill the chip, few enough that a
-// sweep with nothing left to do costs little.
-constexpr int64_t kGemmGrid = 1024, kFinishGrid = 1024;
-
-// Grid of a persistent GEMM: at most kGemmGrid blocks and no more than are resident at
-// once (CUs x blocks per CU).  Its blocks share the tiles evenly, so blocks beyond the
-// resident ones would start only after others had finished all of theirs and run the
-// kernel's second half at a fraction of the occupancy (the 16-bit GEMM, three blocks per
-// CU for its 43 KB of LDS, took twice as long with 1,024 blocks).
-template <typename Kernel>
-static int64_t gemm_grid(Kernel kernel, int64_t tiles) {
-    int dev = 0, cus = 256, per_cu = 0;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, 256, 0) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    return std::max<int64_t>(1, std::min<int64_t>({kGemmGrid, (int64_t)cus * per_cu, tiles}));
-}
-
-// Workspace of the large path: state [tau][2n] (T), B operand [tau rounded to 64][KP] (T),
+// Workspace of the large path: state [tau][2n], B operand [tau rounded to 64][KP] (FP32),
 // dmax [tau] (u64), bad flags [tau] (int), two active lists [tau] (i64), counters.
 // Mixed modes add I_prev [tau][2n] (FP32), the 16-bit B operand [tau rounded to 128][KP16],
 // per-column schedule state and max |U| [tau], and two more active lists.
 size_t large_workspace_bytes(int n, int64_t tau, int mode) {
-    const size_t ts = mode == TPF_MODE_FP64 ? 8 : 4;
+    if (mode == TPF_MODE_FP64) return large64_workspace(n, tau);
     const size_t KP = (size_t)(2 * n + 15) / 16 * 16;
     const size_t rows = (size_t)(tau + 63) / 64 * 64;
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-    size_t bytes = al((size_t)tau * 2 * n * ts) + al(rows * KP * ts) + al((size_t)tau * 8) + al((size_t)tau * 4) +
+    size_t bytes = al((size_t)tau * 2 * n * 4) + al(rows * KP * 4) + al((size_t)tau * 8) + al((size_t)tau * 4) +
                    2 * al((size_t)tau * 8) + 256;
     if (mode == TPF_MODE_MIXED_BF16 || mode == TPF_MODE_MIXED_FP16) {
         const size_t K16 = (size_t)(2 * n + 31) / 32 * 32, rows16 = (size_t)(tau + 127) / 128 * 128;
@@ -816,20 +713,20 @@ size_t large_workspace_bytes(int n, int64_t tau, int mode) {
     return bytes;
 }
 
-template <typename T, typename IO>
+template <typename IO>
 static int run_large(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                      int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, void *ws,
                      hipStream_t st) {
     const int n = net.n;
     const int KP = (2 * n + 15) / 16 * 16;
     const int64_t rows = (tau + 63) / 64 * 64;
-    const int MP = sizeof(T) == 8 ? dn.MPL64 : dn.MPL32;
+    const int MP = dn.MPL32;
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     char *p = static_cast<char *>(ws);
-    T *x = reinterpret_cast<T *>(p);
-    p += al((size_t)tau * 2 * n * sizeof(T));
-    T *B = reinterpret_cast<T *>(p);
-    p += al((size_t)rows * KP * sizeof(T));
+    float *x = reinterpret_cast<float *>(p);
+    p += al((size_t)tau * 2 * n * sizeof(float));
+    float *B = reinterpret_cast<float *>(p);
+    p += al((size_t)rows * KP * sizeof(float));
     auto *dmax = reinterpret_cast<unsigned long long *>(p);
     p += al((size_t)tau * 8);
     int *badf = reinterpret_cast<int *>(p);
@@ -840,21 +737,21 @@ static int run_large(const tpf_network_s &net, const DeviceNet &dn, const void *
     act[1] = reinterpret_cast<long long *>(p);
     p += al((size_t)tau * 8);
     int *cnt = reinterpret_cast<int *>(p);  // three active counts in rotation
-    const T *A = sizeof(T) == 8 ? (const T *)(const void *)dn.AL64 : (const T *)(const void *)dn.AL32;
+    const float *A = dn.AL32;
     const double *w = dn.wl;
     hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)std::min<int64_t>(65536, (tau + 255) / 256)), dim3(256), 0, st,
                        badf, (long long)tau);
     hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, st, cnt, 3LL);
-    hipLaunchKernelGGL((init_kernel<T, IO>), dim3((unsigned)((tau + 3) / 4)), dim3(256), 0, st, (const IO *)V0, w, n,
+    hipLaunchKernelGGL((init_kernel<IO>), dim3((unsigned)((tau + 3) / 4)), dim3(256), 0, st, (const IO *)V0, w, n,
                        (long long)tau, x, iters, act[0], cnt, dmax);
-    hipLaunchKernelGGL((inject_kernel<T, IO>), dim3((unsigned)std::min<long long>(65536, (rows * KP / 2 + 255) / 256)),
+    hipLaunchKernelGGL((inject_kernel<IO>), dim3((unsigned)std::min<long long>(65536, (rows * KP / 2 + 255) / 256)),
                        dim3(256), 0, st, (const IO *)S, x, w, n, KP, act[0], cnt, (int)rows, ZipShares{dn.aP, dn.aI, dn.aZ}, B);
     // Every sweep is queued without waiting, with grids fixed from tau: the active counts
     // stay on the device (three of them in rotation: read, appended, cleared) and the
     // kernels of a sweep with no active column exit at once.  Queueing stops early when
     // the device has already posted that none is left (all_retired).
     const int row_blocks = MP / 64;
-    const unsigned g_mm = (unsigned)gemm_grid(gemm_kernel<T>, (int64_t)row_blocks * (rows / 64));
+    const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm_kernel, 256, (int64_t)row_blocks * (rows / 64));
     const int cpb = finish_chunk(n);
     const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + cpb - 1) / cpb);
     const int seq = ++dn.solve_seq;
@@ -862,9 +759,9 @@ static int run_large(const tpf_network_s &net, const DeviceNet &dn, const void *
         if (all_retired(dn, seq)) break;
         const int cur = sweep & 1;
         int *cr = cnt + sweep % 3, *cn = cnt + (sweep + 1) % 3, *cz = cnt + (sweep + 2) % 3;
-        hipLaunchKernelGGL((gemm_kernel<T>), dim3(g_mm), dim3(256), 0, st, A, KP, B, act[cur], cr, row_blocks, w, n, x,
+        hipLaunchKernelGGL((gemm_kernel), dim3(g_mm), dim3(256), 0, st, A, KP, B, act[cur], cr, row_blocks, w, n, x,
                            dmax, badf);
-        hipLaunchKernelGGL((finish_kernel<T, IO>), dim3(g_fin), dim3(256), 0, st, act[cur], cr, cz, (const IO *)S, x, w,
+        hipLaunchKernelGGL((finish_kernel<IO>), dim3(g_fin), dim3(256), 0, st, act[cur], cr, cz, (const IO *)S, x, w,
                            n, KP, ZipShares{dn.aP, dn.aI, dn.aZ}, tol, max_iter, dmax, badf, iters, status, (IO *)V, act[cur ^ 1], cn,
                            B, dn.done_dev, seq, cpb);
     }
@@ -913,7 +810,7 @@ static int run_large_mixed(const tpf_network_s &net, const DeviceNet &dn, const 
     hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)std::min<int64_t>(65536, (tau + 255) / 256)), dim3(256), 0, st,
                        badf, (long long)tau);
     hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, st, cnt, 6LL);
-    hipLaunchKernelGGL((init_kernel<float, IO>), dim3((unsigned)((tau + 3) / 4)), dim3(256), 0, st, (const IO *)V0, w,
+    hipLaunchKernelGGL((init_kernel<IO>), dim3((unsigned)((tau + 3) / 4)), dim3(256), 0, st, (const IO *)V0, w,
                        n, (long long)tau, U, iters, actL[0], cnt, dmax);
     hipLaunchKernelGGL((init_mix_kernel<MODE, IO>), dim3((unsigned)((tau + 3) / 4)), dim3(256), 0, st, (const IO *)S,
                        n, (long long)tau, dn.sZ, dn.aP ? dn.zscale : 1.0f, ms, umax);
@@ -922,8 +819,8 @@ static int run_large_mixed(const tpf_network_s &net, const DeviceNet &dn, const 
                        (const IO *)S, U, w, Ip, ms, n, K16, actL[0], cnt, (int)rows16, ZipShares{dn.aP, dn.aI, dn.aZ},
                        reinterpret_cast<uint32_t *>(B16));
     // Queued at once as in run_large; counts in pairs {low, refine}, three pairs in rotation.
-    const unsigned g_r = (unsigned)gemm_grid(gemm_kernel<float>, (int64_t)(MP / 64) * (rows / 64));
-    const unsigned g_l = (unsigned)gemm_grid(gemm_low_kernel<MODE>, (int64_t)(MP / 128) * (rows16 / 128));
+    const unsigned g_r = (unsigned)gemm_grid((const void *)gemm_kernel, 256, (int64_t)(MP / 64) * (rows / 64));
+    const unsigned g_l = (unsigned)gemm_grid((const void *)gemm_low_kernel<MODE>, 256, (int64_t)(MP / 128) * (rows16 / 128));
     const int cpb = finish_chunk(n);
     const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + cpb - 1) / cpb);
     const int seq = ++dn.solve_seq;
@@ -932,7 +829,7 @@ static int run_large_mixed(const tpf_network_s &net, const DeviceNet &dn, const 
         const int cur = sweep & 1;
         int *cc = cnt + 2 * (sweep % 3), *cn = cnt + 2 * ((sweep + 1) % 3), *cz = cnt + 2 * ((sweep + 2) % 3);
         if (sweep > 0)  // the first sweep has no refine list
-            hipLaunchKernelGGL((gemm_kernel<float>), dim3(g_r), dim3(256), 0, st, dn.AL32, KP, B32, actR[cur], cc + 1,
+            hipLaunchKernelGGL((gemm_kernel), dim3(g_r), dim3(256), 0, st, dn.AL32, KP, B32, actR[cur], cc + 1,
                                MP / 64, w, n, U, dmax, badf);
         hipLaunchKernelGGL((gemm_low_kernel<MODE>), dim3(g_l), dim3(256), 0, st, A16, K16, B16, actL[cur], cc, ms, n,
                            U, dmax, umax, badf, MP / 128);
@@ -947,13 +844,12 @@ static int run_large_mixed(const tpf_network_s &net, const DeviceNet &dn, const 
 int launch_fpi_large(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype, int64_t tau,
                      double tol, int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, void *ws,
                      hipStream_t st) {
-    if (!dn.AL64) return fail(TPF_ERR_UNSUPPORTED, "large-network operator not staged");
     if (mode == TPF_MODE_FP64)
-        return dtype == TPF_C128 ? run_large<double, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st)
-                                 : run_large<double, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st);
+        return launch_fpi_large64(net, dn, S, dtype, tau, tol, max_iter, V0, V, iters, status, ws, st);
+    if (!dn.AL32) return fail(TPF_ERR_UNSUPPORTED, "large-network operator not staged");
     if (mode == TPF_MODE_FP32)
-        return dtype == TPF_C128 ? run_large<float, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st)
-                                 : run_large<float, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st);
+        return dtype == TPF_C128 ? run_large<double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st)
+                                 : run_large<float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st);
     if (!dn.ALbf) return fail(TPF_ERR_UNSUPPORTED, "16-bit large-network operator not staged");
     if (mode == TPF_MODE_MIXED_BF16)
         return dtype == TPF_C128

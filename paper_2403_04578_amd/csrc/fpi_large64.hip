@@ -1,0 +1,450 @@
+// FP64 sweeps of networks too large for the register-resident kernel (the dense operator no
+// longer fits one workgroup): each sweep of Algorithm 1 is one product kernel, whose
+// epilogue updates the state and forms the next sweep's injection, and one kernel that
+// applies the stopping rule and rebuilds the list of active columns.  Every sweep is queued
+// without waiting on the device: the active counts stay there.
+#include "large_common.h"
+
+namespace tpf {
+
+typedef double d4x __attribute__((ext_vector_type(4)));
+
+namespace {
+
+__device__ __forceinline__ d4x mma64(double a, double b, const d4x &c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// ---- FP64 sweeps
+//
+// The complex product V' = Z I + w as three real ones,
+//     m1 = Zr Ir, m2 = Zi Ii, m3 = (Zr - Zi)(Ir - Ii);  Re = m1 - m2, Im = m1 + m2 - m3
+// (as in the register-resident kernel: a quarter fewer FP64 matrix products), and the next
+// sweep's injection formed by the lane that holds the new voltage, so that between two
+// products only the lists of active columns are rebuilt.  The operand B[column][KB] is kept
+// per column, not per place in the list, in two copies used in turn: a sweep writes one
+// while other tiles still read the other.  The state x is V itself, and for complex128 it
+// is the caller's output array where that can be: a column that retires is in place already.
+
+typedef double d2x __attribute__((ext_vector_type(2)));
+
+// I = conj(S./V) (or the ZIP form) from the new voltage of bus b.
+__device__ __forceinline__ d2x injection64(double sr, double si, double vr, double vi, int b, const ZipShares &zs) {
+    const double inv = 1.0 / (vr * vr + vi * vi);
+    const double pr = sr * vr + si * vi, pi = sr * vi - si * vr;
+    double jr = pr * inv, ji = pi * inv;
+    if (zs.aP) {
+        const double ap = zs.aP[b], ai = zs.aI[b];
+        jr = ap * jr + ai * sr;
+        ji = ap * ji - ai * si;
+        if (zs.aZ) {
+            const double az = zs.aZ[b];
+            jr += az * pr;
+            ji += az * pi;
+        }
+    }
+    return d2x{jr, ji};
+}
+
+// Start voltages (guarded V0 or flat) into x and the first injections into B0; zeroes the
+// K padding of both copies of B, the column maxima and the sweep counts.  One wave per column.
+template <typename IO>
+__global__ void start64_kernel(const IO *__restrict__ S, const IO *__restrict__ V0, int n, int KB, long long tau,
+                               const ZipShares zs, double *__restrict__ x, d2x *__restrict__ B0,
+                               d2x *__restrict__ B1, int32_t *__restrict__ iters, long long *__restrict__ act,
+                               int *__restrict__ cnt, unsigned long long *__restrict__ dmax) {
+    const long long c = blockIdx.x * 4LL + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (c >= tau) return;
+    int ok = V0 != nullptr;
+    if (V0)
+        for (int b = lane; b < n; b += 64) {
+            const double vr = (double)V0[2 * (c * n + b)], vi = (double)V0[2 * (c * n + b) + 1];
+            const double m2 = vr * vr + vi * vi;
+            ok &= (m2 >= 0.25 && m2 <= 2.25) ? 1 : 0;
+        }
+    for (int off = 32; off > 0; off >>= 1) ok &= __shfl_xor(ok, off);
+    for (int b = lane; b < KB; b += 64) {
+        d2x inj = d2x{0.0, 0.0};
+        if (b < n) {
+            double vr = 1.0, vi = 0.0;
+            if (ok) vr = (double)V0[2 * (c * n + b)], vi = (double)V0[2 * (c * n + b) + 1];
+            reinterpret_cast<d2x *>(x)[c * n + b] = d2x{vr, vi};
+            inj = injection64((double)S[2 * (c * n + b)], (double)S[2 * (c * n + b) + 1], vr, vi, b, zs);
+        } else {
+            B1[c * KB + b] = inj;
+        }
+        B0[c * KB + b] = inj;
+    }
+    if (lane == 0) {
+        iters[c] = 0;
+        act[c] = c;
+        dmax[c] = 0ull;
+        if (c < 3) cnt[c] = c == 0 ? (int)tau : 0;
+        if (c == 0 && tau < 3)
+            for (int k = (int)tau; k < 3; ++k) cnt[k] = 0;
+    }
+}
+
+// One bus of one active column: V' = p + w, the step |V' - V|^2 into `dmax` (and NaN into
+// `poison` when it is not finite), V' into x and the next injection into Bn.
+template <typename IO>
+__device__ __forceinline__ void update64(double pr, double pi, d2x w, long long c, int bus, int n, int KB,
+                                         const IO *__restrict__ S, const ZipShares &zs, d2x old, double sr, double si,
+                                         double *__restrict__ x, d2x *__restrict__ Bn, double &dmax, double &poison) {
+    const double nr = pr + w.x, ni = pi + w.y;
+    const double dr = nr - old.x, di = ni - old.y;
+    const double e = dr * dr + di * di;
+    poison = __builtin_fma(e, 0.0, poison);
+    dmax = fmax(dmax, e);
+    reinterpret_cast<d2x *>(x)[c * n + bus] = d2x{nr, ni};
+    Bn[c * KB + bus] = injection64(sr, si, nr, ni, bus, zs);
+}
+
+// Tiles of 64 buses x 64 active columns, four waves of 32 x 32 (2 x 2 MFMA tiles, three
+// accumulators each).  A: fragments [tile of 16 buses][KT k-steps of 4 buses][64 lanes]
+// (Re, Im); k-slabs of two k-steps of both operands go through LDS in fragment order, two
+// buffers.  Bound by the FP64 matrix cores: 24 products (1,536 cycles) per wave and slab
+// against 8 KB of LDS reads; the epilogue's traffic (x, S in, x, B out) hides behind them.
+template <typename IO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gemm64_kernel(
+    const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
+    const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
+    const IO *__restrict__ S, const ZipShares zs, double *__restrict__ x, unsigned long long *__restrict__ dmax) {
+    const int nact = *na;
+    const int ct = (nact + 63) / 64;
+    __shared__ d2x As[2][4][128], Bs[2][4][128];  // [buffer][16-row or 16-column group][k-step, lane]
+    __shared__ unsigned long long red[64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 4, j = lane & 15;
+    const int wr = (wave >> 1) * 2, wc = (wave & 1) * 2;  // first row group, first column group
+    const bool rows_fast = (size_t)row_blocks * 64 * KB * 16 <= ((size_t)2 << 20);
+    for (int t = blockIdx.x; t < ct * row_blocks; t += gridDim.x) {
+        const int c0 = (rows_fast ? t / row_blocks : t % ct) * 64;
+        const int rb = rows_fast ? t % row_blocks : t / ct;
+        d4x m1[2][2], m2[2][2], m3[2][2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) m1[a][b] = m2[a][b] = m3[a][b] = d4x{0, 0, 0, 0};
+        if (tid < 64) red[tid] = 0ull;
+        // A: thread copies fragments tid and tid + 256 of the slab's 512; B: two buses of one column
+        const d2x *Ap = A + ((size_t)(4 * rb + (tid >> 7)) * KT) * 64 + (tid & 127);
+        const size_t a2 = (size_t)2 * KT * 64;
+        const int bc = tid >> 2, bk = 2 * (tid & 3);
+        const int slot = c0 + bc < nact ? c0 + bc : nact - 1;
+        const d2x *Bp = B + act[slot] * KB + bk;
+        d2x *bdst = &Bs[0][bc >> 4][64 * (bk >> 2) + 16 * (bk & 3) + (bc & 15)];
+        d2x *adst = &As[0][tid >> 7][tid & 127];
+        d2x pa0 = Ap[0], pa1 = Ap[a2], pb0 = Bp[0], pb1 = Bp[1];
+        adst[0] = pa0, adst[256] = pa1, bdst[0] = pb0, bdst[16] = pb1;
+        __syncthreads();
+        int buf = 0;
+        for (int s = 0; s < KT / 2; ++s) {
+            const bool more = 2 * s + 2 < KT;
+            if (more) {
+                Ap += 128;
+                Bp += 8;
+                pa0 = Ap[0], pa1 = Ap[a2], pb0 = Bp[0], pb1 = Bp[1];
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                d2x af[2], bf[2];
+                double as[2], bs[2];
+#pragma unroll
+                for (int a = 0; a < 2; ++a) af[a] = As[buf][wr + a][64 * k + lane], as[a] = af[a].x - af[a].y;
+#pragma unroll
+                for (int b = 0; b < 2; ++b) bf[b] = Bs[buf][wc + b][64 * k + lane], bs[b] = bf[b].x - bf[b].y;
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        m1[a][b] = mma64(af[a].x, bf[b].x, m1[a][b]);
+                        m2[a][b] = mma64(af[a].y, bf[b].y, m2[a][b]);
+                        m3[a][b] = mma64(as[a], bs[b], m3[a][b]);
+                    }
+            }
+            if (more) {  // the other buffer: its last readers passed the previous barrier
+                const int o = (buf ^ 1) * 512;
+                adst[o] = pa0, adst[o + 256] = pa1, bdst[o] = pb0, bdst[o + 16] = pb1;
+            }
+            __syncthreads();
+            buf ^= 1;
+        }
+        // lane (g, j) holds buses g + 4 r of the row groups, column j of the column groups
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int ac = c0 + 16 * (wc + b) + j;
+            const bool live = ac < nact;
+            const long long c = act[live ? ac : nact - 1];
+            double e = 0.0, poison = 0.0;
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const int bus0 = 64 * rb + 16 * (wr + a) + g;
+                d2x old[4];
+                double sr[4], si[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (live && bus0 + 4 * r < n) {
+                        old[r] = reinterpret_cast<const d2x *>(x)[c * n + bus0 + 4 * r];
+                        sr[r] = (double)S[2 * (c * n + bus0 + 4 * r)];
+                        si[r] = (double)S[2 * (c * n + bus0 + 4 * r) + 1];
+                    }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (live && bus0 + 4 * r < n)
+                        update64<IO>(m1[a][b][r] - m2[a][b][r], m1[a][b][r] + m2[a][b][r] - m3[a][b][r],
+                                     w[bus0 + 4 * r], c, bus0 + 4 * r, n, KB, S, zs, old[r], sr[r], si[r], x, Bn, e,
+                                     poison);
+            }
+            // non-negative doubles order like their bit patterns; ~0 marks a step that is not finite
+            if (live)
+                atomicMax(red + 16 * (wc + b) + j, poison == 0.0 ? (unsigned long long)__double_as_longlong(e) : ~0ull);
+        }
+        __syncthreads();
+        if (tid < 64 && c0 + tid < nact) atomicMax(dmax + act[c0 + tid], red[tid]);
+        __syncthreads();  // red is reused
+    }
+}
+
+// The same sweep for batches too small to fill the chip with 64 x 64 tiles: tiles of 16 TR
+// buses x 16 TC active columns, whose k-steps are shared out among the NW waves of a
+// workgroup; each wave multiplies its share straight from L2 (a register ring of kSplitRing
+// k-steps, no LDS and no barrier in the loop) and the partial sums meet in LDS.  Bound by the
+// latency of the operand loads, which is why the k-steps are split: one column of a 999-bus
+// feeder spends 63 tiles x 8 waves x 31 k-steps per sweep here, where sixteen 64 x 64 tiles
+// would each walk 125 slabs.
+constexpr int kSplitRing = 4;
+
+template <int TR, int TC, int NW, typename IO>
+__global__ __launch_bounds__(NW * 64) void gemm64_split_kernel(
+    const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
+    const long long *__restrict__ act, const int *__restrict__ na, int row_tiles, const d2x *__restrict__ w, int n,
+    const IO *__restrict__ S, const ZipShares zs, double *__restrict__ x, unsigned long long *__restrict__ dmax) {
+    const int nact = *na;
+    const int ct = (nact + 16 * TC - 1) / (16 * TC);
+    __shared__ d2x part[NW][TR * TC * 4][64];
+    __shared__ unsigned long long red[16 * TC];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, j = lane & 15;
+    const int k0 = wave * KT / NW, k1 = (wave + 1) * KT / NW;
+    for (int t = blockIdx.x; t < ct * row_tiles; t += gridDim.x) {
+        const int c0 = t / row_tiles * 16 * TC, rt = t % row_tiles * TR;
+        if (tid < 16 * TC) red[tid] = 0ull;
+        const d2x *Ap[TR], *Bp[TC];
+#pragma unroll
+        for (int a = 0; a < TR; ++a) Ap[a] = A + (size_t)(rt + a) * KT * 64 + lane;
+#pragma unroll
+        for (int b = 0; b < TC; ++b) {
+            const int slot = c0 + 16 * b + j;
+            Bp[b] = B + act[slot < nact ? slot : nact - 1] * KB + g;
+        }
+        d4x m1[TR][TC], m2[TR][TC], m3[TR][TC];
+#pragma unroll
+        for (int a = 0; a < TR; ++a)
+#pragma unroll
+            for (int b = 0; b < TC; ++b) m1[a][b] = m2[a][b] = m3[a][b] = d4x{0, 0, 0, 0};
+        d2x ra[kSplitRing][TR], rb[kSplitRing][TC];
+        auto fetch = [&](int u, int kt) __attribute__((always_inline)) {
+            const int k = kt < k1 ? kt : k1 - 1;  // past the share: a step already read
+#pragma unroll
+            for (int a = 0; a < TR; ++a) ra[u][a] = Ap[a][(size_t)k * 64];
+#pragma unroll
+            for (int b = 0; b < TC; ++b) rb[u][b] = Bp[b][4 * k];
+        };
+        if (k0 < k1) {
+#pragma unroll
+            for (int u = 0; u < kSplitRing; ++u) fetch(u, k0 + u);
+            for (int kt = k0; kt < k1; kt += kSplitRing) {
+#pragma unroll
+                for (int u = 0; u < kSplitRing; ++u) {
+                    if (kt + u < k1) {
+                        double as[TR], bs[TC];
+#pragma unroll
+                        for (int a = 0; a < TR; ++a) as[a] = ra[u][a].x - ra[u][a].y;
+#pragma unroll
+                        for (int b = 0; b < TC; ++b) bs[b] = rb[u][b].x - rb[u][b].y;
+#pragma unroll
+                        for (int a = 0; a < TR; ++a)
+#pragma unroll
+                            for (int b = 0; b < TC; ++b) {
+                                m1[a][b] = mma64(ra[u][a].x, rb[u][b].x, m1[a][b]);
+                                m2[a][b] = mma64(ra[u][a].y, rb[u][b].y, m2[a][b]);
+                                m3[a][b] = mma64(as[a], bs[b], m3[a][b]);
+                            }
+                        fetch(u, kt + u + kSplitRing);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < TR; ++a)
+#pragma unroll
+            for (int b = 0; b < TC; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    part[wave][(a * TC + b) * 4 + r][lane] =
+                        d2x{m1[a][b][r] - m2[a][b][r], m1[a][b][r] + m2[a][b][r] - m3[a][b][r]};
+        __syncthreads();
+        for (int e = wave; e < TR * TC * 4; e += NW) {  // group e: row tile, column tile, register
+            const int a = e / (4 * TC), b = e / 4 % TC, r = e % 4;
+            const int bus = 16 * (rt + a) + 4 * r + g, slot = c0 + 16 * b + j;
+            if (slot < nact && bus < n) {
+                const long long c = act[slot];
+                const d2x old = reinterpret_cast<const d2x *>(x)[c * n + bus];
+                const double sr = (double)S[2 * (c * n + bus)], si = (double)S[2 * (c * n + bus) + 1];
+                double pr = 0.0, pi = 0.0, d = 0.0, poison = 0.0;
+#pragma unroll
+                for (int v = 0; v < NW; ++v) pr += part[v][e][lane].x, pi += part[v][e][lane].y;
+                update64<IO>(pr, pi, w[bus], c, bus, n, KB, S, zs, old, sr, si, x, Bn, d, poison);
+                atomicMax(red + 16 * b + j, poison == 0.0 ? (unsigned long long)__double_as_longlong(d) : ~0ull);
+            }
+        }
+        __syncthreads();
+        if (tid < 16 * TC && c0 + tid < nact) atomicMax(dmax + act[c0 + tid], red[tid]);
+        __syncthreads();  // red and part are reused
+    }
+}
+
+// Chunks of 256 active columns, one thread each: sweep count, stopping rule (thr: the bit
+// pattern of the smallest |dV|^2 whose root is not below the tolerance), retirement and the
+// staying columns' places in the next list; where the state is kept `apart` from the
+// results one wave per retired column copies it.  `cnt_next` was cleared a sweep earlier; `cnt_clear` (the count
+// two sweeps back, read by no kernel still to run) is cleared for the sweep after next.
+template <typename IO>
+__global__ __launch_bounds__(256) void finish64_kernel(const long long *__restrict__ act, const int *__restrict__ cnt,
+                                                       int *cnt_clear, const double *x, int n,
+                                                       unsigned long long thr, int max_iter,
+                                                       unsigned long long *__restrict__ dmax, int32_t *iters,
+                                                       int8_t *status, IO *V, bool apart,
+                                                       long long *__restrict__ act_next, int *cnt_next,
+                                                       int *done_flag, int seq) {
+    __shared__ long long gone[256];
+    __shared__ int wsum[4], base_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nact = *cnt;
+    if (blockIdx.x == 0 && tid == 0) {
+        *cnt_clear = 0;
+        if (nact == 0) post_done(done_flag, seq);
+    }
+    for (long long c0 = blockIdx.x * 256LL; c0 < nact; c0 += (long long)gridDim.x * 256) {  // block-uniform
+        long long c = -1;
+        bool stay = false;
+        if (c0 + tid < nact) {
+            c = act[c0 + tid];
+            const unsigned long long d = dmax[c];
+            const bool bad = d == ~0ull, conv = d < thr;
+            const int it = iters[c] + 1;
+            stay = !(bad || conv || it >= max_iter);
+            iters[c] = it;
+            dmax[c] = 0ull;
+            if (!stay) status[c] = bad ? TPF_ST_NONFINITE : (conv ? TPF_ST_CONVERGED : TPF_ST_MAX_ITER);
+        }
+        const int slot = chunk_slot(stay, cnt_next, wsum, &base_s);
+        if (stay) act_next[slot] = c;
+        if (apart) {
+            gone[tid] = stay ? -1 : c;
+            __syncthreads();
+            for (int k = wave; k < 256; k += 4) {
+                const long long cc = gone[k];
+                if (cc < 0) continue;
+                for (int b = lane; b < 2 * n; b += 64) V[2 * cc * n + b] = (IO)x[2 * cc * n + b];
+            }
+        }
+        __syncthreads();  // the chunk's tables are reused
+    }
+}
+
+}  // namespace
+
+// Workspace of the FP64 sweeps: two copies of B [tau][KB] (complex), the column maxima
+// [tau], two active lists [tau], three counts, and the state [tau][n] (complex) where it
+// cannot live in the output array.
+struct Large64 {
+    int KT, KB;
+    size_t bB, bD, bA, bX;
+    Large64(int n, int64_t tau) {
+        auto al = [](size_t b) { return (b + 255) / 256 * 256; };
+        KT = large64_ksteps(n);
+        KB = 4 * KT;
+        bB = al((size_t)tau * KB * 16);
+        bD = al((size_t)tau * 8);
+        bA = al((size_t)tau * 8);
+        bX = al((size_t)tau * n * 16);
+    }
+    size_t total() const { return 2 * bB + bD + 2 * bA + bX + 256; }
+};
+
+size_t large64_workspace(int n, int64_t tau) { return Large64(n, tau).total(); }
+
+template <typename IO>
+static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
+                       int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, void *ws,
+                       hipStream_t st) {
+    const int n = net.n;
+    const Large64 L(n, tau);
+    char *p = static_cast<char *>(ws);
+    d2x *B[2];
+    B[0] = reinterpret_cast<d2x *>(p), p += L.bB;
+    B[1] = reinterpret_cast<d2x *>(p), p += L.bB;
+    auto *dmax = reinterpret_cast<unsigned long long *>(p);
+    p += L.bD;
+    long long *act[2];
+    act[0] = reinterpret_cast<long long *>(p), p += L.bA;
+    act[1] = reinterpret_cast<long long *>(p), p += L.bA;
+    int *cnt = reinterpret_cast<int *>(p);  // three active counts in rotation
+    p += 256;
+    // the state lives in a complex128 result, unless the caller solves in place (S is read
+    // by every sweep)
+    const char *s0 = static_cast<const char *>(S), *v0 = static_cast<const char *>(V);
+    const size_t bytes = (size_t)tau * n * 2 * sizeof(IO);
+    const bool apart = sizeof(IO) == 4 || (s0 < v0 + bytes && v0 < s0 + bytes);
+    double *x = apart ? reinterpret_cast<double *>(p) : static_cast<double *>(V);
+    const ZipShares zs{dn.aP, dn.aI, dn.aZ};
+    const auto *A = reinterpret_cast<const d2x *>(dn.AL64);
+    const auto *w = reinterpret_cast<const d2x *>(dn.wl);
+    hipLaunchKernelGGL((start64_kernel<IO>), dim3((unsigned)((tau + 3) / 4)), dim3(256), 0, st, (const IO *)S,
+                       (const IO *)V0, n, L.KB, (long long)tau, zs, x, B[0], B[1], iters, act[0], cnt, dmax);
+    // Every sweep is queued without waiting, with grids fixed from tau: the active counts
+    // stay on the device (three of them in rotation: read, appended, cleared) and the
+    // kernels of a sweep with no active column exit at once.  Queueing stops early when
+    // the device has already posted that none is left (all_retired).
+    // Shape by the tiles a batch has: 64 x 64 once each CU gets four of them, 32 x 32 with the
+    // k-steps split among four waves down to 5/8 of a tile per CU, else 16 x 16 with eight.
+    // Per solve at 999 buses: 1 column 186 us small, 452 middle, 1,510 large; 256 columns
+    // 800, 590, 1,725; 4,096 columns 6,960, 4,315, 4,276; 20,000 columns 20.5 ms middle,
+    // 18.8 large.  At 349 buses the 4,096 columns take 886, 657 and 854 us.
+    const int64_t cus = num_cus();
+    auto tiles = [&](int edge) { return (int64_t)((n + edge - 1) / edge) * ((tau + edge - 1) / edge); };
+    const int edge = tiles(64) >= 4 * cus ? 64 : 8 * tiles(32) >= 5 * cus ? 32 : 16;
+    const int row_blocks = (n + edge - 1) / edge;
+    const auto gemm = edge == 64   ? gemm64_kernel<IO>
+                      : edge == 32 ? gemm64_split_kernel<2, 2, 4, IO>
+                                   : gemm64_split_kernel<1, 1, 8, IO>;
+    const int threads = edge == 16 ? 512 : 256;
+    const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(edge));
+    const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + 255) / 256);
+    const unsigned long long thr = square_bound(tol);
+    const int seq = ++dn.solve_seq;
+    for (int sweep = 0; sweep < max_iter; ++sweep) {
+        if (all_retired(dn, seq)) break;
+        const int cur = sweep & 1;
+        int *cr = cnt + sweep % 3, *cn = cnt + (sweep + 1) % 3, *cz = cnt + (sweep + 2) % 3;
+        hipLaunchKernelGGL(gemm, dim3(g_mm), dim3(threads), 0, st, A, L.KT, B[cur], B[cur ^ 1], L.KB,
+                           act[cur], cr, row_blocks, w, n, (const IO *)S, zs, x, dmax);
+        hipLaunchKernelGGL((finish64_kernel<IO>), dim3(g_fin), dim3(256), 0, st, act[cur], cr, cz, x, n, thr, max_iter,
+                           dmax, iters, status, (IO *)V, apart, act[cur ^ 1], cn, dn.done_dev, seq);
+    }
+    return TPF_OK;
+}
+
+int launch_fpi_large64(const tpf_network_s &net, const DeviceNet &dn, const void *S, int dtype, int64_t tau, double tol,
+                       int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, void *ws,
+                       hipStream_t st) {
+    if (!dn.AL64) return fail(TPF_ERR_UNSUPPORTED, "large-network operator not staged");
+    return dtype == TPF_C128 ? run_large64<double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st)
+                             : run_large64<float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st);
+}
+
+}  // namespace tpf

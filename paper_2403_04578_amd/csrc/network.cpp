@@ -70,12 +70,6 @@ static void lu_solve(const std::vector<cd> &lu, const std::vector<int> &piv, int
     }
 }
 
-// Row position of (PQ bus q, part) inside the real-block operator of the large-network
-// FP64 product: each 16-row tile holds 8 buses, real parts in rows 0-7 and imaginary
-// parts in rows 8-15, so that the FP64 MFMA output layout (lane group g holds tile rows
-// g, g+4, g+8, g+12) keeps Re and Im of a bus in one lane.
-static inline int blk_pos(int q, int part) { return 16 * (q / 8) + 8 * part + (q % 8); }
-
 // Order of the FP32-family kernels: Re/Im of a bus on adjacent tile rows so that
 // the 16x16 output layout (rows 4g..4g+3 in lane group g) keeps a bus in one lane.
 static inline int blk_pos32(int q, int part) { return 16 * (q / 8) + 2 * (q % 8) + part; }
@@ -200,10 +194,9 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
     // ---- large-network operator (FP64 beyond the register kernels, FP32 beyond 128 buses)
     if (n > 128) {
         const int KP = (2 * n + 15) / 16 * 16, K16 = (2 * n + 31) / 32 * 32;
-        const int M64 = (16 * ((n + 7) / 8) + 63) / 64 * 64, M32 = (2 * n + 127) / 128 * 128;
+        const int M32 = (2 * n + 127) / 128 * 128;
         dn.KPL = KP;
         dn.KPL16 = K16;
-        dn.MPL64 = M64;
         dn.MPL32 = M32;
         double zmax = 0.0;
         for (size_t i = 0; i < (size_t)n * n; ++i)
@@ -218,7 +211,18 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
         *dn.done_host = 0;
         if (hipHostGetDevicePointer((void **)&dn.done_dev, dn.done_host, 0) != hipSuccess)
             return fail(TPF_ERR_DEVICE, "pinned host word not mapped (network staging)");
-        std::vector<double> a64((size_t)M64 * KP, 0.0);
+        std::vector<double> a64;
+        if (n > 8 * kMaxSmallTiles) {
+            const int KT = large64_ksteps(n), tiles = (n + 63) / 64 * 4;
+            a64.assign((size_t)tiles * KT * 128, 0.0);
+            for (int i = 0; i < n; ++i)
+                for (int k = 0; k < n; ++k) {
+                    const cd z = net.Z[(size_t)i * n + k];
+                    double *f = &a64[(((size_t)(i / 16) * KT + k / 4) * 64 + 16 * (k % 4) + i % 16) * 2];
+                    f[0] = z.real();
+                    f[1] = z.imag();
+                }
+        }
         std::vector<float> a32((size_t)M32 * KP, 0.0f);
         std::vector<uint16_t> abf((size_t)M32 * K16, 0), ah((size_t)M32 * K16, 0);
         std::vector<double> wn(2 * n);
@@ -230,18 +234,17 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
                 const double blk[2][2] = {{z.real(), -z.imag()}, {z.imag(), z.real()}};
                 for (int pi = 0; pi < 2; ++pi)
                     for (int pk = 0; pk < 2; ++pk) {
-                        a64[(size_t)blk_pos(i, pi) * KP + 2 * k + pk] = blk[pi][pk];
                         a32[(size_t)(2 * i + pi) * KP + 2 * k + pk] = (float)blk[pi][pk];
                         abf[(size_t)(2 * i + pi) * K16 + 2 * k + pk] = to_bf16((float)blk[pi][pk]);
                         ah[(size_t)(2 * i + pi) * K16 + 2 * k + pk] = to_f16((float)std::ldexp(blk[pi][pk], dn.sZ));
                     }
             }
         }
-        if (!dalloc((void **)&dn.AL64, a64.size() * 8) || !dalloc((void **)&dn.AL32, a32.size() * 4) ||
+        if ((!a64.empty() && !dalloc((void **)&dn.AL64, a64.size() * 8)) || !dalloc((void **)&dn.AL32, a32.size() * 4) ||
             !dalloc((void **)&dn.ALbf, abf.size() * 2) || !dalloc((void **)&dn.ALh, ah.size() * 2) ||
             !dalloc((void **)&dn.wl, wn.size() * 8))
             return fail(TPF_ERR_OOM, "device allocation failed (network staging)");
-        if (!h2d(dn.AL64, a64.data(), a64.size() * 8) || !h2d(dn.AL32, a32.data(), a32.size() * 4) ||
+        if ((!a64.empty() && !h2d(dn.AL64, a64.data(), a64.size() * 8)) || !h2d(dn.AL32, a32.data(), a32.size() * 4) ||
             !h2d(dn.ALbf, abf.data(), abf.size() * 2) || !h2d(dn.ALh, ah.data(), ah.size() * 2) ||
             !h2d(dn.wl, wn.data(), wn.size() * 8))
             return fail(TPF_ERR_DEVICE, "host-to-device copy failed (network staging)");

@@ -58,11 +58,12 @@ struct DeviceNet {
     uint16_t *Abf = nullptr;     // BF16 fragments, [NW][TPW][KTL][64][8]
     uint16_t *Ah = nullptr;      // FP16 fragments of Z 2^sZ, [NW][TPW][KTL][64][8]
     uint16_t *Al = nullptr;      // FP16 residual Z 2^sZ - Ah, same layout
-    // Large-network path (fpi_large.hip): operator [MPL][KPL] row-major, K interleaved
-    // Re/Im per bus; FP64 rows in 16-row tiles of 8 buses (Re rows 0-7, Im rows 8-15),
-    // FP32-family rows interleaved (2 q + part).  wl = w as [n][2].  The 16-bit
-    // operands (BF16 Z, FP16 Z 2^sZ) have K padded to KPL16, a multiple of 32.
-    int MPL64 = 0, MPL32 = 0, KPL = 0, KPL16 = 0;
+    // Large-network path (fpi_large.hip).  FP64 (n > 8 kMaxSmallTiles): fragments of Z
+    // [16-bus tiles, a multiple of 4][large64_ksteps][64 lanes][Re, Im].  FP32 family
+    // (n > 128): operator [MPL32][KPL] row-major, rows and K interleaved Re/Im per bus.
+    // wl = w as [n][2].  The 16-bit operands (BF16 Z, FP16 Z 2^sZ) have K padded to KPL16, a
+    // multiple of 32.
+    int MPL32 = 0, KPL = 0, KPL16 = 0;
     double *AL64 = nullptr;
     float *AL32 = nullptr;
     uint16_t *ALbf = nullptr, *ALh = nullptr;
@@ -161,7 +162,16 @@ int launch_fpi_mixed(const tpf_network_s &net, const DeviceNet &dn, int mode, co
 int launch_fpi_large(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype,
                      int64_t tau, double tol, int max_iter, const void *V0, void *V, int32_t *iters,
                      int8_t *status, void *workspace, hipStream_t stream);
+int launch_fpi_large64(const tpf_network_s &net, const DeviceNet &dn, const void *S, int dtype, int64_t tau, double tol,
+                       int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, void *workspace,
+                       hipStream_t stream);
 size_t large_workspace_bytes(int n, int64_t tau, int mode);
+size_t large64_workspace(int n, int64_t tau);
+// k-steps of four buses in the large FP64 operand (even: two per LDS slab).
+inline int large64_ksteps(int n) { return (n + 7) / 8 * 2; }
+// Bit pattern of the smallest double x >= 0 with sqrt(x) >= tol, so that x < it exactly when
+// sqrt(x) < tol (sqrt is monotone and correctly rounded).
+unsigned long long square_bound(double tol);
 // The register-resident kernels cover FP64 up to 8 * kMaxSmallTiles PQ buses and the
 // FP32/mixed ones up to 128; larger networks use the large path (FP64, FP32).
 inline bool uses_large_path(int n, int mode) { return mode == TPF_MODE_FP64 ? n > 8 * kMaxSmallTiles : n > 128; }
@@ -169,6 +179,8 @@ int launch_start_only(int n, const void *V0, int dtype, int64_t tau, void *V, in
                       int8_t *status, hipStream_t stream);
 int launch_mismatch_f64(const tpf_network_s &net, const DeviceNet &dn, const void *S, const void *V,
                         int dtype, int64_t tau, double *out, hipStream_t stream);
+// Compute units of the current device (looked up once per device).
+int num_cus();
 int launch_zero_u64(unsigned long long *p, int count, hipStream_t stream);
 
 }  // namespace tpf
