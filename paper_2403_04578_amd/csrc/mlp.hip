@@ -11,8 +11,9 @@
 //                      the weight gradient into the flat FP32 gradient vector
 //   output_grad_kernel MSE loss and dY = 2 (y - target) / (rows outputs)
 //   colsum_kernel      bias gradients
-//   adamw_kernel       decoupled-weight-decay Adam on the FP32 master vector
-//   sync_kernel        BF16 copies of the weights in both layouts the GEMMs read
+//   adamw_sync_kernel  decoupled-weight-decay Adam on the FP32 master vector, and the BF16
+//                      copies of the changed weights (mlp_train.h)
+//   sync_kernel        BF16 copies of the weights in the layouts the products read
 //   predict_out_kernel y -> V0 = v_s + (y_re + j y_im)/20
 //   gather_rows_kernel one shuffled mini-batch (S, V, minute index) for training
 //   loss_accum_kernel  running mean of the batch losses of an epoch
@@ -181,35 +182,6 @@ __global__ void colsum_kernel(const __bf16 *__restrict__ dZ, int64_t rows_pad, i
         __syncthreads();
     }
     if (threadIdx.x == 0 && c < nvalid) g[c] = red[0];
-}
-
-__global__ void adamw_kernel(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
-                             float *__restrict__ v, int64_t P, float lr, float wd, float b1, float b2, float eps,
-                             float bc1, float bc2) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < P; i += (int64_t)gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.0f - b1) * gi;
-        const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        const float mh = mi / bc1, vh = vi / bc2;
-        p[i] -= lr * (mh / (sqrtf(vh) + eps) + wd * p[i]);
-    }
-}
-
-// BF16 copies of layer l: Wt [out_p][in_p] (= W, k contiguous for X W^T) and
-// Wn [in_p][out_p] (= W^T, for dZ W), zero in the padding.
-__global__ void sync_kernel(const float *__restrict__ p, int64_t woff, int in, int out, int in_p, int out_p,
-                            __bf16 *__restrict__ Wt, __bf16 *__restrict__ Wn, float *__restrict__ bias_p,
-                            int64_t boff) {
-    const int64_t total = (int64_t)in_p * out_p;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int o = (int)(e / in_p), i = (int)(e - (int64_t)o * in_p);
-        const float w = (o < out && i < in) ? p[woff + (int64_t)o * in + i] : 0.0f;
-        Wt[(int64_t)o * in_p + i] = (__bf16)w;
-        Wn[(int64_t)i * out_p + o] = (__bf16)w;
-        if (i == 0) bias_p[o] = o < out ? p[boff + o] : 0.0f;
-    }
 }
 
 // BF16 MFMA A fragments of layer l, [T][K / 32][64 lanes][8] (lane (g, j) of fragment (t, s)
@@ -569,6 +541,29 @@ unsigned grid_for(int64_t work, int64_t per_block = 256) {
 }  // namespace
 }  // namespace tpf
 
+#include "mlp_train.h"
+
+namespace tpf {
+namespace {
+
+// BF16 copies of layer l's weights, zero in the padding: W for X W^T, and with `chain` also W^T
+// for dZ W, both in the chain kernel's fragment order (else W row-major [out_p][in_p]).
+__global__ void sync_kernel(const float *__restrict__ p, int64_t woff, int in, int out, int in_p, int out_p,
+                            __bf16 *__restrict__ Wt, __bf16 *__restrict__ Wn, float *__restrict__ bias_p,
+                            int64_t boff, bool chain) {
+    const int64_t total = (int64_t)in_p * out_p;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+        const int o = (int)(e / in_p), i = (int)(e - (int64_t)o * in_p);
+        const float w = (o < out && i < in) ? p[woff + (int64_t)o * in + i] : 0.0f;
+        Wt[chain ? frag_place(o, i, in_p) : e] = (__bf16)w;
+        if (chain) Wn[frag_place(i, o, out_p)] = (__bf16)w;
+        if (i == 0) bias_p[o] = o < out ? p[boff + o] : 0.0f;
+    }
+}
+
+}  // namespace
+}  // namespace tpf
+
 using namespace tpf;
 
 struct tpf_mlp_s {
@@ -580,7 +575,7 @@ struct tpf_mlp_s {
     int64_t P = 0;
     int64_t step = 0;                    // AdamW steps taken
     float *p = nullptr, *m = nullptr, *v = nullptr, *grad = nullptr;  // device FP32 [P]
-    std::vector<__bf16 *> Wt, Wn;        // device BF16 copies per layer
+    std::vector<__bf16 *> Wt, Wn;        // device BF16 copies per layer (sync_kernel)
     std::vector<float *> bias;           // device padded FP32 bias per layer
     std::vector<uint16_t *> Wf;          // BF16 MFMA A fragments per layer (frag_kernel)
     std::vector<float *> bf;             // bias in the fragments' row order
@@ -594,15 +589,18 @@ int64_t rows_pad(int64_t rows) { return (rows + 63) / 64 * 64; }
 
 // Workspace carving: X/activations bf16 [rows_pad][Dmax] x (L+1), pre-activations f32
 // [rows_pad][Dmax] x L, output f32 [rows_pad][Dout], gradient scratch bf16 x 2, and the
-// buffers of one gathered training batch (S, V, minute index) for tpf_mlp_train.
+// buffers of one gathered training batch (S, V, minute index) for tpf_mlp_train; for the
+// chain kernel the transposed gradients of every layer.
 struct MlpWs {
     std::vector<__bf16 *> H;   // H[0] = X, H[l] = activation of hidden layer l
     std::vector<float *> Z;    // Z[l] pre-activation of hidden layer l (1-based, l = 1..L)
     float *Y = nullptr;
     __bf16 *G0 = nullptr, *G1 = nullptr;
-    float *loss = nullptr;
+    std::vector<__bf16 *> GT;  // every layer's output gradient, transposed (chain kernel)
+    float *loss = nullptr;     // the loss, or the chain kernel's partial losses (one per kChainRows rows)
     void *Sb = nullptr, *Vb = nullptr;  // a gathered training batch [rows][n] complex (up to complex128)
-    int64_t *tb = nullptr;              // its minute indices
+    int64_t *tb = nullptr;              // its minute indices, or the chain kernel's row order
+    float *phase = nullptr;             // the chain kernel's calendar phases [rows][4]
 };
 
 size_t carve(const tpf_mlp_s &M, int64_t rows, void *base, MlpWs *ws) {
@@ -628,10 +626,17 @@ size_t carve(const tpf_mlp_s &M, int64_t rows, void *base, MlpWs *ws) {
     char *y = take((size_t)rp * Dmax * 4);
     char *g0 = take((size_t)rp * Dmax * 2);
     char *g1 = take((size_t)rp * Dmax * 2);
-    char *ls = take(256);
+    if (ws) ws->GT.assign(L + 1, nullptr);
+    if (Dmax <= kChainWidth)
+        for (int l = 0; l <= L; ++l) {
+            char *q = take((size_t)rp * Dmax * 2);
+            if (ws) ws->GT[l] = reinterpret_cast<__bf16 *>(q);
+        }
+    char *ls = take((size_t)rp / kChainRows * 4 + 256);
     char *sb = take((size_t)rows * M.n * 16);
     char *vb = take((size_t)rows * M.n * 16);
     char *tb = take((size_t)rows * 8);
+    char *ph = take((size_t)rows * 16);
     if (ws) {
         ws->Y = reinterpret_cast<float *>(y);
         ws->G0 = reinterpret_cast<__bf16 *>(g0);
@@ -640,6 +645,7 @@ size_t carve(const tpf_mlp_s &M, int64_t rows, void *base, MlpWs *ws) {
         ws->Sb = sb;
         ws->Vb = vb;
         ws->tb = reinterpret_cast<int64_t *>(tb);
+        ws->phase = reinterpret_cast<float *>(ph);
     }
     return off;
 }
@@ -657,11 +663,18 @@ int last_launch(const char *what) {
     return TPF_OK;
 }
 
+// Whether the three-kernel training step applies.
+bool chain_fits(const tpf_mlp_s &M) {
+    int Dmax = 0;
+    for (int w : M.dp) Dmax = std::max(Dmax, w);
+    return Dmax <= kChainWidth;
+}
+
 int sync_weights(tpf_mlp_s &M, hipStream_t st) {
     for (int l = 0; l <= M.layers; ++l) {
         hipLaunchKernelGGL(sync_kernel, dim3(grid_for((int64_t)M.dp[l] * M.dp[l + 1])), dim3(256), 0, st, M.p,
                            M.woff[l], M.d[l], M.d[l + 1], M.dp[l], M.dp[l + 1], M.Wt[l], M.Wn[l], M.bias[l],
-                           M.boff[l]);
+                           M.boff[l], chain_fits(M));
         hipLaunchKernelGGL(frag_kernel, dim3(grid_for((int64_t)M.frows[l] * M.dp[l])), dim3(256), 0, st, M.p,
                            M.woff[l], M.boff[l], M.d[l], M.d[l + 1], M.dp[l], M.frows[l], l == M.layers ? M.n : 0,
                            l == 0 ? M.n : 0, M.Wf[l], M.bf[l]);
@@ -671,16 +684,31 @@ int sync_weights(tpf_mlp_s &M, hipStream_t st) {
 
 // One AdamW step of the FP32 master parameters with the gradient in M.grad (step count
 // advanced first: the bias corrections use t = 1 on the first step), then the BF16 copies.
-int adamw_update(tpf_mlp_s &M, float lr, float wd, hipStream_t st) {
+// The partial losses in `lossp`, when given, are summed and added to acc times scale.
+int adamw_update(tpf_mlp_s &M, float lr, float wd, hipStream_t st, const float *lossp = nullptr, int loss_n = 0,
+                 float *acc = nullptr, float scale = 0.0f) {
     M.step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float bc1 = 1.0f - (float)std::pow((double)b1, (double)M.step);
     const float bc2 = 1.0f - (float)std::pow((double)b2, (double)M.step);
-    hipLaunchKernelGGL(adamw_kernel, dim3(grid_for(M.P)), dim3(256), 0, st, M.p, M.grad, M.m, M.v, M.P, lr, wd, b1,
-                       b2, 1e-8f, bc1, bc2);
-    int rc = last_launch("AdamW");
-    if (rc != TPF_OK) return rc;
-    return sync_weights(M, st);
+    ParamView pv{};
+    pv.L = M.layers;
+    pv.n = M.n;
+    pv.chain = chain_fits(M);
+    for (int l = 0; l <= M.layers; ++l) {
+        pv.Wt[l] = M.Wt[l];
+        pv.Wn[l] = M.Wn[l];
+        pv.Wf[l] = M.Wf[l];
+        pv.bias[l] = M.bias[l];
+        pv.bf[l] = M.bf[l];
+        pv.woff[l] = M.woff[l];
+        pv.boff[l] = M.boff[l];
+    }
+    pv.woff[M.layers + 1] = M.P;
+    for (int l = 0; l < M.layers + 2; ++l) pv.d[l] = M.d[l], pv.dp[l] = M.dp[l];
+    hipLaunchKernelGGL(adamw_sync_kernel, dim3(grid_for(M.P)), dim3(256), 0, st, M.p, M.grad, M.m, M.v, pv, lr, wd, b1,
+                       b2, 1e-8f, bc1, bc2, lossp, loss_n, acc, scale);
+    return last_launch("AdamW");
 }
 
 // The shuffle key of an epoch: MurmurHash3's 64-bit finaliser of the seed and epoch.
@@ -699,6 +727,52 @@ void gemm(const __bf16 *A, int64_t sam, int64_t sak, const __bf16 *B, int64_t sb
           int vn, int64_t goff, hipStream_t st) {
     hipLaunchKernelGGL((gemm_bf16_kernel<AK, BK, EP>), dim3((unsigned)(Mrows / 64), (unsigned)(N / 64)), dim3(256),
                        0, st, A, sam, sak, B, sbk, sbn, K, bias, Cf, Cb, ldc, Z, ldz, vm, vn, goff);
+}
+
+// The rows of a batch (of a shuffled set with sh.h > 0) for the chain kernel.
+BatchRows batch_rows(const MlpWs &ws, const int64_t *t, int64_t rows, const Shuffle &sh) {
+    return BatchRows{t, ws.tb, ws.phase, rows, sh};
+}
+
+void launch_batch_rows(const BatchRows &br, hipStream_t st) {
+    hipLaunchKernelGGL(batch_rows_kernel, dim3((unsigned)((br.rows + 31) / 32)), dim3(128), 0, st, br);
+}
+
+// Loss partials and gradient of the prepared batch of `rows` rows by the chain and
+// weight-gradient kernels; the latter prepares the batch `next` (rows = 0: none).
+template <typename IO>
+int chain_loss_grad(tpf_mlp_s &M, const IO *S, const IO *V, int64_t rows, const BatchRows &next, float *gout,
+                    const MlpWs &ws, hipStream_t st) {
+    const int64_t rp = rows_pad(rows);
+    TrainView tv{};
+    GradView gv{};
+    tv.L = gv.L = M.layers;
+    tv.n = M.n;
+    int tiles = 0, cols = 0;
+    for (int l = 0; l <= M.layers; ++l) {
+        tv.Wt[l] = M.Wt[l];
+        tv.Wn[l] = M.Wn[l];
+        tv.b[l] = M.bias[l];
+        tv.HT[l] = ws.H[l];
+        tv.GT[l] = ws.GT[l];
+        tv.Z[l] = l ? ws.Z[l] : nullptr;
+        gv.HT[l] = ws.H[l];
+        gv.GT[l] = ws.GT[l];
+        gv.woff[l] = M.woff[l];
+        gv.boff[l] = M.boff[l];
+        gv.tile0[l] = tiles;
+        gv.col0[l] = cols;
+        tiles += M.dp[l + 1] / 64 * (M.dp[l] / 16);
+        cols += M.d[l + 1];
+    }
+    gv.tile0[M.layers + 1] = tiles;
+    gv.col0[M.layers + 1] = cols;
+    for (int l = 0; l < M.layers + 2; ++l) tv.d[l] = gv.d[l] = M.d[l], tv.dp[l] = gv.dp[l] = M.dp[l];
+    hipLaunchKernelGGL(train_chain_kernel<IO>, dim3((unsigned)(rp / kChainRows)), dim3(kChainThreads), 0, st, S, V,
+                       ws.tb, ws.phase, rows, rp, tv, M.vs_re, M.vs_im, ws.loss);
+    hipLaunchKernelGGL(train_dw_kernel, dim3((unsigned)(tiles + (cols + 1) / 2 + (next.rows + 31) / 32)), dim3(128), 0,
+                       st, gv, (int)rp, gout, next);
+    return last_launch("MLP training step");
 }
 
 template <typename IO>
@@ -724,6 +798,14 @@ int forward(tpf_mlp_s &M, const IO *S, const int64_t *t, int64_t rows, const Mlp
 template <typename IO>
 int loss_grad(tpf_mlp_s &M, const IO *S, const int64_t *t, const IO *V, int64_t rows, float *loss_out, float *gout,
               const MlpWs &ws, hipStream_t st) {
+    if (chain_fits(M)) {
+        launch_batch_rows(batch_rows(ws, t, rows, Shuffle{}), st);
+        int rc = chain_loss_grad(M, S, V, rows, BatchRows{}, gout, ws, st);
+        if (rc != TPF_OK || !loss_out) return rc;
+        hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(64), 0, st, ws.loss, (int)(rows_pad(rows) / kChainRows),
+                           loss_out);
+        return last_launch("MLP loss");
+    }
     int rc = forward(M, S, t, rows, ws, st);
     if (rc != TPF_OK) return rc;
     const int64_t rp = rows_pad(rows);
@@ -938,6 +1020,19 @@ extern "C" int tpf_mlp_train(tpf_mlp M, const void *S, int32_t dtype, const int6
             const double k = (double)e * (double)nb + (double)b;
             const double rate = (double)lr_min + 0.5 * ((double)lr - (double)lr_min) *
                                                      (1.0 + std::cos(M_PI * k / std::max(1.0, total - 1.0)));
+            if (chain_fits(*M)) {
+                if (b == 0) launch_batch_rows(batch_rows(ws, t_index, B, Shuffle{rows, 0, key, h}), st);
+                const BatchRows next =
+                    b + 1 < nb ? batch_rows(ws, t_index, B, Shuffle{rows, (b + 1) * B, key, h}) : BatchRows{};
+                rc = dtype == TPF_C128
+                         ? chain_loss_grad(*M, (const double *)S, (const double *)V, B, next, M->grad, ws, st)
+                         : chain_loss_grad(*M, (const float *)S, (const float *)V, B, next, M->grad, ws, st);
+                if (rc != TPF_OK) return rc;
+                rc = adamw_update(*M, (float)rate, weight_decay, st, ws.loss, (int)(rows_pad(B) / kChainRows), acc,
+                                  1.0f / (float)nb);
+                if (rc != TPF_OK) return rc;
+                continue;
+            }
             const unsigned blocks = (unsigned)((B + 3) / 4);
             if (dtype == TPF_C128) {
                 hipLaunchKernelGGL(gather_rows_kernel<double>, dim3(blocks), dim3(256), 0, st, (const double *)S,
