@@ -90,6 +90,9 @@ int solve_impl(tpf_network net, const void *S, int32_t dtype, int64_t T, double 
         rc = launch_start_only(n, V0, dtype, T, V_out, iters_out, status_out, st);
     } else if (is_tree(mode)) {
         rc = launch_fpi_tree(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out, st);
+    } else if (mode != TPF_MODE_FP64 && n > 128 && n <= kMaxMidBuses) {
+        rc = launch_fpi_mid(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out,
+                            reinterpret_cast<unsigned long long *>(workspace), st);
     } else if (uses_large_path(n, mode)) {
         rc = launch_fpi_large(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out,
                               workspace, st);

@@ -9,10 +9,10 @@
 //           sweep's injection (the first sweep's comes from its own kernel).
 // Every sweep is queued without waiting on the device: the active counts stay there.
 #include "large_common.h"
+#include "mixed_steps.h"
 
 namespace tpf {
 
-typedef float f4x __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -58,23 +58,10 @@ __device__ __forceinline__ void injection_at(const IO *__restrict__ S, const flo
                                              const ZipShares zs, float &ir, float &ii) {
     ir = 0, ii = 0;
     if (b >= n) return;
-    const double sr = (double)S[2 * (c * n + b)], si = (double)S[2 * (c * n + b) + 1];
-    double vr = (double)x[2 * (c * n + b)], vi = (double)x[2 * (c * n + b) + 1];
-    vr += w[2 * b], vi += w[2 * b + 1];
-    const double inv = 1.0 / (vr * vr + vi * vi);
-    double jr = (sr * vr + si * vi) * inv, ji = (sr * vi - si * vr) * inv;
-    if (zs.aP) {
-        const double ap = zs.aP[b], ai = zs.aI[b];
-        jr = ap * jr + ai * sr;
-        ji = ap * ji - ai * si;
-        if (zs.aZ) {
-            const double az = zs.aZ[b];
-            jr += az * (sr * vr + si * vi);
-            ji += az * (sr * vi - si * vr);
-        }
-    }
-    ir = (float)jr;
-    ii = (float)ji;
+    const float2 o = full_injection((double)S[2 * (c * n + b)], (double)S[2 * (c * n + b) + 1], w[2 * b], w[2 * b + 1],
+                                    x[2 * (c * n + b)], x[2 * (c * n + b) + 1], zs, b);
+    ir = o.x;
+    ii = o.y;
 }
 
 // The first sweep's B operand [rows][KP]: row a = injection of column act[a] (zero past na).
@@ -171,14 +158,11 @@ __global__ __launch_bounds__(256) void gemm_kernel(const float *__restrict__ A, 
                 for (int h = 0; h < 2; ++h) {
                     const int bus = (tile0 + 4 * g + 2 * h) >> 1;
                     if (live && bus < n) {
-                        const double nr = (double)acc[a][b][2 * h], ni = (double)acc[a][b][2 * h + 1];
                         float *xp = x + 2 * (c * n + bus);
-                        const double dr = nr - (double)xp[0], di = ni - (double)xp[1];
-                        const double e2 = dr * dr + di * di;
-                        bad |= !(e2 < HUGE_VAL);
-                        emax = e2 > emax ? e2 : emax;
-                        xp[0] = (float)nr;
-                        xp[1] = (float)ni;
+                        const float2 nu = full_update(acc[a][b][2 * h], acc[a][b][2 * h + 1],
+                                                      make_float2(xp[0], xp[1]), emax, bad);
+                        xp[0] = nu.x;
+                        xp[1] = nu.y;
                     }
                 }
             }
@@ -282,45 +266,6 @@ __global__ void zero_i32_kernel(int *p, long long count) {
 // new refine once the distance they travelled makes their rounding matter.  Columns
 // are kept in two lists per sweep, refine and low, each with its own product.
 
-struct MixState {
-    int it, ph, want;            // sweeps done; 0 = full low sweeps, 1 = difference sweeps; refine wanted
-    float dprev, sumd, uref;     // previous step, steps since the last refine, max |U| seen
-    float ks, inv;               // B scale 2^sB and product unscale 2^-(sB + sZ) (FP16); 1, 1 (BF16)
-};
-
-typedef short s8x __attribute__((ext_vector_type(8)));
-typedef __bf16 bf8x __attribute__((ext_vector_type(8)));
-typedef _Float16 h8x __attribute__((ext_vector_type(8)));
-
-template <int MODE>
-struct Low16;
-template <>
-struct Low16<TPF_MODE_MIXED_BF16> {
-    static constexpr float u = 0.00390625f;  // 2^-8
-    __device__ static uint32_t enc2(float a, float b) {
-        return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)a) |
-               ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)b) << 16);
-    }
-    __device__ static f4x mma(const uint4 &a, const uint4 &b, const f4x &c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8x, a), __builtin_bit_cast(bf8x, b), c,
-                                                       0, 0, 0);
-    }
-};
-template <>
-struct Low16<TPF_MODE_MIXED_FP16> {
-    static constexpr float u = 0.00048828125f;  // 2^-11
-    __device__ static uint32_t enc2(float a, float b) {
-        a = __builtin_amdgcn_fmed3f(a, -65504.f, 65504.f);
-        b = __builtin_amdgcn_fmed3f(b, -65504.f, 65504.f);
-        return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)a) |
-               ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)b) << 16);
-    }
-    __device__ static f4x mma(const uint4 &a, const uint4 &b, const f4x &c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8x, a), __builtin_bit_cast(h8x, b), c, 0,
-                                                      0, 0);
-    }
-};
-
 // One wave per column: FP16 scale from max |S| (times zscale = max |alpha_P| + |alpha_I| +
 // |alpha_Z| for ZIP loads) and the initial schedule state.
 template <int MODE, typename IO>
@@ -342,38 +287,10 @@ __global__ void init_mix_kernel(const IO *__restrict__ S, int n, long long tau, 
         sbad |= __shfl_xor(sbad, off);
     }
     if (lane == 0) {
-        int sB = 0;
-        if (MODE == TPF_MODE_MIXED_FP16) {
-            int e = 0;
-            (void)frexpf(sm > 0.f && sm < 1e30f ? sm : 1.0f, &e);
-            sB = 12 - e;  // max |S| 2^sB < 2^12: |I| 2^sB < 2^15 while |V| > 1/4
-        }
-        MixState m;
-        m.it = m.ph = m.want = 0;
-        m.dprev = m.sumd = m.uref = 0.f;
-        m.ks = ldexpf(1.0f, sB);
-        m.inv = ldexpf(1.0f, -(sB + (MODE == TPF_MODE_MIXED_FP16 ? sZ : 0)));
-        // the FP16 saturation would clip a non-finite load; the unscale carries it into
-        // the iterate instead, so the column ends NONFINITE
-        if (sbad) m.inv = __builtin_nanf("");
+        const MixState m = mixed_start<MODE>(sm, sbad, sZ);
         ms[c] = m;
         umax[c] = 0u;
     }
-}
-
-// alpha_P conj(S./V) + alpha_I conj(S) + alpha_Z conj(S) V for ZIP loads, else conj(S./V)
-// (given as ir, ii).
-__device__ __forceinline__ float2 zip_injection(float ir, float ii, float sr, float si, float vr, float vi,
-                                                const ZipShares &zs, int b) {
-    if (!zs.aP) return make_float2(ir, ii);
-    const float ap = (float)zs.aP[b], ai = (float)zs.aI[b];
-    float2 o = make_float2(ap * ir + ai * sr, ap * ii - ai * si);
-    if (zs.aZ) {
-        const float az = (float)zs.aZ[b];
-        o.x += az * (sr * vr + si * vi);
-        o.y += az * (sr * vi - si * vr);
-    }
-    return o;
 }
 
 // FP32 injection of column c at bus b (o = 2 (c n + b)) from U = V - w.
@@ -381,10 +298,7 @@ template <typename IO>
 __device__ __forceinline__ float2 injection32(const IO *__restrict__ S, const float *__restrict__ U,
                                               const double *__restrict__ w, long long o, int b,
                                               const ZipShares &zs) {
-    const float sr = (float)S[o], si = (float)S[o + 1];
-    const float vr = (float)w[2 * b] + U[o], vi = (float)w[2 * b + 1] + U[o + 1];
-    const float r = 1.0f / fmaxf(vr * vr + vi * vi, kMinV2);
-    return zip_injection((sr * vr + si * vi) * r, (sr * vi - si * vr) * r, sr, si, vr, vi, zs, b);
+    return mixed_injection((float)S[o], (float)S[o + 1], (float)w[2 * b], (float)w[2 * b + 1], U[o], U[o + 1], zs, b);
 }
 
 // 16-bit B entry of a low-list column: I 2^sB on a full sweep (ph = 0), (I - I_prev) 2^sB
@@ -394,8 +308,8 @@ __device__ __forceinline__ uint32_t low_entry(float2 iz, float2 *ip, int ph, flo
     float br = iz.x, bi = iz.y;
     if (ph) {
         const float2 p = *ip;
-        br -= p.x;
-        bi -= p.y;
+        br = rounded_difference(br, p.x);
+        bi = rounded_difference(bi, p.y);
     }
     *ip = iz;
     return Low16<MODE>::enc2(br * ks, bi * ks);
@@ -534,15 +448,8 @@ __global__ __launch_bounds__(256) void gemm_low_kernel(const uint16_t *__restric
                 for (int h = 0; h < 2; ++h) {
                     const int bus = (r0 + wr + 16 * a + 4 * g + 2 * h) >> 1;
                     if (live && bus < n) {
-                        const float2 old = oldv[b][a][h];
-                        const float pr = acc[a][b][2 * h] * inv, pi = acc[a][b][2 * h + 1] * inv;
-                        const float nr = ph ? old.x + pr : pr, ni = ph ? old.y + pi : pi;
-                        const float dr = nr - old.x, di = ni - old.y;
-                        const float e2 = dr * dr + di * di;
-                        bad |= !(e2 < HUGE_VALF);
-                        emax = e2 > emax ? e2 : emax;
-                        umx = fmaxf(umx, fmaxf(fabsf(nr), fabsf(ni)));
-                        *reinterpret_cast<float2 *>(U + 2 * (c * n + bus)) = make_float2(nr, ni);
+                        *reinterpret_cast<float2 *>(U + 2 * (c * n + bus)) =
+                            low_update(acc[a][b][2 * h], acc[a][b][2 * h + 1], oldv[b][a][h], ph, inv, emax, umx, bad);
                     }
                 }
             }
@@ -594,8 +501,6 @@ __global__ __launch_bounds__(256) void finish_mixed_kernel(
     const long long total = (long long)nr + nl;
     if (blockIdx.x == 0 && tid < 2) cnt_clear[tid] = 0;
     if (blockIdx.x == 0 && tid == 0 && total == 0) post_done(done_flag, seq);
-    constexpr float u = Low16<MODE>::u;
-    const float theta = 4.0f * u, refresh = 6.7e-8f / u, margin = 1.0f + 8.0f * u;
     for (long long c0 = blockIdx.x * (long long)cpb; c0 < total; c0 += (long long)gridDim.x * cpb) {  // block-uniform
         const long long a = c0 + tid;
         long long c = -1;
@@ -606,24 +511,8 @@ __global__ __launch_bounds__(256) void finish_mixed_kernel(
             c = refine ? actR[a] : actL[a - nr];
             m = ms[c];
             const float d = (float)sqrt(__longlong_as_double((long long)dmax[c]));
-            const float um = __uint_as_float(umax[c]);
             const int bad = badf[c];
-            m.it += 1;
-            bool conv = false;
-            if (refine) {
-                conv = d < tol;
-                m.ph = 1;
-                m.want = 0;
-                m.sumd = 0.f;
-            } else if (m.ph == 0) {
-                m.uref = fmaxf(m.uref, um);
-                if (!m.want && (d <= theta * m.uref || (m.it >= 2 && d > 0.5f * m.dprev))) m.want = 1;
-            } else {
-                conv = d * margin < tol;
-                m.sumd += d;
-                if (!m.want && m.sumd > refresh) m.want = 1;
-            }
-            m.dprev = d;
+            const bool conv = mixed_schedule<MODE>(m, refine, d, __uint_as_float(umax[c]), tol);
             const bool done = bad || conv || m.it >= max_iter;
             iters[c] = m.it;
             dmax[c] = 0ull;
@@ -684,15 +573,6 @@ __global__ __launch_bounds__(256) void finish_mixed_kernel(
 }
 
 }  // namespace
-
-// Columns per finish chunk: about 16,384 buses' worth, a power of two in [4, 256] (one
-// atomic per chunk keeps a million-column sweep from serialising on the list counter,
-// and small chunks keep a few wide columns spread over many wavefronts).
-static int finish_chunk(int n) {
-    int c = 4;
-    while (c < 256 && 2 * c * n <= 16384) c *= 2;
-    return c;
-}
 
 // Workspace of the large path: state [tau][2n], B operand [tau rounded to 64][KP] (FP32),
 // dmax [tau] (u64), bad flags [tau] (int), two active lists [tau] (i64), counters.

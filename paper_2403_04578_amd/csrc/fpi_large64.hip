@@ -47,7 +47,7 @@ __device__ __forceinline__ d2x injection64(double sr, double si, double vr, doub
 }
 
 // Start voltages (guarded V0 or flat) into x and the first injections into B0; zeroes the
-// K padding of both copies of B, the column maxima and the sweep counts.  One wave per column.
+// K padding of the copies of B (B1 may be NULL), the column maxima and the sweep counts.  One wave per column.
 template <typename IO>
 __global__ void start64_kernel(const IO *__restrict__ S, const IO *__restrict__ V0, int n, int KB, long long tau,
                                const ZipShares zs, double *__restrict__ x, d2x *__restrict__ B0,
@@ -71,7 +71,7 @@ __global__ void start64_kernel(const IO *__restrict__ S, const IO *__restrict__ 
             if (ok) vr = (double)V0[2 * (c * n + b)], vi = (double)V0[2 * (c * n + b) + 1];
             reinterpret_cast<d2x *>(x)[c * n + b] = d2x{vr, vi};
             inj = injection64((double)S[2 * (c * n + b)], (double)S[2 * (c * n + b) + 1], vr, vi, b, zs);
-        } else {
+        } else if (B1) {
             B1[c * KB + b] = inj;
         }
         B0[c * KB + b] = inj;
@@ -87,7 +87,7 @@ __global__ void start64_kernel(const IO *__restrict__ S, const IO *__restrict__ 
 }
 
 // One bus of one active column: V' = p + w, the step |V' - V|^2 into `dmax` (and NaN into
-// `poison` when it is not finite), V' into x and the next injection into Bn.
+// `poison` when it is not finite), V' into x and the next injection into Bn (unless NULL).
 template <typename IO>
 __device__ __forceinline__ void update64(double pr, double pi, d2x w, long long c, int bus, int n, int KB,
                                          const IO *__restrict__ S, const ZipShares &zs, d2x old, double sr, double si,
@@ -98,7 +98,7 @@ __device__ __forceinline__ void update64(double pr, double pi, d2x w, long long 
     poison = __builtin_fma(e, 0.0, poison);
     dmax = fmax(dmax, e);
     reinterpret_cast<d2x *>(x)[c * n + bus] = d2x{nr, ni};
-    Bn[c * KB + bus] = injection64(sr, si, nr, ni, bus, zs);
+    if (Bn) Bn[c * KB + bus] = injection64(sr, si, nr, ni, bus, zs);
 }
 
 // Tiles of 64 buses x 64 active columns, four waves of 32 x 32 (2 x 2 MFMA tiles, three
@@ -307,20 +307,22 @@ __global__ __launch_bounds__(NW * 64) void gemm64_split_kernel(
     }
 }
 
-// Chunks of 256 active columns, one thread each: sweep count, stopping rule (thr: the bit
+// Chunks of cpb <= 256 active columns, one thread each: sweep count, stopping rule (thr: the bit
 // pattern of the smallest |dV|^2 whose root is not below the tolerance), retirement and the
-// staying columns' places in the next list; where the state is kept `apart` from the
-// results one wave per retired column copies it.  `cnt_next` was cleared a sweep earlier; `cnt_clear` (the count
+// staying columns' places in the next list.  Where the state is kept `apart` from the
+// results (and B has no second copy) one wave per column then copies a retired one and forms
+// a staying one's next injection.  `cnt_next` was cleared a sweep earlier; `cnt_clear` (the count
 // two sweeps back, read by no kernel still to run) is cleared for the sweep after next.
 template <typename IO>
 __global__ __launch_bounds__(256) void finish64_kernel(const long long *__restrict__ act, const int *__restrict__ cnt,
                                                        int *cnt_clear, const double *x, int n,
+                                                       const IO *S, const ZipShares zs, int KB, d2x *B,
                                                        unsigned long long thr, int max_iter,
                                                        unsigned long long *__restrict__ dmax, int32_t *iters,
-                                                       int8_t *status, IO *V, bool apart,
+                                                       int8_t *status, IO *V, bool apart, int cpb,
                                                        long long *__restrict__ act_next, int *cnt_next,
                                                        int *done_flag, int seq) {
-    __shared__ long long gone[256];
+    __shared__ long long cols[256];  // column + 1, negative when retired; 0: none
     __shared__ int wsum[4], base_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nact = *cnt;
@@ -328,10 +330,10 @@ __global__ __launch_bounds__(256) void finish64_kernel(const long long *__restri
         *cnt_clear = 0;
         if (nact == 0) post_done(done_flag, seq);
     }
-    for (long long c0 = blockIdx.x * 256LL; c0 < nact; c0 += (long long)gridDim.x * 256) {  // block-uniform
+    for (long long c0 = blockIdx.x * (long long)cpb; c0 < nact; c0 += (long long)gridDim.x * cpb) {  // block-uniform
         long long c = -1;
         bool stay = false;
-        if (c0 + tid < nact) {
+        if (tid < cpb && c0 + tid < nact) {
             c = act[c0 + tid];
             const unsigned long long d = dmax[c];
             const bool bad = d == ~0ull, conv = d < thr;
@@ -344,12 +346,22 @@ __global__ __launch_bounds__(256) void finish64_kernel(const long long *__restri
         const int slot = chunk_slot(stay, cnt_next, wsum, &base_s);
         if (stay) act_next[slot] = c;
         if (apart) {
-            gone[tid] = stay ? -1 : c;
+            cols[tid] = c < 0 ? 0 : stay ? c + 1 : -c - 1;
             __syncthreads();
-            for (int k = wave; k < 256; k += 4) {
-                const long long cc = gone[k];
-                if (cc < 0) continue;
-                for (int b = lane; b < 2 * n; b += 64) V[2 * cc * n + b] = (IO)x[2 * cc * n + b];
+            for (int k = wave; k < cpb; k += 4) {
+                if (cols[k] == 0) break;  // past the active columns (wave-uniform)
+                const bool on = cols[k] > 0;
+                const long long cc = (on ? cols[k] : -cols[k]) - 1;
+                for (int b = lane; b < n; b += 64) {
+                    const d2x v = reinterpret_cast<const d2x *>(x)[cc * n + b];
+                    if (on) {
+                        B[cc * KB + b] = injection64((double)S[2 * (cc * n + b)], (double)S[2 * (cc * n + b) + 1], v.x,
+                                                     v.y, b, zs);
+                    } else {
+                        V[2 * (cc * n + b)] = (IO)v.x;
+                        V[2 * (cc * n + b) + 1] = (IO)v.y;
+                    }
+                }
             }
         }
         __syncthreads();  // the chunk's tables are reused
@@ -359,11 +371,11 @@ __global__ __launch_bounds__(256) void finish64_kernel(const long long *__restri
 }  // namespace
 
 // Workspace of the FP64 sweeps: two copies of B [tau][KB] (complex), the column maxima
-// [tau], two active lists [tau], three counts, and the state [tau][n] (complex) where it
-// cannot live in the output array.
+// [tau], two active lists [tau], three counts.  Where the state cannot live in the output
+// array it takes the second copy's place.
 struct Large64 {
     int KT, KB;
-    size_t bB, bD, bA, bX;
+    size_t bB, bD, bA;
     Large64(int n, int64_t tau) {
         auto al = [](size_t b) { return (b + 255) / 256 * 256; };
         KT = large64_ksteps(n);
@@ -371,9 +383,8 @@ struct Large64 {
         bB = al((size_t)tau * KB * 16);
         bD = al((size_t)tau * 8);
         bA = al((size_t)tau * 8);
-        bX = al((size_t)tau * n * 16);
     }
-    size_t total() const { return 2 * bB + bD + 2 * bA + bX + 256; }
+    size_t total() const { return 2 * bB + bD + 2 * bA + 256; }
 };
 
 size_t large64_workspace(int n, int64_t tau) { return Large64(n, tau).total(); }
@@ -394,13 +405,16 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     act[0] = reinterpret_cast<long long *>(p), p += L.bA;
     act[1] = reinterpret_cast<long long *>(p), p += L.bA;
     int *cnt = reinterpret_cast<int *>(p);  // three active counts in rotation
-    p += 256;
     // the state lives in a complex128 result, unless the caller solves in place (S is read
     // by every sweep)
     const char *s0 = static_cast<const char *>(S), *v0 = static_cast<const char *>(V);
     const size_t bytes = (size_t)tau * n * 2 * sizeof(IO);
     const bool apart = sizeof(IO) == 4 || (s0 < v0 + bytes && v0 < s0 + bytes);
-    double *x = apart ? reinterpret_cast<double *>(p) : static_cast<double *>(V);
+    double *x = static_cast<double *>(V);
+    if (apart) {
+        x = reinterpret_cast<double *>(B[1]);
+        B[1] = nullptr;
+    }
     const ZipShares zs{dn.aP, dn.aI, dn.aZ};
     const auto *A = reinterpret_cast<const d2x *>(dn.AL64);
     const auto *w = reinterpret_cast<const d2x *>(dn.wl);
@@ -424,17 +438,20 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
                                    : gemm64_split_kernel<1, 1, 8, IO>;
     const int threads = edge == 16 ? 512 : 256;
     const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(edge));
-    const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + 255) / 256);
+    const int cpb = apart ? finish_chunk(n) : 256;
+    const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + cpb - 1) / cpb);
     const unsigned long long thr = square_bound(tol);
     const int seq = ++dn.solve_seq;
     for (int sweep = 0; sweep < max_iter; ++sweep) {
         if (all_retired(dn, seq)) break;
         const int cur = sweep & 1;
         int *cr = cnt + sweep % 3, *cn = cnt + (sweep + 1) % 3, *cz = cnt + (sweep + 2) % 3;
-        hipLaunchKernelGGL(gemm, dim3(g_mm), dim3(threads), 0, st, A, L.KT, B[cur], B[cur ^ 1], L.KB,
-                           act[cur], cr, row_blocks, w, n, (const IO *)S, zs, x, dmax);
-        hipLaunchKernelGGL((finish64_kernel<IO>), dim3(g_fin), dim3(256), 0, st, act[cur], cr, cz, x, n, thr, max_iter,
-                           dmax, iters, status, (IO *)V, apart, act[cur ^ 1], cn, dn.done_dev, seq);
+        hipLaunchKernelGGL(gemm, dim3(g_mm), dim3(threads), 0, st, A, L.KT, apart ? B[0] : B[cur],
+                           apart ? nullptr : B[cur ^ 1], L.KB, act[cur], cr, row_blocks, w, n, (const IO *)S, zs, x,
+                           dmax);
+        hipLaunchKernelGGL((finish64_kernel<IO>), dim3(g_fin), dim3(256), 0, st, act[cur], cr, cz, x, n,
+                           (const IO *)S, zs, L.KB, B[0], thr, max_iter, dmax, iters, status, (IO *)V, apart, cpb,
+                           act[cur ^ 1], cn, dn.done_dev, seq);
     }
     return TPF_OK;
 }

@@ -44,8 +44,17 @@ __device__ __forceinline__ int chunk_slot(bool stay, int *counter, int *wsum, in
 // Whether a sweep of solve `seq` already found every column retired: the sweeps queued
 // after it would all exit at once, so the host queues no more.  A read of pinned host
 // memory; it never waits for the device.
-static bool all_retired(const DeviceNet &dn, int seq) {
+[[maybe_unused]] static bool all_retired(const DeviceNet &dn, int seq) {
     return dn.done_host && __atomic_load_n(dn.done_host, __ATOMIC_ACQUIRE) == seq;
+}
+
+// Columns per finish chunk: about 16,384 buses' worth, a power of two in [4, 256] (one
+// atomic per chunk keeps a million-column sweep from serialising on the list counter,
+// and small chunks keep a few wide columns spread over many wavefronts).
+[[maybe_unused]] static int finish_chunk(int n) {
+    int c = 4;
+    while (c < 256 && 2 * c * n <= 16384) c *= 2;
+    return c;
 }
 
 // Fixed grids of the queued sweeps: enough blocks to fill the chip, few enough that a
@@ -57,7 +66,7 @@ constexpr int64_t kGemmGrid = 1024, kFinishGrid = 1024;
 // resident ones would start only after others had finished all of theirs and run the
 // kernel's second half at a fraction of the occupancy (the 16-bit GEMM, three blocks per
 // CU for its 43 KB of LDS, took twice as long with 1,024 blocks).
-static int64_t gemm_grid(const void *kernel, int threads, int64_t tiles) {
+[[maybe_unused]] static int64_t gemm_grid(const void *kernel, int threads, int64_t tiles) {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1)
         per_cu = 1;

@@ -191,7 +191,7 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
             !h2d(dn.Ah, fh.data(), nl * 2) || !h2d(dn.Al, fl.data(), nl * 2))
             return fail(TPF_ERR_DEVICE, "host-to-device copy failed (network staging)");
     }
-    // ---- large-network operator (FP64 beyond the register kernels, FP32 beyond 128 buses)
+    // ---- operators beyond the register kernels (FP64 from 321 buses, FP32 family from 129)
     if (n > 128) {
         const int KP = (2 * n + 15) / 16 * 16, K16 = (2 * n + 31) / 32 * 32;
         const int M32 = (2 * n + 127) / 128 * 128;
@@ -204,13 +204,15 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
         int e = 0;
         (void)std::frexp(zmax > 0 ? zmax : 1.0, &e);
         dn.sZ = 14 - e;  // FP16 operand Z 2^sZ: largest entry just below 2^14
-        if (hipHostMalloc((void **)&dn.done_host, 256, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
-            dn.done_host = nullptr;
-            return fail(TPF_ERR_OOM, "pinned host allocation failed (network staging)");
+        if (n > kMaxMidBuses) {  // the per-sweep paths
+            if (hipHostMalloc((void **)&dn.done_host, 256, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+                dn.done_host = nullptr;
+                return fail(TPF_ERR_OOM, "pinned host allocation failed (network staging)");
+            }
+            *dn.done_host = 0;
+            if (hipHostGetDevicePointer((void **)&dn.done_dev, dn.done_host, 0) != hipSuccess)
+                return fail(TPF_ERR_DEVICE, "pinned host word not mapped (network staging)");
         }
-        *dn.done_host = 0;
-        if (hipHostGetDevicePointer((void **)&dn.done_dev, dn.done_host, 0) != hipSuccess)
-            return fail(TPF_ERR_DEVICE, "pinned host word not mapped (network staging)");
         std::vector<double> a64;
         if (n > 8 * kMaxSmallTiles) {
             const int KT = large64_ksteps(n), tiles = (n + 63) / 64 * 4;
@@ -223,8 +225,20 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
                     f[1] = z.imag();
                 }
         }
-        std::vector<float> a32((size_t)M32 * KP, 0.0f);
-        std::vector<uint16_t> abf((size_t)M32 * K16, 0), ah((size_t)M32 * K16, 0);
+        // FP32 family: fragments for the persistent kernel, row-major beyond it
+        const bool mid = n <= kMaxMidBuses;
+        const int MT = (2 * n + 15) / 16;
+        const size_t n32 = mid ? (size_t)MT * MT * 256 : (size_t)M32 * KP;
+        const size_t n16 = mid ? (size_t)MT * (K16 / 32) * 512 : (size_t)M32 * K16;
+        std::vector<float> a32(n32, 0.0f);
+        std::vector<uint16_t> abf(n16, 0), ah(n16, 0);
+        auto at32 = [&](int r, int k) {
+            return mid ? (((size_t)(r / 16) * MT + k / 16) * 64 + 16 * (k % 4) + r % 16) * 4 + k % 16 / 4 : (size_t)r * KP + k;
+        };
+        auto at16 = [&](int r, int k) {
+            return mid ? (((size_t)(r / 16) * (K16 / 32) + k / 32) * 64 + 16 * (k % 32 / 8) + r % 16) * 8 + k % 8
+                       : (size_t)r * K16 + k;
+        };
         std::vector<double> wn(2 * n);
         for (int i = 0; i < n; ++i) {
             wn[2 * i] = net.w[i].real();
@@ -234,18 +248,23 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
                 const double blk[2][2] = {{z.real(), -z.imag()}, {z.imag(), z.real()}};
                 for (int pi = 0; pi < 2; ++pi)
                     for (int pk = 0; pk < 2; ++pk) {
-                        a32[(size_t)(2 * i + pi) * KP + 2 * k + pk] = (float)blk[pi][pk];
-                        abf[(size_t)(2 * i + pi) * K16 + 2 * k + pk] = to_bf16((float)blk[pi][pk]);
-                        ah[(size_t)(2 * i + pi) * K16 + 2 * k + pk] = to_f16((float)std::ldexp(blk[pi][pk], dn.sZ));
+                        a32[at32(2 * i + pi, 2 * k + pk)] = (float)blk[pi][pk];
+                        const size_t o = at16(2 * i + pi, 2 * k + pk);
+                        abf[o] = to_bf16((float)blk[pi][pk]);
+                        ah[o] = to_f16((float)std::ldexp(blk[pi][pk], dn.sZ));
                     }
             }
         }
-        if ((!a64.empty() && !dalloc((void **)&dn.AL64, a64.size() * 8)) || !dalloc((void **)&dn.AL32, a32.size() * 4) ||
-            !dalloc((void **)&dn.ALbf, abf.size() * 2) || !dalloc((void **)&dn.ALh, ah.size() * 2) ||
+        if ((!a64.empty() && !dalloc((void **)&dn.AL64, a64.size() * 8)) ||
+            !dalloc((void **)(mid ? &dn.AM32 : &dn.AL32), a32.size() * 4) ||
+            !dalloc((void **)(mid ? &dn.AMbf : &dn.ALbf), abf.size() * 2) ||
+            !dalloc((void **)(mid ? &dn.AMh : &dn.ALh), ah.size() * 2) ||
             !dalloc((void **)&dn.wl, wn.size() * 8))
             return fail(TPF_ERR_OOM, "device allocation failed (network staging)");
-        if ((!a64.empty() && !h2d(dn.AL64, a64.data(), a64.size() * 8)) || !h2d(dn.AL32, a32.data(), a32.size() * 4) ||
-            !h2d(dn.ALbf, abf.data(), abf.size() * 2) || !h2d(dn.ALh, ah.data(), ah.size() * 2) ||
+        if ((!a64.empty() && !h2d(dn.AL64, a64.data(), a64.size() * 8)) ||
+            !h2d(mid ? dn.AM32 : dn.AL32, a32.data(), a32.size() * 4) ||
+            !h2d(mid ? dn.AMbf : dn.ALbf, abf.data(), abf.size() * 2) ||
+            !h2d(mid ? dn.AMh : dn.ALh, ah.data(), ah.size() * 2) ||
             !h2d(dn.wl, wn.data(), wn.size() * 8))
             return fail(TPF_ERR_DEVICE, "host-to-device copy failed (network staging)");
     }

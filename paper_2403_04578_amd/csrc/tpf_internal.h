@@ -19,6 +19,10 @@ using cd = std::complex<double>;
 // Register-resident sweep kernels: n <= 8 * kMaxSmallTiles.
 constexpr int kMaxSmallTiles = 40;
 
+// Persistent FP32-family kernel beyond the register-resident ones: the drops, operands and
+// schedule of a batch of columns fill the LDS and registers of a workgroup at this size.
+constexpr int kMaxMidBuses = 320;
+
 // FP64: MT = ceil(n / 16) tiles of 16 buses over NW waves, at most TPW each; no more waves
 // than tiles, so that small networks pay for fewer waves at their barriers.
 inline void f64_config(int MT, int &NW, int &TPW) {
@@ -60,7 +64,7 @@ struct DeviceNet {
     uint16_t *Al = nullptr;      // FP16 residual Z 2^sZ - Ah, same layout
     // Large-network path (fpi_large.hip).  FP64 (n > 8 kMaxSmallTiles): fragments of Z
     // [16-bus tiles, a multiple of 4][large64_ksteps][64 lanes][Re, Im].  FP32 family
-    // (n > 128): operator [MPL32][KPL] row-major, rows and K interleaved Re/Im per bus.
+    // (n > kMaxMidBuses): operator [MPL32][KPL] row-major, rows and K interleaved Re/Im per bus.
     // wl = w as [n][2].  The 16-bit operands (BF16 Z, FP16 Z 2^sZ) have K padded to KPL16, a
     // multiple of 32.
     int MPL32 = 0, KPL = 0, KPL16 = 0;
@@ -68,6 +72,11 @@ struct DeviceNet {
     float *AL32 = nullptr;
     uint16_t *ALbf = nullptr, *ALh = nullptr;
     double *wl = nullptr;
+    // FP32 family for 128 < n <= kMaxMidBuses (fpi_mid.hip): fragments of the operator (rows and
+    // K interleaved Re/Im per bus), [16-row tiles][K groups of 16][64 lanes][4 k-steps] FP32 and
+    // [16-row tiles][32-wide k-steps][64 lanes][8] 16-bit.
+    float *AM32 = nullptr;
+    uint16_t *AMbf = nullptr, *AMh = nullptr;
     // Large path: a pinned host word, mapped for the device (done_dev), to which a sweep
     // that finds no active column posts its solve's sequence number; the host loop that
     // queues the sweeps reads it without waiting and stops queueing once it matches.
@@ -159,6 +168,9 @@ int launch_fpi_tree(const tpf_network_s &net, const DeviceNet &dn, int mode, con
 int launch_fpi_mixed(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype,
                      int64_t tau, double tol, int max_iter, const void *V0, void *V, int32_t *iters,
                      int8_t *status, unsigned long long *queue, hipStream_t stream);
+int launch_fpi_mid(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype, int64_t tau,
+                   double tol, int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
+                   unsigned long long *queue, hipStream_t stream);
 int launch_fpi_large(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype,
                      int64_t tau, double tol, int max_iter, const void *V0, void *V, int32_t *iters,
                      int8_t *status, void *workspace, hipStream_t stream);
