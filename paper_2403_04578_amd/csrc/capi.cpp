@@ -98,16 +98,10 @@ int solve_impl(tpf_network net, const void *S, int32_t dtype, int64_t T, double 
                               workspace, st);
     } else if (n <= 8 * kMaxSmallTiles) {
         auto *queue = reinterpret_cast<unsigned long long *>(workspace);
-        if (mode == TPF_MODE_FP64) {
-            rc = launch_fpi_small_f64(*net, *dn, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out,
-                                      queue, st);
-        } else {
-            rc = launch_zero_u64(queue, 1, st);
-            if (rc == TPF_OK) rc = check_launch("queue reset");
-            if (rc == TPF_OK)
-                rc = launch_fpi_mixed(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out,
-                                      queue, st);
-        }
+        rc = mode == TPF_MODE_FP64 ? launch_fpi_small_f64(*net, *dn, S, dtype, T, tol, max_iter, V0, V_out, iters_out,
+                                                          status_out, queue, st)
+                                   : launch_fpi_mixed(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out,
+                                                      iters_out, status_out, queue, st);
     } else {
         return fail(TPF_ERR_UNSUPPORTED, "no sweep path for this network size and mode");
     }

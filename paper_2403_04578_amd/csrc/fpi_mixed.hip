@@ -271,6 +271,15 @@ __global__ __launch_bounds__(NW * 64) void fpi_mixed_kernel(
             }
         }
     };
+    // The first batches are dealt by block, the others by the queue (past the first NC
+    // gridDim.x columns); when the first ones are all, it is not touched, nor cleared by the
+    // launch.
+    bool first = true;
+    auto claim = [&]() -> unsigned long long {
+        const unsigned long long dealt = (unsigned long long)NC * gridDim.x;
+        return dealt >= (unsigned long long)tau ? (unsigned long long)tau
+                                                : dealt + atomicAdd(queue, (unsigned long long)NC);
+    };
     bool from_pf = false;  // this refill's batch was claimed ahead and its rows copied
     int slot = 1;          // qb[slot]: the batch whose rows are being copied
     auto refill = [&]() -> bool {
@@ -278,7 +287,10 @@ __global__ __launch_bounds__(NW * 64) void fpi_mixed_kernel(
             rsm[tid] = 0.0f;
             rok[tid] = 0;
         }
-        if (tid == 0 && !from_pf) qb[0] = atomicAdd(queue, (unsigned long long)NC);
+        if (tid == 0 && !from_pf) {
+            qb[0] = first ? (unsigned long long)NC * blockIdx.x : claim();
+            first = false;
+        }
         if (from_pf) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wavefront's copies landed
         __syncthreads();
         const unsigned long long base = from_pf ? qb[slot] : qb[0];
@@ -302,7 +314,7 @@ __global__ __launch_bounds__(NW * 64) void fpi_mixed_kernel(
         // claim the batch after this one now; the atomic's latency overlaps the loads below
         unsigned long long next = (unsigned long long)tau;
         if (kPfS && tid == 0 && base + NC < (unsigned long long)tau)
-            next = atomicAdd(queue, (unsigned long long)NC);
+            next = claim();
 #pragma unroll
         for (int c = 0; c < CG; ++c) {
             const long long cc = (long long)base + 16 * c + j;
@@ -640,6 +652,10 @@ static int launch_one(const tpf_network_s &net, const DeviceNet &dn, const void 
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const long long blocks = std::min<long long>((long long)cus * per_cu, (tau + (long long)NC - 1) / (long long)NC);
+    if ((long long)NC * blocks < tau) {  // the batches past the first come from the queue
+        const int rc = launch_zero_u64(queue, 1, stream);
+        if (rc != TPF_OK) return rc;
+    }
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NW * 64), lds, stream, (const IO *)S, (IO *)V, iters,
                        status, (const IO *)V0, dn.A32, MODE == TPF_MODE_MIXED_BF16 ? dn.Abf : dn.Ah, dn.Al,
                        dn.w32, net.n, MT, dn.sZ, (long long)tau, (float)tol, max_iter, queue, dn.aP, dn.aI,
