@@ -22,6 +22,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "device_math.h"
 #include "tpf_internal.h"
 
 namespace tpf {
@@ -51,15 +52,6 @@ template <int TPW>
 struct SlotState {
     d4 vr[TPW], vi[TPW], sr[TPW], si[TPW];
 };
-
-// 1 / x for a finite positive x: the hardware estimate and two Newton steps (within an ulp).
-// The compiler's division spends eleven vector instructions where this takes five, and
-// vector instructions take their issue slots from the FP64 matrix products (see below).
-__device__ __forceinline__ double reciprocal(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-    return __builtin_fma(__builtin_fma(-x, y, 1.0), y, y);
-}
 
 // a - b of the rounded terms, whatever products they came from: the third product's operand
 // has to be the difference of the values the other two use.

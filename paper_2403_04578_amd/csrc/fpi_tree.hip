@@ -18,6 +18,9 @@
 // workgroup barrier is needed.  Columns are dealt to the slots round robin.  Per sweep
 // each column reads and writes only LDS and registers; S, V0 and the result cross HBM
 // once.
+#include <algorithm>
+
+#include "device_math.h"
 #include "tpf_internal.h"
 
 namespace tpf {
@@ -971,12 +974,417 @@ int launch_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int6
     return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 1,024 PQ buses");
 }
 
+// ---- shallow trees
+//
+// Feeders grown as k-ary trees have few, wide levels (99 buses: 3, 12, 36, 48), so the levels
+// can be laid out as whole rows of a column's LPC lanes: row r holds up to LPC positions of
+// one level, lane sl of the column owns slot r LPC + sl for the whole solve, and its places
+// (children, parent) are registers instead of tables read from LDS at every visit.  The
+// injection is formed where the backward pass needs it and V' where the forward pass makes
+// the drop, so that a position costs its children's reads and two writes per sweep.  The
+// kernels above visit a level's positions through the tables (four dependent LDS reads per
+// visit) and serve the trees whose rows do not fit B registers (long chains).  Sums and
+// roundings are those of the kernels above.
+//
+// Bound by the chain of LDS round trips, one per row and pass, between which a wavefront
+// waits; reading the next row's operands ahead did not pay (registers cost a wavefront per
+// SIMD: 998 against 888 us at 99 buses, 525,600 columns, FP64).  Loading a column without
+// branches, all rows in flight together, took the three-phase FP32 kernel from 1,373 to
+// 1,008 us (99 buses, 262,800 columns).
+template <typename R>
+struct Pair2v {
+    typedef R T __attribute__((ext_vector_type(2)));
+};
+
+__device__ __forceinline__ double inverse_square(double m2) { return reciprocal(m2); }
+__device__ __forceinline__ float inverse_square(float m2) { return reciprocal32(fmaxf(m2, kMinV2)); }
+
+// R: double keeps the state V, float the drop U = V - w.  PH phases per bus, ZIP: constant-power
+// and constant-current shares (single-phase).
+template <typename IO, typename R, int CPW, int B, int PH, bool ZIP>
+__global__ __launch_bounds__(kTreeWaves * 64) void fpi_tree_rows_kernel(
+    const IO *__restrict__ S, IO *__restrict__ Vout, int32_t *__restrict__ iters_out,
+    int8_t *__restrict__ status_out, const IO *__restrict__ V0, const int32_t *__restrict__ tree_i,
+    const double *__restrict__ tree_z, int nb, int levels, int rows, long long tau, R tol, int max_iter,
+    const double *__restrict__ aP, const double *__restrict__ aI) {
+    typedef typename Pair2v<R>::T c2;
+    typedef IO io2 __attribute__((ext_vector_type(2)));
+    constexpr bool kDrop = sizeof(R) == 4;  // the state is the drop from w
+    constexpr int LPC = 64 / CPW, NT = kTreeWaves * 64, TZ = 2 * (PH * PH + PH);
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int slots = rows * LPC, col = slots + 1;  // slot `slots`: the slack, and children that are not there
+    const int n = PH * nb;
+    c2 *Jw = reinterpret_cast<c2 *>(smem);                    // [waves][CPW][col][PH] currents, then drops
+    c2 *zt = Jw + kTreeWaves * CPW * PH * col;                // [slots][PH][PH] branch impedances
+    c2 *wt = zt + PH * PH * slots;                            // [slots][PH] w
+    double *wd = reinterpret_cast<double *>(wt + PH * slots); // [slots][PH][2] w in FP64 (kDrop)
+    R *za = reinterpret_cast<R *>(wd + (kDrop ? 2 * PH * slots : 0));  // [2][slots] shares (ZIP)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int slot = lane / LPC;
+    int sl = lane % LPC;
+    const int32_t *ls = tree_i + 4 * (nb + 1);
+
+    // slot of a breadth-first position in level L, whose rows start at row0
+    auto walk = [&](auto visit) {  // levels in order: (level, its first row)
+        int row0 = 0;
+        for (int L = 1; L <= levels; ++L) {
+            visit(L, row0);
+            row0 += (ls[L + 1] - ls[L] + LPC - 1) / LPC;
+        }
+    };
+    for (int e = threadIdx.x; e < slots; e += NT) {
+        int p = -1;
+        walk([&](int L, int row0) {
+            const int next = row0 + (ls[L + 1] - ls[L] + LPC - 1) / LPC;
+            if (e >= row0 * LPC && e < next * LPC) p = ls[L] + e - row0 * LPC < ls[L + 1] ? ls[L] + e - row0 * LPC : -1;
+        });
+        for (int k = 0; k < PH * PH; ++k)
+            zt[PH * PH * e + k] = p < 0 ? c2{0, 0} : c2{(R)tree_z[TZ * p + 2 * k], (R)tree_z[TZ * p + 2 * k + 1]};
+        for (int f = 0; f < PH; ++f) {
+            const double wr = p < 0 ? 1.0 : tree_z[TZ * p + 2 * PH * PH + 2 * f];
+            const double wi = p < 0 ? 0.0 : tree_z[TZ * p + 2 * PH * PH + 2 * f + 1];
+            wt[PH * e + f] = c2{(R)wr, (R)wi};
+            if constexpr (kDrop) wd[2 * (PH * e + f)] = wr, wd[2 * (PH * e + f) + 1] = wi;
+        }
+        if constexpr (ZIP) {
+            za[e] = p < 0 ? (R)0 : (R)aP[tree_i[4 * p]];
+            za[slots + e] = p < 0 ? (R)0 : (R)aI[tree_i[4 * p]];
+        }
+    }
+    // the lane's places: parent and first child (slots), children and bus (PQ index) per row
+    uint32_t place[B], extra[B];
+#pragma unroll
+    for (int r = 0; r < B; ++r) place[r] = (uint32_t)slots | ((uint32_t)slots << 16), extra[r] = 0xffffu;
+    walk([&](int L, int row0) {
+        const int prev0 = L > 1 ? row0 - (ls[L] - ls[L - 1] + LPC - 1) / LPC : 0;
+        const int next0 = row0 + (ls[L + 1] - ls[L] + LPC - 1) / LPC;
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            const int p = ls[L] + (r - row0) * LPC + sl;
+            if (r >= row0 && r < next0 && p < ls[L + 1]) {
+                const int par = tree_i[4 * p + 1], c0 = tree_i[4 * p + 2], c1 = tree_i[4 * p + 3];
+                const int ps = L > 1 ? prev0 * LPC + par - ls[L - 1] : slots;
+                const int cs = c1 > c0 ? next0 * LPC + c0 - ls[L + 1] : slots;
+                place[r] = (uint32_t)ps | ((uint32_t)cs << 16);
+                extra[r] = (uint32_t)tree_i[4 * p] | ((uint32_t)(c1 - c0) << 16);
+            }
+        }
+    });
+    c2 *J = Jw + (wave * CPW + slot) * PH * col;
+    if (sl == 0)
+        for (int f = 0; f < PH; ++f) J[PH * slots + f] = c2{0, 0};
+    __syncthreads();
+
+    // Column slots take columns round robin; a slot that finishes a column loads its next
+    // one at once, so the slots of a wavefront may be at different sweeps.
+    const long long nslots = (long long)gridDim.x * kTreeWaves * CPW;
+    long long c = ((long long)blockIdx.x * kTreeWaves + wave) * CPW + slot;
+    c2 s[B][PH], v[B][PH];
+    int it = 0;
+    auto load = [&]() __attribute__((always_inline)) {
+        // The rows are loaded without branches (places without a bus read the column's first
+        // value), so that the loads of CH rows are in flight together.
+        constexpr int CH = kDrop ? (12 + PH - 1) / PH : B;
+        const long long base = (c < tau ? c : tau - 1) * n;
+        io2 in[CH][PH];
+        auto rows_of = [&](const IO *X, int r0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < CH; ++r) {
+                const int q = r0 + r < B ? (int)(extra[r0 + r] & 0xffff) : 0xffff;
+#pragma unroll
+                for (int f = 0; f < PH; ++f)
+                    in[r][f] = reinterpret_cast<const io2 *>(X)[base + (q != 0xffff ? PH * q + f : 0)];
+            }
+        };
+        int ok = 1;
+#pragma unroll
+        for (int r0 = 0; r0 < B; r0 += CH) {
+            rows_of(S, r0);
+#pragma unroll
+            for (int r = r0; r < B && r < r0 + CH; ++r) {
+                const bool on = c < tau && (extra[r] & 0xffff) != 0xffff;
+#pragma unroll
+                for (int f = 0; f < PH; ++f) {
+                    s[r][f] = on ? c2{(R)in[r - r0][f].x, (R)in[r - r0][f].y} : c2{0, 0};
+                    asm volatile("" : "+v"(s[r][f]));  // narrowed here, not past the last row
+                }
+            }
+        }
+        if (V0) {
+#pragma unroll
+            for (int r0 = 0; r0 < B; r0 += CH) {
+                rows_of(V0, r0);
+#pragma unroll
+                for (int r = r0; r < B && r < r0 + CH; ++r) {
+                    const bool on = c < tau && (extra[r] & 0xffff) != 0xffff;
+                    const int e = on ? r * LPC + sl : 0;
+#pragma unroll
+                    for (int f = 0; f < PH; ++f) {
+                        const double vr = (double)in[r - r0][f].x, vi = (double)in[r - r0][f].y;
+                        const double m2 = vr * vr + vi * vi;
+                        ok &= !on || (m2 >= 0.25 && m2 <= 2.25) ? 1 : 0;
+                        const double *w = wd + 2 * (PH * e + f);
+                        if constexpr (kDrop)
+                            v[r][f] = on ? c2{(R)(vr - w[0]), (R)(vi - w[1])} : c2{0, 0};
+                        else
+                            v[r][f] = on ? c2{(R)vr, (R)vi} : c2{1, 0};
+                        asm volatile("" : "+v"(v[r][f]), "+v"(ok));  // formed here, not past the last row
+                    }
+                }
+            }
+#pragma unroll
+            for (int off = LPC / 2; off > 0; off >>= 1) ok &= __shfl_xor(ok, off);
+        }
+        if (!V0 || !ok) {  // flat start, also where the guard failed somewhere in the column
+#pragma unroll
+            for (int r = 0; r < B; ++r)
+#pragma unroll
+                for (int f = 0; f < PH; ++f) {
+                    v[r][f] = kDrop ? c2{0, 0} : c2{1, 0};
+                    if (kDrop && r < rows) {
+                        const double *w = wd + 2 * (PH * (r * LPC + sl) + f);
+                        v[r][f] = c2{(R)(1.0 - w[0]), (R)(0.0 - w[1])};
+                    }
+                }
+        }
+        it = 0;
+    };
+    load();
+    while (__ballot(c < tau)) {
+        const bool live = c < tau;
+        // backward pass, deepest rows first: J_b = I_b + the sum of its children's J
+#pragma unroll
+        for (int r = B - 1; r >= 0; --r) {
+            if (r >= rows) continue;
+            asm volatile("" : "+v"(place[r]), "+v"(extra[r]), "+v"(sl));  // (keeps the addresses out of registers)
+            const int e = r * LPC + sl, cs = place[r] >> 16, cnt = extra[r] >> 16;
+            c2 j[PH];
+#pragma unroll
+            for (int f = 0; f < PH; ++f) {
+                R vr = v[r][f].x, vi = v[r][f].y;
+                const R sr = s[r][f].x, si = s[r][f].y;
+                if constexpr (kDrop) {
+                    const c2 w = wt[PH * e + f];
+                    vr = w.x + vr, vi = w.y + vi;
+                }
+                const R inv = inverse_square(vr * vr + vi * vi);
+                R ir = (sr * vr + si * vi) * inv, ii = (sr * vi - si * vr) * inv;
+                if constexpr (ZIP) {
+                    const R ap = za[e], ai = za[slots + e];
+                    ir = ap * ir + ai * sr;
+                    ii = ap * ii - ai * si;
+                }
+                if constexpr (kDrop) asm volatile("" : "+v"(ir), "+v"(ii));  // rounded before the sum, not fused with it
+                j[f] = c2{ir, ii};
+            }
+            for (int k = 0; __ballot(k < cnt); k += 2) {
+                // two children at a time; the ones that are not there read the zero slot
+                const int a = k < cnt ? cs + k : slots, b = k + 1 < cnt ? cs + k + 1 : slots;
+                c2 x[PH], y[PH];
+#pragma unroll
+                for (int f = 0; f < PH; ++f) x[f] = J[PH * a + f], y[f] = J[PH * b + f];
+#pragma unroll
+                for (int f = 0; f < PH; ++f) {
+                    j[f].x += x[f].x;
+                    j[f].y += x[f].y;
+                    j[f].x += y[f].x;
+                    j[f].y += y[f].y;
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < PH; ++f) J[PH * e + f] = j[f];
+            wave_sync();
+        }
+        // forward pass, slack first: D_b = D_parent + z_b J_b in place of J_b; V' = w - D
+        R dmax = 0, poison = 0;
+#pragma unroll
+        for (int r = 0; r < B; ++r) {
+            if (r >= rows) continue;
+            asm volatile("" : "+v"(place[r]), "+v"(sl));
+            const int e = r * LPC + sl, ps = place[r] & 0xffff;
+            c2 j[PH], d[PH];
+#pragma unroll
+            for (int f = 0; f < PH; ++f) j[f] = J[PH * e + f], d[f] = J[PH * ps + f];
+#pragma unroll
+            for (int a = 0; a < PH; ++a) {
+                if constexpr (PH == 1) {
+                    const c2 z = zt[e];
+                    const R pr = d[0].x, pi = d[0].y;
+                    d[0].x = pr + z.x * j[0].x - z.y * j[0].y;
+                    d[0].y = pi + z.x * j[0].y + z.y * j[0].x;
+                } else {
+#pragma unroll
+                    for (int b = 0; b < PH; ++b) {
+                        const c2 z = zt[PH * PH * e + PH * a + b];
+                        d[a].x += z.x * j[b].x - z.y * j[b].y;
+                        d[a].y += z.x * j[b].y + z.y * j[b].x;
+                    }
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < PH; ++f) {
+                J[PH * e + f] = d[f];
+                R nr, ni;
+                if constexpr (kDrop) {
+                    nr = -d[f].x, ni = -d[f].y;
+                } else {
+                    const c2 w = wt[PH * e + f];
+                    nr = w.x - d[f].x, ni = w.y - d[f].y;
+                }
+                const R er = nr - v[r][f].x, ei = ni - v[r][f].y;
+                const R q = er * er + ei * ei;
+                poison = kDrop ? __builtin_fmaf((float)q, 0.0f, (float)poison)
+                               : __builtin_fma((double)q, 0.0, (double)poison);  // NaN once a step is not finite
+                dmax = q > dmax ? q : dmax;
+                v[r][f] = c2{nr, ni};
+            }
+            wave_sync();
+        }
+        int bad = poison == 0 ? 0 : 1;
+#pragma unroll
+        for (int off = LPC / 2; off > 0; off >>= 1) {
+            const R o = __shfl_xor(dmax, off);
+            dmax = o > dmax ? o : dmax;
+            bad |= __shfl_xor(bad, off);
+        }
+        ++it;
+        const bool conv = !bad && (kDrop ? sqrtf((float)dmax) < (float)tol : sqrt((double)dmax) < (double)tol);
+        if (live && (bad || conv || it >= max_iter)) {
+#pragma unroll
+            for (int r = 0; r < B; ++r) {
+                const int q = extra[r] & 0xffff;
+#pragma unroll
+                for (int f = 0; f < PH; ++f)
+                    if (q != 0xffff) {
+                        const int e = 2 * (PH * (r * LPC + sl) + f);
+                        io2 o;
+                        if constexpr (kDrop)
+                            o = io2{(IO)(wd[e] + (double)v[r][f].x), (IO)(wd[e + 1] + (double)v[r][f].y)};
+                        else
+                            o = io2{(IO)v[r][f].x, (IO)v[r][f].y};
+                        reinterpret_cast<io2 *>(Vout)[c * n + PH * q + f] = o;
+                    }
+            }
+            if (sl == 0) {
+                iters_out[c] = it;
+                status_out[c] = bad ? TPF_ST_NONFINITE : (conv ? TPF_ST_CONVERGED : TPF_ST_MAX_ITER);
+            }
+            c += nslots;
+            load();
+        }
+        wave_sync();
+    }
+}
+
+// Rows of LPC lanes that a network's levels take.
+int level_rows(const tpf_network_s &net, int LPC) {
+    int rows = 0;
+    const int levels = (int)net.tree_level_start.size() - 2;
+    for (int L = 1; L <= levels; ++L)
+        rows += (net.tree_level_start[L + 1] - net.tree_level_start[L] + LPC - 1) / LPC;
+    return rows;
+}
+
+// Launches the row kernel; TPF_ERR_UNSUPPORTED (nothing launched) when the tree's rows or
+// their LDS do not fit.
+template <typename IO, typename R, int CPW, int B, int PH, bool ZIP>
+int launch_rows_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
+                   const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
+    const int nb = net.n / PH, rows = level_rows(net, 64 / CPW), slots = rows * (64 / CPW);
+    const size_t c2 = 2 * sizeof(R);
+    const size_t lds = (size_t)kTreeWaves * CPW * PH * (slots + 1) * c2 + (size_t)(PH * PH + PH) * slots * c2 +
+                       (sizeof(R) == 4 ? (size_t)PH * slots * 16 : 0) + (ZIP ? (size_t)2 * slots * sizeof(R) : 0);
+    if (rows > B || nb >= 0xffff || lds > (size_t)160 * 1024) return TPF_ERR_UNSUPPORTED;
+    auto k = fpi_tree_rows_kernel<IO, R, CPW, B, PH, ZIP>;
+    if (hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return fail(TPF_ERR_DEVICE, "hipFuncSetAttribute failed");
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kTreeWaves * 64, lds) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    const long long per_block = (long long)kTreeWaves * CPW;
+    const long long blocks =
+        std::max<long long>(1, std::min<long long>((long long)num_cus() * per_cu, (tau + per_block - 1) / per_block));
+    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kTreeWaves * 64), lds, st, (const IO *)S, (IO *)V, iters, status,
+                       (const IO *)V0, dn.tree_i, dn.tree_z, nb, dn.tree_levels, rows, (long long)tau, (R)tol, max_iter,
+                       (const double *)dn.aP, (const double *)dn.aI);
+    return TPF_OK;
+}
+
+// Lanes per column and registers per lane: the fewest padded lanes per column whose state
+// still leaves two wavefronts per SIMD, with rows close to B (a lane's B places are loaded and
+// looped over, used or not).  Measured against the table kernels, us: one phase, 50,000
+// columns, FP64 / FP32: 19 buses 20.7 (28.1) / 17.8 (18.4); 59: 50.1 (67.1) / -; 99 buses,
+// 525,600 columns: 887 (1,349) / 672 (771); 127: 108 (194) / 78 (94); 199: 199 (335) / -;
+// 299: 393 (639) / 269 (273); 399: 614 (794) / 327 (579); 499: 721 (1,091) / 471 (481); 999:
+// 3,695 (4,774) / 1,671 (2,293).  Three phases, 20,000 columns: 39 buses 60 (149) / 44 (64);
+// 79: 153 (270) / 94 (104); 119: 288 (394) / -; 99 buses, 262,800 columns, FP32: 1,024 (1,502).
+// Left to the table kernels (the dashes), which were faster: FP32 with 9 rows of 8 lanes but 6
+// of 16 (59 buses, 40.7 against 38.7), FP32 up to 256 buses with over 10 rows of 16 (159:
+// 137.9 against 120.8), FP64 up to 730 buses with over 12 rows of 64 (699: 2,844 against
+// 2,237; the padded rows leave one workgroup per CU where the tables leave two), three-phase
+// FP32 with over 8 rows of 16 (119: 210 against 180).
+template <typename IO, typename R>
+int launch_rows(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
+                const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
+    constexpr bool kF64 = sizeof(R) == 8;
+    // (rows are at least the levels; a constant-impedance share needs the tables' G')
+    if (dn.aZ || dn.tree_levels > 20) return TPF_ERR_UNSUPPORTED;
+    const int r8 = level_rows(net, 8), r16 = level_rows(net, 16), r32 = level_rows(net, 32), r64 = level_rows(net, 64);
+#define TPF_ROWS3(C, B) \
+    return launch_rows_as<IO, R, C, B, 3, false>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st)
+#define TPF_ROWS(C, B)                                                                                           \
+    return dn.aP ? launch_rows_as<IO, R, C, B, 1, true>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st) \
+                 : launch_rows_as<IO, R, C, B, 1, false>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st)
+    if (dn.tree_phases == 3) {
+        if (r8 <= 4) TPF_ROWS3(8, 4);
+        if (r16 <= 5) TPF_ROWS3(4, 5);
+        if (r16 <= 8) TPF_ROWS3(4, 8);
+        if constexpr (kF64) {
+            if (r32 <= 8) TPF_ROWS3(2, 8);
+        }
+        return TPF_ERR_UNSUPPORTED;
+    }
+    if (r8 <= 4) TPF_ROWS(8, 4);
+    if (r8 <= 8) TPF_ROWS(8, 8);
+    if constexpr (kF64) {
+        if (r8 <= 10) TPF_ROWS(8, 10);
+    } else {
+        if (r16 <= 6) return TPF_ERR_UNSUPPORTED;
+    }
+    if (r16 <= 8) TPF_ROWS(4, 8);
+    if (r16 <= 10) TPF_ROWS(4, 10);
+    if constexpr (kF64) {
+        if (r16 <= 12) TPF_ROWS(4, 12);
+        if (r16 <= 15) TPF_ROWS(4, 15);
+        if (r32 <= 13) TPF_ROWS(2, 13);
+    } else {
+        if (net.n <= 256) return TPF_ERR_UNSUPPORTED;
+        if (r32 <= 13) TPF_ROWS(2, 13);
+        if (r32 <= 16) TPF_ROWS(2, 16);
+    }
+    if (r64 <= 12) TPF_ROWS(1, 12);
+    if (kF64 && net.n <= 730) return TPF_ERR_UNSUPPORTED;
+    TPF_ROWS(1, 20);
+#undef TPF_ROWS
+#undef TPF_ROWS3
+}
+
 }  // namespace
 
 int launch_fpi_tree(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype, int64_t tau,
                     double tol, int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
                     hipStream_t stream) {
     if (!dn.tree_i) return fail(TPF_ERR_UNSUPPORTED, "the tree operator needs a radial network (n_bus - 1 branches)");
+    if (net.n / dn.tree_phases <= (dn.tree_phases == 3 ? 512 : 1024)) {  // shallow trees: rows of lanes
+        const bool c128 = dtype == TPF_C128;
+        const int rc =
+            mode == TPF_MODE_TREE_FP32
+                ? (c128 ? launch_rows<double, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream)
+                        : launch_rows<float, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream))
+                : (c128 ? launch_rows<double, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream)
+                        : launch_rows<float, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream));
+        if (rc != TPF_ERR_UNSUPPORTED) return rc;
+    }
     if (mode == TPF_MODE_TREE_FP32) {
         if (dn.tree_phases == 3) {
             if (dtype == TPF_C128)

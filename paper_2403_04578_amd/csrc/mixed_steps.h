@@ -3,6 +3,7 @@
 // (fpi_mid.hip): both compute the same iterates bit for bit.
 #pragma once
 
+#include "device_math.h"
 #include "large_common.h"
 
 namespace tpf {
@@ -69,15 +70,6 @@ __device__ __forceinline__ float2 zip_injection(float ir, float ii, float sr, fl
         o.y += az * (sr * vi - si * vr);
     }
     return o;
-}
-
-// 1 / x, correctly rounded, for x from 1e-30 to 2^125: the hardware estimate and one Newton
-// step, equal to the division for every mantissa (checked over all of them) at three
-// instructions instead of ten.  Beyond, where an iterate has diverged and the injection
-// vanishes against any voltage, the estimate itself (0 for inf).
-__device__ __forceinline__ float reciprocal32(float x) {
-    const float y = __builtin_amdgcn_rcpf(x);
-    return x < 0x1p125f ? __builtin_fmaf(__builtin_fmaf(-x, y, 1.0f), y, y) : y;
 }
 
 // FP32 injection of one bus with load s and drop u from w.
