@@ -110,12 +110,15 @@ def ingest_pmc(fetch_dir: str, write_dir: str):
 
     def mixed(mode):  # fpi_mixed_kernel<TPW, NW, KTL, MODE, CG, PF, IO>
         return lambda k: (targs(k, "fpi_mixed_kernel") or [""] * 4)[3] == mode
+
+    def rows(state):  # fpi_tree_rows_kernel<IO, R, CPW, B, PH, ZIP>
+        return lambda k: (targs(k, "fpi_tree_rows_kernel") or [""] * 2)[1] == state
     dense, tree = ("fpi_small.hip", "fpi_mixed.hip"), ("fpi_tree.hip",)
     for key, match, src in (("fp64/year100", lambda k: "fpi_f64_kernel<" in k, dense),
                             ("mixed_fp16+warm/year100", mixed("3"), dense),
                             ("mixed_bf16+warm/year100", mixed("2"), dense),
-                            ("tree_fp64/year100", lambda k: "fpi_tree_kernel<" in k, tree),
-                            ("tree_fp32/year100", lambda k: "fpi_tree32_kernel<" in k, tree)):
+                            ("tree_fp64/year100", rows("double"), tree),
+                            ("tree_fp32/year100", rows("float"), tree)):
         kf, kw = pick(fetch, match), pick(write, match)
         if kf is None or kw is None:
             continue
@@ -140,8 +143,9 @@ def summarize_pmc(out_txt: str, command: str, dirs):
     import csv
     import glob
     import statistics
-    keys = ("fpi_f64_kernel", "fpi_mixed_kernel", "predict_fused_kernel", "mismatch_tile_kernel", "fpi_tree_kernel",
-            "fpi_tree32_kernel", "gemm_low_kernel", "gemm_kernel", "finish_mixed_kernel", "finish_kernel")
+    keys = ("fpi_f64_kernel", "fpi_mixed_kernel", "predict_fused_kernel", "mismatch_tile_kernel",
+            "fpi_tree_rows_kernel", "fpi_mid_kernel", "gemm_low_kernel", "gemm_kernel", "gemm64_kernel",
+            "finish_mixed_kernel", "finish_kernel")
     vals = {}
     for d in dirs:
         for path in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
@@ -192,8 +196,8 @@ def summarize_trace(trace_dir: str, out_txt: str, command: str):
                      f"{float(r['TotalDurationNs']) / 1e6:10.2f} {float(r['Percentage']):6.1f}")
     rows = sorted(csv.DictReader(open(trace[0])), key=lambda r: int(r["Start_Timestamp"]))
     lines += ["", "launches of the year-long sweep, inference and mismatch kernels, in order (us):"]
-    for key in ("fpi_f64_kernel", "fpi_mixed_kernel", "fpi_tree_kernel", "fpi_tree32_kernel", "fpi_tree3_kernel",
-                "fpi_tree3_32_kernel", "predict_fused_kernel", "mismatch_tile_kernel"):
+    for key in ("fpi_f64_kernel", "fpi_mixed_kernel", "fpi_mid_kernel", "fpi_tree_rows_kernel", "predict_fused_kernel",
+                "mismatch_tile_kernel"):
         by = {}
         for r in rows:
             if key in r["Kernel_Name"]:
