@@ -1,4 +1,4 @@
-// Reciprocals shared by the sweep kernels.
+// Reciprocals of the sweep kernels and a barrier for LDS alone.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -22,6 +22,11 @@ __device__ __forceinline__ float reciprocal32(float x) {
     const float y = __builtin_amdgcn_rcpf(x);
     return x < 0x1p125f ? __builtin_fmaf(__builtin_fmaf(-x, y, 1.0f), y, y) : y;
 }
+
+// A barrier for data exchanged in LDS alone: it waits for this wave's LDS accesses, not for its
+// global ones, so that the operands requested ahead and the results on their way out stay in
+// flight across it (__syncthreads drains both, an L2 round trip each time).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 }  // namespace
 }  // namespace tpf

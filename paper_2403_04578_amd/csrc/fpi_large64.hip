@@ -3,6 +3,9 @@
 // epilogue updates the state and forms the next sweep's injection, and one kernel that
 // applies the stopping rule and rebuilds the list of active columns.  Every sweep is queued
 // without waiting on the device: the active counts stay there.
+#include <type_traits>
+
+#include "device_math.h"
 #include "large_common.h"
 
 namespace tpf {
@@ -28,19 +31,22 @@ __device__ __forceinline__ d4x mma64(double a, double b, const d4x &c) {
 
 typedef double d2x __attribute__((ext_vector_type(2)));
 
-// I = conj(S./V) (or the ZIP form) from the new voltage of bus b.
+// I = conj(S./V) (or the ZIP form) from the new voltage of bus b.  The fused operations are
+// written out here and in update64: left to the compiler, kernels that inline these may fuse
+// differently, and a column's bits would depend on the kernel its call picks.
 __device__ __forceinline__ d2x injection64(double sr, double si, double vr, double vi, int b, const ZipShares &zs) {
-    const double inv = 1.0 / (vr * vr + vi * vi);
-    const double pr = sr * vr + si * vi, pi = sr * vi - si * vr;
+#pragma clang fp contract(off)
+    const double inv = 1.0 / __builtin_fma(vr, vr, vi * vi);
+    const double pr = __builtin_fma(sr, vr, si * vi), pi = __builtin_fma(sr, vi, -(si * vr));
     double jr = pr * inv, ji = pi * inv;
     if (zs.aP) {
         const double ap = zs.aP[b], ai = zs.aI[b];
-        jr = ap * jr + ai * sr;
-        ji = ap * ji - ai * si;
+        jr = __builtin_fma(ap, jr, ai * sr);
+        ji = __builtin_fma(ap, ji, -(ai * si));
         if (zs.aZ) {
             const double az = zs.aZ[b];
-            jr += az * pr;
-            ji += az * pi;
+            jr = __builtin_fma(az, pr, jr);
+            ji = __builtin_fma(az, pi, ji);
         }
     }
     return d2x{jr, ji};
@@ -92,9 +98,10 @@ template <typename IO>
 __device__ __forceinline__ void update64(double pr, double pi, d2x w, long long c, int bus, int n, int KB,
                                          const IO *__restrict__ S, const ZipShares &zs, d2x old, double sr, double si,
                                          double *__restrict__ x, d2x *__restrict__ Bn, double &dmax, double &poison) {
+#pragma clang fp contract(off)
     const double nr = pr + w.x, ni = pi + w.y;
     const double dr = nr - old.x, di = ni - old.y;
-    const double e = dr * dr + di * di;
+    const double e = __builtin_fma(dr, dr, di * di);
     poison = __builtin_fma(e, 0.0, poison);
     dmax = fmax(dmax, e);
     reinterpret_cast<d2x *>(x)[c * n + bus] = d2x{nr, ni};
@@ -207,102 +214,221 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
     }
 }
 
-// The same sweep for batches too small to fill the chip with 64 x 64 tiles: tiles of 16 TR
-// buses x 16 TC active columns, whose k-steps are shared out among the NW waves of a
-// workgroup; each wave multiplies its share straight from L2 (a register ring of kSplitRing
-// k-steps, no LDS and no barrier in the loop) and the partial sums meet in LDS.  Bound by the
-// latency of the operand loads, which is why the k-steps are split: one column of a 999-bus
-// feeder spends 63 tiles x 8 waves x 31 k-steps per sweep here, where sixteen 64 x 64 tiles
-// would each walk 125 slabs.
-constexpr int kSplitRing = 4;
-
-template <int TR, int TC, int NW, typename IO>
-__global__ __launch_bounds__(NW * 64) void gemm64_split_kernel(
+// The same sweep for batches that leave a CU fewer than six such workgroups: the operands
+// straight from L2 through a register ring (no LDS and no barrier in the loop).  Every element's
+// three sums run over the k-steps in the order of gemm64_kernel, so a column has the same bits
+// whichever kernel its batch picks; splitting the k-steps among wavefronts is faster for a few
+// columns (192 against 313 us for one at 999 buses) but adds the terms in another order.
+// Four wavefronts, 2 x 2, with TW x TW tiles each; TW = 1 is bound by the operands' way through L1
+// (43 bytes per cycle and CU), TW = 2 halves that.
+template <int TW, typename IO>
+__global__ __launch_bounds__(256) void gemm64_direct_kernel(
     const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
-    const long long *__restrict__ act, const int *__restrict__ na, int row_tiles, const d2x *__restrict__ w, int n,
+    const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
     const IO *__restrict__ S, const ZipShares zs, double *__restrict__ x, unsigned long long *__restrict__ dmax) {
+    constexpr int E = 2 * TW;  // tiles per side of a workgroup's block
+    constexpr int kRing = TW == 1 ? 6 : 3;
     const int nact = *na;
-    const int ct = (nact + 16 * TC - 1) / (16 * TC);
-    __shared__ d2x part[NW][TR * TC * 4][64];
-    __shared__ unsigned long long red[16 * TC];
+    const int ct = (nact + 16 * E - 1) / (16 * E);
+    __shared__ unsigned long long red[16 * E];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, j = lane & 15;
-    const int k0 = wave * KT / NW, k1 = (wave + 1) * KT / NW;
-    for (int t = blockIdx.x; t < ct * row_tiles; t += gridDim.x) {
-        const int c0 = t / row_tiles * 16 * TC, rt = t % row_tiles * TR;
-        if (tid < 16 * TC) red[tid] = 0ull;
-        const d2x *Ap[TR], *Bp[TC];
+    for (int t = blockIdx.x; t < ct * row_blocks; t += gridDim.x) {
+        const int cb = t / row_blocks * 16 * E;              // the block's first column,
+        const int c0 = cb + 16 * TW * (wave & 1);            // the wavefront's,
+        const int rt = t % row_blocks * E + TW * (wave >> 1);  // and its first row tile
+        if (tid < 16 * E) red[tid] = 0ull;
+        const d2x *Ap[TW], *Bp[TW];
 #pragma unroll
-        for (int a = 0; a < TR; ++a) Ap[a] = A + (size_t)(rt + a) * KT * 64 + lane;
+        for (int a = 0; a < TW; ++a) Ap[a] = A + (size_t)(rt + a) * KT * 64 + lane;
 #pragma unroll
-        for (int b = 0; b < TC; ++b) {
+        for (int b = 0; b < TW; ++b) {
             const int slot = c0 + 16 * b + j;
             Bp[b] = B + act[slot < nact ? slot : nact - 1] * KB + g;
         }
-        d4x m1[TR][TC], m2[TR][TC], m3[TR][TC];
+        d4x m1[TW][TW], m2[TW][TW], m3[TW][TW];
 #pragma unroll
-        for (int a = 0; a < TR; ++a)
+        for (int a = 0; a < TW; ++a)
 #pragma unroll
-            for (int b = 0; b < TC; ++b) m1[a][b] = m2[a][b] = m3[a][b] = d4x{0, 0, 0, 0};
-        d2x ra[kSplitRing][TR], rb[kSplitRing][TC];
+            for (int b = 0; b < TW; ++b) m1[a][b] = m2[a][b] = m3[a][b] = d4x{0, 0, 0, 0};
+        d2x ra[kRing][TW], rb[kRing][TW];
         auto fetch = [&](int u, int kt) __attribute__((always_inline)) {
-            const int k = kt < k1 ? kt : k1 - 1;  // past the share: a step already read
+            const int k = kt < KT ? kt : KT - 1;  // past the end: a step already read
 #pragma unroll
-            for (int a = 0; a < TR; ++a) ra[u][a] = Ap[a][(size_t)k * 64];
+            for (int a = 0; a < TW; ++a) ra[u][a] = Ap[a][(size_t)k * 64];
 #pragma unroll
-            for (int b = 0; b < TC; ++b) rb[u][b] = Bp[b][4 * k];
+            for (int b = 0; b < TW; ++b) rb[u][b] = Bp[b][4 * k];
         };
-        if (k0 < k1) {
+        auto step = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < kSplitRing; ++u) fetch(u, k0 + u);
-            for (int kt = k0; kt < k1; kt += kSplitRing) {
+            for (int a = 0; a < TW; ++a)
 #pragma unroll
-                for (int u = 0; u < kSplitRing; ++u) {
-                    if (kt + u < k1) {
-                        double as[TR], bs[TC];
-#pragma unroll
-                        for (int a = 0; a < TR; ++a) as[a] = ra[u][a].x - ra[u][a].y;
-#pragma unroll
-                        for (int b = 0; b < TC; ++b) bs[b] = rb[u][b].x - rb[u][b].y;
-#pragma unroll
-                        for (int a = 0; a < TR; ++a)
-#pragma unroll
-                            for (int b = 0; b < TC; ++b) {
-                                m1[a][b] = mma64(ra[u][a].x, rb[u][b].x, m1[a][b]);
-                                m2[a][b] = mma64(ra[u][a].y, rb[u][b].y, m2[a][b]);
-                                m3[a][b] = mma64(as[a], bs[b], m3[a][b]);
-                            }
-                        fetch(u, kt + u + kSplitRing);
-                    }
+                for (int b = 0; b < TW; ++b) {
+                    const d2x z = ra[u][a], i = rb[u][b];
+                    m1[a][b] = mma64(z.x, i.x, m1[a][b]);
+                    m2[a][b] = mma64(z.y, i.y, m2[a][b]);
+                    m3[a][b] = mma64(z.x - z.y, i.x - i.y, m3[a][b]);
                 }
+        };
+#pragma unroll
+        for (int u = 0; u < kRing; ++u) {
+            fetch(u, u);
+            __builtin_amdgcn_sched_barrier(0);  // (in the order they are used)
+        }
+        // whole turns of the ring without a branch, which would wait for every load in flight
+        int kt = 0;
+        for (; kt + kRing <= KT; kt += kRing) {
+#pragma unroll
+            for (int u = 0; u < kRing; ++u) {
+                step(u);
+                fetch(u, kt + u + kRing);
+                __builtin_amdgcn_sched_barrier(0);  // (the loads stay spread over the turn)
             }
         }
 #pragma unroll
-        for (int a = 0; a < TR; ++a)
+        for (int u = 0; u < kRing; ++u)
+            if (kt + u < KT) step(u);
+        __syncthreads();  // red clear
 #pragma unroll
-            for (int b = 0; b < TC; ++b)
+        for (int b = 0; b < TW; ++b) {
+            const int slot = c0 + 16 * b + j;
+            const bool live = slot < nact;
+            const long long c = act[live ? slot : nact - 1];
+            double e = 0.0, poison = 0.0;
+#pragma unroll
+            for (int a = 0; a < TW; ++a) {
+                const int bus0 = 16 * (rt + a) + g;
+                d2x old[4];
+                double sr[4], si[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    part[wave][(a * TC + b) * 4 + r][lane] =
-                        d2x{m1[a][b][r] - m2[a][b][r], m1[a][b][r] + m2[a][b][r] - m3[a][b][r]};
-        __syncthreads();
-        for (int e = wave; e < TR * TC * 4; e += NW) {  // group e: row tile, column tile, register
-            const int a = e / (4 * TC), b = e / 4 % TC, r = e % 4;
-            const int bus = 16 * (rt + a) + 4 * r + g, slot = c0 + 16 * b + j;
-            if (slot < nact && bus < n) {
-                const long long c = act[slot];
-                const d2x old = reinterpret_cast<const d2x *>(x)[c * n + bus];
-                const double sr = (double)S[2 * (c * n + bus)], si = (double)S[2 * (c * n + bus) + 1];
-                double pr = 0.0, pi = 0.0, d = 0.0, poison = 0.0;
+                    if (live && bus0 + 4 * r < n) {
+                        old[r] = reinterpret_cast<const d2x *>(x)[c * n + bus0 + 4 * r];
+                        sr[r] = (double)S[2 * (c * n + bus0 + 4 * r)];
+                        si[r] = (double)S[2 * (c * n + bus0 + 4 * r) + 1];
+                    }
 #pragma unroll
-                for (int v = 0; v < NW; ++v) pr += part[v][e][lane].x, pi += part[v][e][lane].y;
-                update64<IO>(pr, pi, w[bus], c, bus, n, KB, S, zs, old, sr, si, x, Bn, d, poison);
-                atomicMax(red + 16 * b + j, poison == 0.0 ? (unsigned long long)__double_as_longlong(d) : ~0ull);
+                for (int r = 0; r < 4; ++r)
+                    if (live && bus0 + 4 * r < n)
+                        update64<IO>(m1[a][b][r] - m2[a][b][r], m1[a][b][r] + m2[a][b][r] - m3[a][b][r],
+                                     w[bus0 + 4 * r], c, bus0 + 4 * r, n, KB, S, zs, old[r], sr[r], si[r], x, Bn, e,
+                                     poison);
             }
+            if (live)
+                atomicMax(red + slot - cb, poison == 0.0 ? (unsigned long long)__double_as_longlong(e) : ~0ull);
         }
         __syncthreads();
-        if (tid < 16 * TC && c0 + tid < nact) atomicMax(dmax + act[c0 + tid], red[tid]);
+        if (tid < 16 * E && cb + tid < nact) atomicMax(dmax + act[cb + tid], red[tid]);
+        __syncthreads();  // red is reused
+    }
+}
+
+// The same for the fewest columns: a workgroup of three wavefronts per 16 x 16 tile, one of the
+// sums each, so that a sweep takes about one chain of KT products (64 cycles each).  Bound by the
+// latency of the operands, which the three wavefronts stage through LDS for one another in
+// chunks of kChunk k-steps, requested two chunks ahead of their products.
+constexpr int kChunk = 12;
+
+template <typename IO>
+__global__ __launch_bounds__(192) void gemm64_sums_kernel(
+    const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
+    const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
+    const IO *__restrict__ S, const ZipShares zs, double *__restrict__ x, unsigned long long *__restrict__ dmax) {
+    constexpr int kOwn = kChunk / 3;  // k-steps of a chunk that a wavefront stages
+    constexpr int kAhead = 4;         // k-steps between a read from LDS and its product
+    const int nact = *na;
+    const int ct = (nact + 15) / 16;
+    __shared__ d2x stage[2][kChunk][2][64];  // [buffer][k-step][Z, I][lane]
+    __shared__ double part[3][4][64];
+    __shared__ unsigned long long red[16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, j = lane & 15;
+    for (int t = blockIdx.x; t < ct * row_blocks; t += gridDim.x) {
+        const int c0 = t / row_blocks * 16, rt = t % row_blocks;
+        if (tid < 16) red[tid] = 0ull;
+        const bool live = c0 + j < nact;
+        const long long c = act[live ? c0 + j : nact - 1];
+        const d2x *Ap = A + (size_t)rt * KT * 64 + lane;
+        const d2x *Bp = B + c * KB + g;
+        d2x ra[2][kOwn], rb[2][kOwn];
+        auto fetch = [&](int u, int k0) __attribute__((always_inline)) {  // chunk that starts at k-step k0
+#pragma unroll
+            for (int i = 0; i < kOwn; ++i) {
+                const int kt = k0 + kOwn * wave + i, k = kt < KT ? kt : KT - 1;  // past the end: unused
+                ra[u][i] = Ap[(size_t)k * 64];
+                rb[u][i] = Bp[4 * k];
+            }
+        };
+        auto put = [&](int u) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < kOwn; ++i) {
+                stage[u][kOwn * wave + i][0][lane] = ra[u][i];
+                stage[u][kOwn * wave + i][1][lane] = rb[u][i];
+            }
+        };
+        auto sum = [&](auto which) __attribute__((always_inline)) {
+            constexpr int P = decltype(which)::value;
+            d4x m = d4x{0, 0, 0, 0};
+            d2x z[kChunk], i[kChunk];
+            auto read = [&](int u, int k) __attribute__((always_inline)) {
+                z[k] = stage[u][k][0][lane];
+                i[k] = stage[u][k][1][lane];
+            };
+            auto step = [&](int k) __attribute__((always_inline)) {
+                m = mma64(P == 0 ? z[k].x : P == 1 ? z[k].y : z[k].x - z[k].y,
+                          P == 0 ? i[k].x : P == 1 ? i[k].y : i[k].x - i[k].y, m);
+            };
+            fetch(0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(1, kChunk);
+            put(0);
+            lds_barrier();
+            for (int k0 = 0; k0 < KT; k0 += 2 * kChunk) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {  // buffer u: the chunk at k0 + u kChunk
+                    const int k1 = k0 + u * kChunk;
+                    fetch(u, k1 + 2 * kChunk);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (k1 + kChunk <= KT) {
+#pragma unroll
+                        for (int k = 0; k < kAhead; ++k) read(u, k);
+#pragma unroll
+                        for (int k = 0; k < kChunk; ++k) {
+                            if (k + kAhead < kChunk) read(u, k + kAhead);
+                            __builtin_amdgcn_sched_barrier(0);
+                            step(k);
+                        }
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < kChunk; ++k)
+                            if (k1 + k < KT) read(u, k), step(k);
+                    }
+                    put(u ^ 1);  // its last readers passed the previous barrier
+                    lds_barrier();
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[P][r][lane] = m[r];
+        };
+        if (wave == 0) sum(std::integral_constant<int, 0>{});
+        if (wave == 1) sum(std::integral_constant<int, 1>{});
+        if (wave == 2) sum(std::integral_constant<int, 2>{});
+        __syncthreads();  // the sums visible, red clear
+        double e = 0.0, poison = 0.0;
+        for (int r = wave; r < 4; r += 3) {
+            const int bus = 16 * rt + g + 4 * r;
+            if (live && bus < n) {
+                const double p1 = part[0][r][lane], p2 = part[1][r][lane], p3 = part[2][r][lane];
+                update64<IO>(p1 - p2, p1 + p2 - p3, w[bus], c, bus, n, KB, S, zs,
+                             reinterpret_cast<const d2x *>(x)[c * n + bus], (double)S[2 * (c * n + bus)],
+                             (double)S[2 * (c * n + bus) + 1], x, Bn, e, poison);
+            }
+        }
+        if (live) atomicMax(red + j, poison == 0.0 ? (unsigned long long)__double_as_longlong(e) : ~0ull);
+        __syncthreads();
+        if (tid < 16 && c0 + tid < nact) atomicMax(dmax + act[c0 + tid], red[tid]);
         __syncthreads();  // red and part are reused
     }
 }
@@ -424,19 +550,23 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     // stay on the device (three of them in rotation: read, appended, cleared) and the
     // kernels of a sweep with no active column exit at once.  Queueing stops early when
     // the device has already posted that none is left (all_retired).
-    // Shape by the tiles a batch has: 64 x 64 once each CU gets four of them, 32 x 32 with the
-    // k-steps split among four waves down to 5/8 of a tile per CU, else 16 x 16 with eight.
-    // Per solve at 999 buses: 1 column 186 us small, 452 middle, 1,510 large; 256 columns
-    // 800, 590, 1,725; 4,096 columns 6,960, 4,315, 4,276; 20,000 columns 20.5 ms middle,
-    // 18.8 large.  At 349 buses the 4,096 columns take 886, 657 and 854 us.
+    // Shape by the tiles a batch has (the results do not depend on it): staged 64 x 64 tiles once
+    // each CU gets six of them, the direct ones from three quarters of a 64 x 64 tile per CU,
+    // 32 x 32 below, and single tiles by three wavefronts up to two per CU.  Per solve, us, at
+    // 999 buses (sums / direct 32 / direct 64 / staged): 1 column 313 / 461 / 1,226 / 1,525;
+    // 128: 529 / 636 / 1,396 / 1,745; 256: 916 / 649 / 1,411 / 1,764; 1,000: - / 1,750 / 1,430 /
+    // 1,795; 4,096: - / 5,732 / 4,144 / 4,339; 8,192: - / - / 7,899 / 7,769.  At 349 buses: 256:
+    // 161 / 172 / 346 / 484; 2,000: - / 386 / 383 / 491; 8,000: - / 1,183 / 941 / 1,009.
     const int64_t cus = num_cus();
     auto tiles = [&](int edge) { return (int64_t)((n + edge - 1) / edge) * ((tau + edge - 1) / edge); };
-    const int edge = tiles(64) >= 4 * cus ? 64 : 8 * tiles(32) >= 5 * cus ? 32 : 16;
+    const int shape = tiles(64) >= 6 * cus ? 3 : 4 * tiles(64) >= 3 * cus ? 2 : tiles(16) > 2 * cus ? 1 : 0;
+    const int edge = shape >= 2 ? 64 : shape == 1 ? 32 : 16;
     const int row_blocks = (n + edge - 1) / edge;
-    const auto gemm = edge == 64   ? gemm64_kernel<IO>
-                      : edge == 32 ? gemm64_split_kernel<2, 2, 4, IO>
-                                   : gemm64_split_kernel<1, 1, 8, IO>;
-    const int threads = edge == 16 ? 512 : 256;
+    const auto gemm = shape == 3   ? gemm64_kernel<IO>
+                      : shape == 2 ? gemm64_direct_kernel<2, IO>
+                      : shape == 1 ? gemm64_direct_kernel<1, IO>
+                                   : gemm64_sums_kernel<IO>;
+    const int threads = shape == 0 ? 192 : 256;
     const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(edge));
     const int cpb = apart ? finish_chunk(n) : 256;
     const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + cpb - 1) / cpb);

@@ -10,6 +10,8 @@
 // Sums run in the same order as in the per-layer kernels of mlp.hip.
 #pragma once
 
+#include "device_math.h"
+
 namespace tpf {
 namespace {
 
@@ -66,11 +68,6 @@ __device__ __forceinline__ void prepare_rows(const BatchRows &br, int block) {
 }
 
 __global__ __launch_bounds__(128) void batch_rows_kernel(const BatchRows br) { prepare_rows(br, blockIdx.x); }
-
-// A barrier for data exchanged in LDS alone: it waits for this wave's LDS accesses, not for its
-// global ones, so that the weights requested ahead and the results on their way out stay in
-// flight across it (__syncthreads drains both, an L2 round trip per layer).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // One workgroup: rows r0 .. r0 + 7, 8 waves, wave w owning neurons 32 w .. 32 w + 31 of every
 // layer as two product tiles (weights as the B operand, straight from L2: a layer's
