@@ -20,11 +20,13 @@ __device__ __forceinline__ d4x mma64(double a, double b, const d4x &c) {
 
 // ---- FP64 sweeps
 //
-// The complex product V' = Z I + w as three real ones,
-//     m1 = Zr Ir, m2 = Zi Ii, m3 = (Zr - Zi)(Ir - Ii);  Re = m1 - m2, Im = m1 + m2 - m3
-// (as in the register-resident kernel: a quarter fewer FP64 matrix products), and the next
-// sweep's injection formed by the lane that holds the new voltage, so that between two
-// products only the lists of active columns are rebuilt.  The operand B[column][KB] is kept
+// The complex product V' = Z I + w in separate sums m1 = Zr Ir, m2 = Zi Ii and m3, with THREE as
+// three real products,
+//     m3 = (Zr - Zi)(Ir - Ii);  Re = m1 - m2, Im = m1 + m2 - m3,
+// else m3 = Zr Ii + Zi Ir = Im (as in the register-resident kernel: a quarter fewer FP64 matrix
+// products, for the networks of three_products), and the next sweep's injection formed by the
+// lane that holds the new voltage, so that between two products only the lists of active
+// columns are rebuilt.  The operand B[column][KB] is kept
 // per column, not per place in the list, in two copies used in turn: a sweep writes one
 // while other tiles still read the other.  The state x is V itself, and for complex128 it
 // is the caller's output array where that can be: a column that retires is in place already.
@@ -92,6 +94,19 @@ __global__ void start64_kernel(const IO *__restrict__ S, const IO *__restrict__ 
     }
 }
 
+// The products of entry (z, i) added to m3; zd = z.x - z.y, id = i.x - i.y.
+template <bool THREE>
+__device__ __forceinline__ d4x third(const d2x &z, const d2x &i, double zd, double id, const d4x &m3) {
+    if constexpr (THREE) return mma64(zd, id, m3);
+    return mma64(z.y, i.x, mma64(z.x, i.y, m3));
+}
+
+// Im(Z I) from the three sums.
+template <bool THREE>
+__device__ __forceinline__ double imaginary(double m1, double m2, double m3) {
+    return THREE ? m1 + m2 - m3 : m3;
+}
+
 // One bus of one active column: V' = p + w, the step |V' - V|^2 into `dmax` (and NaN into
 // `poison` when it is not finite), V' into x and the next injection into Bn (unless NULL).
 template <typename IO>
@@ -113,7 +128,7 @@ __device__ __forceinline__ void update64(double pr, double pi, d2x w, long long 
 // (Re, Im); k-slabs of two k-steps of both operands go through LDS in fragment order, two
 // buffers.  Bound by the FP64 matrix cores: 24 products (1,536 cycles) per wave and slab
 // against 8 KB of LDS reads; the epilogue's traffic (x, S in, x, B out) hides behind them.
-template <typename IO>
+template <bool THREE, typename IO>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gemm64_kernel(
     const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
     const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
@@ -168,7 +183,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
                     for (int b = 0; b < 2; ++b) {
                         m1[a][b] = mma64(af[a].x, bf[b].x, m1[a][b]);
                         m2[a][b] = mma64(af[a].y, bf[b].y, m2[a][b]);
-                        m3[a][b] = mma64(as[a], bs[b], m3[a][b]);
+                        m3[a][b] = third<THREE>(af[a], bf[b], as[a], bs[b], m3[a][b]);
                     }
             }
             if (more) {  // the other buffer: its last readers passed the previous barrier
@@ -200,9 +215,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (live && bus0 + 4 * r < n)
-                        update64<IO>(m1[a][b][r] - m2[a][b][r], m1[a][b][r] + m2[a][b][r] - m3[a][b][r],
-                                     w[bus0 + 4 * r], c, bus0 + 4 * r, n, KB, S, zs, old[r], sr[r], si[r], x, Bn, e,
-                                     poison);
+                        update64<IO>(m1[a][b][r] - m2[a][b][r],
+                                     imaginary<THREE>(m1[a][b][r], m2[a][b][r], m3[a][b][r]), w[bus0 + 4 * r], c,
+                                     bus0 + 4 * r, n, KB, S, zs, old[r], sr[r], si[r], x, Bn, e, poison);
             }
             // non-negative doubles order like their bit patterns; ~0 marks a step that is not finite
             if (live)
@@ -221,7 +236,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
 // columns (192 against 313 us for one at 999 buses) but adds the terms in another order.
 // Four wavefronts, 2 x 2, with TW x TW tiles each; TW = 1 is bound by the operands' way through L1
 // (43 bytes per cycle and CU), TW = 2 halves that.
-template <int TW, typename IO>
+template <bool THREE, int TW, typename IO>
 __global__ __launch_bounds__(256) void gemm64_direct_kernel(
     const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
     const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
@@ -268,7 +283,7 @@ __global__ __launch_bounds__(256) void gemm64_direct_kernel(
                     const d2x z = ra[u][a], i = rb[u][b];
                     m1[a][b] = mma64(z.x, i.x, m1[a][b]);
                     m2[a][b] = mma64(z.y, i.y, m2[a][b]);
-                    m3[a][b] = mma64(z.x - z.y, i.x - i.y, m3[a][b]);
+                    m3[a][b] = third<THREE>(z, i, z.x - z.y, i.x - i.y, m3[a][b]);
                 }
         };
 #pragma unroll
@@ -311,9 +326,9 @@ __global__ __launch_bounds__(256) void gemm64_direct_kernel(
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
                     if (live && bus0 + 4 * r < n)
-                        update64<IO>(m1[a][b][r] - m2[a][b][r], m1[a][b][r] + m2[a][b][r] - m3[a][b][r],
-                                     w[bus0 + 4 * r], c, bus0 + 4 * r, n, KB, S, zs, old[r], sr[r], si[r], x, Bn, e,
-                                     poison);
+                        update64<IO>(m1[a][b][r] - m2[a][b][r],
+                                     imaginary<THREE>(m1[a][b][r], m2[a][b][r], m3[a][b][r]), w[bus0 + 4 * r], c,
+                                     bus0 + 4 * r, n, KB, S, zs, old[r], sr[r], si[r], x, Bn, e, poison);
             }
             if (live)
                 atomicMax(red + slot - cb, poison == 0.0 ? (unsigned long long)__double_as_longlong(e) : ~0ull);
@@ -330,7 +345,7 @@ __global__ __launch_bounds__(256) void gemm64_direct_kernel(
 // chunks of kChunk k-steps, requested two chunks ahead of their products.
 constexpr int kChunk = 12;
 
-template <typename IO>
+template <bool THREE, typename IO>
 __global__ __launch_bounds__(192) void gemm64_sums_kernel(
     const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
     const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
@@ -377,8 +392,9 @@ __global__ __launch_bounds__(192) void gemm64_sums_kernel(
                 i[k] = stage[u][k][1][lane];
             };
             auto step = [&](int k) __attribute__((always_inline)) {
-                m = mma64(P == 0 ? z[k].x : P == 1 ? z[k].y : z[k].x - z[k].y,
-                          P == 0 ? i[k].x : P == 1 ? i[k].y : i[k].x - i[k].y, m);
+                m = P == 0   ? mma64(z[k].x, i[k].x, m)
+                    : P == 1 ? mma64(z[k].y, i[k].y, m)
+                             : third<THREE>(z[k], i[k], z[k].x - z[k].y, i[k].x - i[k].y, m);
             };
             fetch(0, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -421,7 +437,7 @@ __global__ __launch_bounds__(192) void gemm64_sums_kernel(
             const int bus = 16 * rt + g + 4 * r;
             if (live && bus < n) {
                 const double p1 = part[0][r][lane], p2 = part[1][r][lane], p3 = part[2][r][lane];
-                update64<IO>(p1 - p2, p1 + p2 - p3, w[bus], c, bus, n, KB, S, zs,
+                update64<IO>(p1 - p2, imaginary<THREE>(p1, p2, p3), w[bus], c, bus, n, KB, S, zs,
                              reinterpret_cast<const d2x *>(x)[c * n + bus], (double)S[2 * (c * n + bus)],
                              (double)S[2 * (c * n + bus) + 1], x, Bn, e, poison);
             }
@@ -515,7 +531,7 @@ struct Large64 {
 
 size_t large64_workspace(int n, int64_t tau) { return Large64(n, tau).total(); }
 
-template <typename IO>
+template <bool THREE, typename IO>
 static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                        int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, void *ws,
                        hipStream_t st) {
@@ -562,10 +578,10 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     const int shape = tiles(64) >= 6 * cus ? 3 : 4 * tiles(64) >= 3 * cus ? 2 : tiles(16) > 2 * cus ? 1 : 0;
     const int edge = shape >= 2 ? 64 : shape == 1 ? 32 : 16;
     const int row_blocks = (n + edge - 1) / edge;
-    const auto gemm = shape == 3   ? gemm64_kernel<IO>
-                      : shape == 2 ? gemm64_direct_kernel<2, IO>
-                      : shape == 1 ? gemm64_direct_kernel<1, IO>
-                                   : gemm64_sums_kernel<IO>;
+    const auto gemm = shape == 3   ? gemm64_kernel<THREE, IO>
+                      : shape == 2 ? gemm64_direct_kernel<THREE, 2, IO>
+                      : shape == 1 ? gemm64_direct_kernel<THREE, 1, IO>
+                                   : gemm64_sums_kernel<THREE, IO>;
     const int threads = shape == 0 ? 192 : 256;
     const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(edge));
     const int cpb = apart ? finish_chunk(n) : 256;
@@ -590,8 +606,14 @@ int launch_fpi_large64(const tpf_network_s &net, const DeviceNet &dn, const void
                        int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, void *ws,
                        hipStream_t st) {
     if (!dn.AL64) return fail(TPF_ERR_UNSUPPORTED, "large-network operator not staged");
-    return dtype == TPF_C128 ? run_large64<double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st)
-                             : run_large64<float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st);
+#define TPF_GO(M, IO) return run_large64<M, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, ws, st)
+    if (dtype == TPF_C128) {
+        if (dn.three) TPF_GO(true, double);
+        TPF_GO(false, double);
+    }
+    if (dn.three) TPF_GO(true, float);
+    TPF_GO(false, float);
+#undef TPF_GO
 }
 
 }  // namespace tpf

@@ -94,22 +94,26 @@ __device__ __forceinline__ void put_injection(const Inj<SUM> &I, int t, int lane
 
 typedef int i4 __attribute__((ext_vector_type(4)));
 
-// The complex product Z I, as three real products instead of four:
-//     m1 = Zr Ir, m2 = Zi Ii, m3 = (Zr - Zi)(Ir - Ii);  Re = m1 - m2, Im = m1 + m2 - m3.
+// The complex product Z I in separate sums m1 = Zr Ir, m2 = Zi Ii and m3.  THREE: three real
+// products instead of four,
+//     m3 = (Zr - Zi)(Ir - Ii);  Re = m1 - m2, Im = m1 + m2 - m3;
+// else m3 = Zr Ii + Zi Ir = Im.
 // The sweep is bound by the FP64 units (64 cycles per 16x16x4 product, and the vector
 // instructions beside it do not overlap with the matrix ones: their busy shares add up to
 // the same 85 % in every form of this kernel), so a quarter fewer products is a quarter
-// less time there.  Every term stays in FP64; taking the differences makes m3 the smallest
-// of the three on lines with r ~ x, and the result is no less exact than the four-product
-// form's (rms error of V against 80-bit arithmetic at 999 buses: 1.04e-16 against 1.38e-16;
-// 8.8e-17 both at 99).  Fragments of Z (Re and Im of a lane's entry as
+// less time there.  Every term stays in FP64, but with three products Im is the difference of
+// sums of the size of Re's: the voltage angles of a resistive feeder would lose digits (rms error
+// of Im V against 80-bit arithmetic 3 to 40 times the four products' at x = 0.3 r).  Networks
+// whose reactances allow it take three (three_products in network.cpp: rms error of V there 0.7
+// to 1.0 times the four products', of its imaginary part 0.8 to 0.9 times for loads at power
+// factors from 0.9), the others four.  Fragments of Z (Re and Im of a lane's entry as
 // one 16-byte load) stream from L2 through a 4-deep register ring, issued three k-steps
 // ahead of their products.
 //
 // NV tiles into slots Q0 .. Q0 + NV - 1 over the k-steps [k0, k1); the first one's fragments
 // [KT + pad][64] start at fragment group `a0` (of 64) of the buffer, the others `stride`
 // groups further each.
-template <int TPW, int Q0, int NV, bool SUM>
+template <bool THREE, int TPW, int Q0, int NV, bool SUM>
 __device__ __forceinline__ void sweep_product(d4 (&m1)[TPW], d4 (&m2)[TPW], d4 (&m3)[TPW],
                                               __amdgpu_buffer_rsrc_t A, int a0, int stride, const Inj<SUM> &I, int k0,
                                               int k1, int lane) {
@@ -139,7 +143,12 @@ __device__ __forceinline__ void sweep_product(d4 (&m1)[TPW], d4 (&m2)[TPW], d4 (
             const double as = r[q].x - r[q].y;
             m1[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[q].x, b.x, m1[Q0 + q], 0, 0, 0);
             m2[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[q].y, b.y, m2[Q0 + q], 0, 0, 0);
-            m3[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(as, bs, m3[Q0 + q], 0, 0, 0);
+            if constexpr (THREE) {
+                m3[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(as, bs, m3[Q0 + q], 0, 0, 0);
+            } else {
+                m3[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[q].x, b.y, m3[Q0 + q], 0, 0, 0);
+                m3[Q0 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(r[q].y, b.x, m3[Q0 + q], 0, 0, 0);
+            }
         }
     };
     fetch(r0, k0);
@@ -174,14 +183,14 @@ __device__ __forceinline__ void sweep_product(d4 (&m1)[TPW], d4 (&m2)[TPW], d4 (
 // `thr` is the bit pattern of the smallest double whose square root is not below the
 // tolerance: non-negative doubles order like their bit patterns, so the stopping rule and
 // the column maxima (|dV|^2 by LDS atomics) are integer work.
-template <int TPW, int NW, bool SHARE, bool ZIP, typename IO>
+template <int TPW, int NW, bool SHARE, bool ZIP, bool THREE, typename IO>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(TPW == 1 ? 4 : 2))) void fpi_f64_kernel(
     const IO *__restrict__ S, IO *__restrict__ Vout, int32_t *__restrict__ iters_out,
     int8_t *__restrict__ status_out, const IO *__restrict__ V0, const double *__restrict__ A,
     const double *__restrict__ wv, int n, int MT, long long tau, unsigned long long thr, int max_iter, int bufs,
     unsigned long long *__restrict__ queue, const double *__restrict__ aP, const double *__restrict__ aI,
     const double *__restrict__ aZ) {
-    constexpr bool SUM = TPW == 1;
+    constexpr bool SUM = THREE && TPW == 1;
     extern __shared__ __align__(16) double lds[];
     const int KT = (n + 3) / 4, rows = 4 * KT;
     d2 *Ibuf = reinterpret_cast<d2 *>(lds);                      // [bufs][rows][16]
@@ -299,12 +308,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(TPW == 
         for (int q = 0; q < TPW; ++q) m1[q] = m2[q] = m3[q] = d4{0.0, 0.0, 0.0, 0.0};
         if constexpr (!SHARE) {
             if (nf == TPW)
-                sweep_product<TPW, 0, TPW>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
+                sweep_product<THREE, TPW, 0, TPW>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
             else if constexpr (TPW > 1)
-                sweep_product<TPW, 0, TPW - 1>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
+                sweep_product<THREE, TPW, 0, TPW - 1>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
         } else {
             if constexpr (TPW > 1)
-                sweep_product<TPW, 0, TPW - 1>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
+                sweep_product<THREE, TPW, 0, TPW - 1>(m1, m2, m3, Az, tw * tstride, NW * tstride, I, 0, KT, lane);
             // the last slot: a whole tile, an owner's part of a shared one, or a helper's parts.
             // extra = 3: role 7 does the rest of each of the three tiles; 2: roles 6 and 7 of one
             // each; 1: roles 5, 6 and 7 a third of it each
@@ -315,12 +324,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(TPW == 
                 const int k0 = !helper ? 0 : extra == 1 ? min(KT, ks + e * third) : ks;
                 const int k1 = owner ? ks : helper && extra == 1 ? min(KT, k0 + third) : KT;
                 m1[TPW - 1] = m2[TPW - 1] = m3[TPW - 1] = d4{0.0, 0.0, 0.0, 0.0};
-                sweep_product<TPW, TPW - 1, 1>(m1, m2, m3, Az, t * tstride, 0, I, k0, k1, lane);
+                sweep_product<THREE, TPW, TPW - 1, 1>(m1, m2, m3, Az, t * tstride, 0, I, k0, k1, lane);
                 if (helper) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        hand[256 * e + 64 * r + lane] = d2{m1[TPW - 1][r] - m2[TPW - 1][r],
-                                                           m1[TPW - 1][r] + m2[TPW - 1][r] - m3[TPW - 1][r]};
+                        hand[256 * e + 64 * r + lane] =
+                            d2{m1[TPW - 1][r] - m2[TPW - 1][r],
+                               THREE ? m1[TPW - 1][r] + m2[TPW - 1][r] - m3[TPW - 1][r] : m3[TPW - 1][r]};
                 }
             }
         }
@@ -339,7 +349,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(TPW == 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const d2 w = wl[16 * t + g + 4 * r];
-                    double pr = m1[q][r] - m2[q][r], pi = m1[q][r] + m2[q][r] - m3[q][r];
+                    double pr = m1[q][r] - m2[q][r], pi = THREE ? m1[q][r] + m2[q][r] - m3[q][r] : m3[q][r];
                     if (SHARE && q == TPW - 1 && owner) {
                         const int e1 = extra == 1 ? 3 : tw - 3;
                         for (int e = extra == 1 ? 0 : tw - 4; e < e1; ++e) {
@@ -451,14 +461,14 @@ unsigned long long square_bound(double tol) {
     return bits;
 }
 
-template <int TPW, int NW, bool SHARE, bool ZIP, typename IO>
+template <int TPW, int NW, bool SHARE, bool ZIP, bool THREE, typename IO>
 static int launch_rows_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                           int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
                           unsigned long long *queue, hipStream_t stream) {
     const int n = net.n, MT = dn.MT64;
-    const size_t ib = (size_t)(n + 3) / 4 * 4 * (TPW == 1 ? 384 : 256);  // one copy of the injections
+    const size_t ib = (size_t)(n + 3) / 4 * 4 * (THREE && TPW == 1 ? 384 : 256);  // one copy of the injections
     size_t rest = (size_t)16 * MT * 16 + 48 * 8 + 16 + 64 + (SHARE ? 768 * 16 : 0) + (size_t)(ZIP ? 48 : 0) * MT * 8;
-    auto kern = fpi_f64_kernel<TPW, NW, SHARE, ZIP, IO>;
+    auto kern = fpi_f64_kernel<TPW, NW, SHARE, ZIP, THREE, IO>;
     rest = std::max(rest, (size_t)1024);  // the product reads one row group past the last
     // Two copies of the injections where they do not cost a resident workgroup (half of the
     // barriers against fewer workgroups to fill the waits of the others).
@@ -492,11 +502,15 @@ template <int TPW, int NW, bool SHARE, typename IO>
 static int launch_rows(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                        int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
                        unsigned long long *queue, hipStream_t stream) {
-    if (dn.aP)
-        return launch_rows_as<TPW, NW, SHARE, true, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue,
-                                                        stream);
-    return launch_rows_as<TPW, NW, SHARE, false, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue,
-                                                     stream);
+#define TPF_GO(Z, M) \
+    return launch_rows_as<TPW, NW, SHARE, Z, M, IO>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, queue, stream)
+    if (dn.aP) {
+        if (dn.three) TPF_GO(true, true);
+        TPF_GO(true, false);
+    }
+    if (dn.three) TPF_GO(false, true);
+    TPF_GO(false, false);
+#undef TPF_GO
 }
 
 // Leftover tiles are shared out among the waves wherever there are some, as long as a wave

@@ -50,6 +50,7 @@ struct DeviceNet {
     int MT = 0;                  // 16-row tiles of the real-block operator (FP32-family kernels)
     int NW = 0, TPW = 0;         // their workgroup shape (rows_config)
     int MT64 = 0;                // 16-bus tiles of the FP64 kernel
+    bool three = false;          // FP64 complex products as three real ones (three_products)
     double *A64 = nullptr;       // FP64 MFMA A fragments of Z, [tiles][ceil(n/4)+pad k-steps][64 lanes][Re, Im]
     double *w64 = nullptr;       // [2][16 MT64]: Re w then Im w per bus (padding buses: 1, 0)
     // FP32-family kernels (FP32 and mixed modes), n <= 128.  Rows/cols use the order
