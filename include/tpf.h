@@ -105,7 +105,8 @@ typedef struct {
     int32_t reserved0;
     const void *V0;        /* device [tau][n] start voltages (same dtype as S), or NULL for the
                               flat start 1 + j0 of Algorithm 1.  A column whose V0 holds a
-                              non-finite value or a modulus outside [0.5, 1.5] pu starts flat. */
+                              non-finite value or a modulus outside [0.5, 1.5] pu starts flat.
+                              V_out may be V0 itself, or overlap it where S lies apart. */
     double *mismatch_out;  /* device [tau] float64, or NULL: per-column max |S + V.*conj(Y_ds v_s +
                               Y_dd V)| of the returned V, computed in FP64 (Eq. (1) balance). */
     tpf_mlp warm_start;    /* learned warm start (tpf_mlp_create / tpf_mlp_load on this device) or

@@ -86,6 +86,16 @@ int solve_impl(tpf_network net, const void *S, int32_t dtype, int64_t T, double 
         if (rc != TPF_OK) return rc;
         V0 = v0buf;
     }
+    // The persistent kernels read a column's start when its turn comes and write V_out column by
+    // column: a start that V_out partly covers is moved into V_out first (a start in V_out itself
+    // is read before its column is written).  The per-sweep paths read every start first.
+    const size_t bytes = (size_t)T * n * (dtype == TPF_C128 ? 16 : 8);
+    const bool per_sweep = max_iter > 0 && !is_tree(mode) && n > (mode == TPF_MODE_FP64 ? 8 * kMaxSmallTiles : kMaxMidBuses);
+    if (V0 && V0 != V_out && !per_sweep && overlap(V0, V_out, bytes) && !overlap(S, V_out, bytes)) {
+        rc = launch_move(V0, V_out, dtype, T * n, st);
+        if (rc != TPF_OK) return rc;
+        V0 = V_out;
+    }
     if (max_iter == 0) {
         rc = launch_start_only(n, V0, dtype, T, V_out, iters_out, status_out, st);
     } else if (is_tree(mode)) {

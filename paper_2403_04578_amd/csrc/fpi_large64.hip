@@ -55,10 +55,11 @@ __device__ __forceinline__ d2x injection64(double sr, double si, double vr, doub
 }
 
 // Start voltages (guarded V0 or flat) into x and the first injections into B0; zeroes the
-// K padding of the copies of B (B1 may be NULL), the column maxima and the sweep counts.  One wave per column.
+// K padding of the copies of B (B1 may be NULL), the column maxima and the sweep counts.  One wave
+// per column.  x may be V0.
 template <typename IO>
-__global__ void start64_kernel(const IO *__restrict__ S, const IO *__restrict__ V0, int n, int KB, long long tau,
-                               const ZipShares zs, double *__restrict__ x, d2x *__restrict__ B0,
+__global__ void start64_kernel(const IO *__restrict__ S, const IO *V0, int n, int KB, long long tau,
+                               const ZipShares zs, double *x, d2x *__restrict__ B0,
                                d2x *__restrict__ B1, int32_t *__restrict__ iters, long long *__restrict__ act,
                                int *__restrict__ cnt, unsigned long long *__restrict__ dmax) {
     const long long c = blockIdx.x * 4LL + (threadIdx.x >> 6);
@@ -548,10 +549,10 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     act[1] = reinterpret_cast<long long *>(p), p += L.bA;
     int *cnt = reinterpret_cast<int *>(p);  // three active counts in rotation
     // the state lives in a complex128 result, unless the caller solves in place (S is read
-    // by every sweep)
-    const char *s0 = static_cast<const char *>(S), *v0 = static_cast<const char *>(V);
+    // by every sweep) or the result begins inside the start voltages (a column's first state would
+    // overwrite another's start; the very same array is fine)
     const size_t bytes = (size_t)tau * n * 2 * sizeof(IO);
-    const bool apart = sizeof(IO) == 4 || (s0 < v0 + bytes && v0 < s0 + bytes);
+    const bool apart = sizeof(IO) == 4 || overlap(S, V, bytes) || (V0 != V && overlap(V0, V, bytes));
     double *x = static_cast<double *>(V);
     if (apart) {
         x = reinterpret_cast<double *>(B[1]);

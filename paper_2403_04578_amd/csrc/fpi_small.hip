@@ -439,6 +439,31 @@ __global__ void zero_u64_kernel(unsigned long long *p, int count) {
     if (i < count) p[i] = 0ull;
 }
 
+// One workgroup copies chunk after chunk from the end that the destination does not reach first: a
+// chunk is read whole before any of it is written.
+constexpr int kMoveThreads = 1024, kMoveEach = 4;
+
+template <typename T>
+__global__ __launch_bounds__(kMoveThreads) void move_kernel(const T *src, T *dst, long long count, bool up) {
+    constexpr long long kChunk = (long long)kMoveThreads * kMoveEach;
+    for (long long done = 0; done < count; done += kChunk) {
+        const long long base = (up ? done : count - done - kChunk) + threadIdx.x;  // (below 0: not there)
+        T v[kMoveEach];
+#pragma unroll
+        for (int u = 0; u < kMoveEach; ++u) {
+            const long long e = base + u * kMoveThreads;
+            if (e >= 0 && e < count) v[u] = src[e];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kMoveEach; ++u) {
+            const long long e = base + u * kMoveThreads;
+            if (e >= 0 && e < count) dst[e] = v[u];
+        }
+        __syncthreads();
+    }
+}
+
 int num_cus() {
     static int cached[64] = {0};
     int dev = 0;
@@ -558,6 +583,18 @@ int launch_start_only(int n, const void *V0, int dtype, int64_t tau, void *V, in
 
 int launch_zero_u64(unsigned long long *p, int count, hipStream_t stream) {
     hipLaunchKernelGGL(zero_u64_kernel, dim3((count + 63) / 64), dim3(64), 0, stream, p, count);
+    return TPF_OK;
+}
+
+int launch_move(const void *src, void *dst, int dtype, int64_t count, hipStream_t stream) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const bool up = static_cast<const char *>(dst) < static_cast<const char *>(src);
+    if (dtype == TPF_C128)
+        hipLaunchKernelGGL(move_kernel<d2>, dim3(1), dim3(kMoveThreads), 0, stream, (const d2 *)src, (d2 *)dst,
+                           (long long)count, up);
+    else
+        hipLaunchKernelGGL(move_kernel<f2>, dim3(1), dim3(kMoveThreads), 0, stream, (const f2 *)src, (f2 *)dst,
+                           (long long)count, up);
     return TPF_OK;
 }
 

@@ -195,5 +195,12 @@ int launch_mismatch_f64(const tpf_network_s &net, const DeviceNet &dn, const voi
 // Compute units of the current device (looked up once per device).
 int num_cus();
 int launch_zero_u64(unsigned long long *p, int count, hipStream_t stream);
+// Whether two arrays of `bytes` bytes share any.
+inline bool overlap(const void *a, const void *b, size_t bytes) {
+    const char *p = static_cast<const char *>(a), *q = static_cast<const char *>(b);
+    return p && q && p < q + bytes && q < p + bytes;
+}
+// dst[0 .. count) = src[0 .. count) (complex values) for overlapping arrays.
+int launch_move(const void *src, void *dst, int dtype, int64_t count, hipStream_t stream);
 
 }  // namespace tpf
