@@ -1,4 +1,5 @@
 // C ABI entry points: argument checks, workspace carving and kernel dispatch.
+#include <algorithm>
 #include <cmath>
 
 #include "tpf_internal.h"
@@ -27,7 +28,10 @@ bool is_tree(int mode) { return mode == TPF_MODE_TREE_FP64 || mode == TPF_MODE_T
 
 // Workspace of the sweeps alone: the atomic column queue, or the per-sweep path's state.
 size_t base_workspace(const tpf_network_s &net, int64_t tau, int mode) {
-    if (!is_tree(mode) && uses_large_path(net.n, mode)) return large_workspace_bytes(net.n, tau, mode);
+    if (!is_tree(mode) && uses_large_path(net.n, mode)) {
+        const size_t large = large_workspace_bytes(net.n, tau, mode);
+        return mode != TPF_MODE_FP64 && net.n <= kMaxMidBuses ? std::max(large, mid_workspace_bytes(net.n, tau)) : large;
+    }
     return kQueueBytes;
 }
 
@@ -101,8 +105,7 @@ int solve_impl(tpf_network net, const void *S, int32_t dtype, int64_t T, double 
     } else if (is_tree(mode)) {
         rc = launch_fpi_tree(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out, st);
     } else if (mode != TPF_MODE_FP64 && n > 128 && n <= kMaxMidBuses) {
-        rc = launch_fpi_mid(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out,
-                            reinterpret_cast<unsigned long long *>(workspace), st);
+        rc = launch_fpi_mid(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out, workspace, st);
     } else if (uses_large_path(n, mode)) {
         rc = launch_fpi_large(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out,
                               workspace, st);

@@ -171,7 +171,7 @@ int launch_fpi_mixed(const tpf_network_s &net, const DeviceNet &dn, int mode, co
                      int8_t *status, unsigned long long *queue, hipStream_t stream);
 int launch_fpi_mid(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype, int64_t tau,
                    double tol, int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status,
-                   unsigned long long *queue, hipStream_t stream);
+                   void *workspace, hipStream_t stream);
 int launch_fpi_large(const tpf_network_s &net, const DeviceNet &dn, int mode, const void *S, int dtype,
                      int64_t tau, double tol, int max_iter, const void *V0, void *V, int32_t *iters,
                      int8_t *status, void *workspace, hipStream_t stream);
@@ -180,6 +180,7 @@ int launch_fpi_large64(const tpf_network_s &net, const DeviceNet &dn, const void
                        hipStream_t stream);
 size_t large_workspace_bytes(int n, int64_t tau, int mode);
 size_t large64_workspace(int n, int64_t tau);
+size_t mid_workspace_bytes(int n, int64_t tau);
 // k-steps of four buses in the large FP64 operand (even: two per LDS slab).
 inline int large64_ksteps(int n) { return (n + 7) / 8 * 2; }
 // Bit pattern of the smallest double x >= 0 with sqrt(x) >= tol, so that x < it exactly when
