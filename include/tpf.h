@@ -67,8 +67,7 @@ enum { TPF_C64 = 0, TPF_C128 = 1 };
  * Network size: these four modes run any n.  Beyond 320 PQ buses they use a per-sweep
  * kernel sequence (dense Z no longer fits one workgroup's registers), queued up to
  * max_iter sweeps without waiting for the device (a sweep with no active column left
- * exits at once); smaller networks run one persistent kernel per solve.  The workspace
- * of the FP32 and mixed modes is that of the per-sweep sequence from 129 PQ buses on. */
+ * exits at once); smaller networks run one persistent kernel per solve. */
 /* TREE_FP64   the FP64 iteration with Z I evaluated by two passes over the feeder's
  *             tree instead of the dense product: on a radial network without shunts,
  *             -Z is the path-impedance matrix, so Z I = -D with branch currents
@@ -188,9 +187,10 @@ int tpf_network_get_zw(tpf_network net, double *Z_out, double *w_out);
 
 /* Bytes of device workspace that tpf_solve_* needs for tau columns with these
  * options (opts may be NULL).  The solve calls allocate nothing themselves.  Small
- * networks need 256 B; the per-sweep path for large networks holds its state, operand
- * and active lists there (about tau * 2n * 16 B in FP64); a warm start adds its V0
- * (tau * n * 16 B) and inference scratch. */
+ * networks need 256 B; the FP32 and mixed modes at 129 to 320 PQ buses room for columns set
+ * aside while others go on (at most 64 MB, whatever tau); the per-sweep path for large
+ * networks holds its state, operand and active lists there (about tau * 2n * 16 B in FP64); a
+ * warm start adds its V0 (tau * n * 16 B) and inference scratch. */
 size_t tpf_workspace_bytes(tpf_network net, int64_t tau, const tpf_options *opts);
 
 /* Algorithm 1 over a [T][n] load matrix (Sec. IV-A: each time step is a column).
@@ -224,9 +224,10 @@ int tpf_solve_tensor(tpf_network net, const void *S, int32_t dtype, int64_t n_sc
  * nothing: the network must already be resident on the current device (the first
  * tpf_solve_timeseries, tpf_solve_tensor or tpf_mismatch call with it there uploads it), else
  * TPF_ERR_UNSUPPORTED.  A request whose tpf_workspace_bytes exceeds 4096 -- the per-sweep path
- * of large networks, a learned warm start -- returns TPF_ERR_UNSUPPORTED.  Every call on a
- * GPU uses that GPU's one array (cleared by each call where it must start at zero), so calls
- * that overlap on one GPU (other streams or threads) race: the caller serialises them. */
+ * of large networks, the FP32 and mixed modes from 129 PQ buses on, a learned warm start --
+ * returns TPF_ERR_UNSUPPORTED.  Every call on a GPU uses that GPU's one array (cleared by each
+ * call where it must start at zero), so calls that overlap on one GPU (other streams or threads)
+ * race: the caller serialises them. */
 int tpf_solve_timeseries_noalloc(tpf_network net, const void *S, int32_t dtype, int64_t T, double tol,
                                  int32_t max_iter, const tpf_options *opts, void *V_out, int32_t *iters_out,
                                  int8_t *status_out, void *stream);

@@ -1,5 +1,4 @@
 // C ABI entry points: argument checks, workspace carving and kernel dispatch.
-#include <algorithm>
 #include <cmath>
 
 #include "tpf_internal.h"
@@ -26,12 +25,12 @@ size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 bool is_tree(int mode) { return mode == TPF_MODE_TREE_FP64 || mode == TPF_MODE_TREE_FP32; }
 
-// Workspace of the sweeps alone: the atomic column queue, or the per-sweep path's state.
+// Workspace of the sweeps alone: the atomic column queue, with the mid-size kernel's pools of
+// set-aside columns, or the per-sweep paths' state.
 size_t base_workspace(const tpf_network_s &net, int64_t tau, int mode) {
-    if (!is_tree(mode) && uses_large_path(net.n, mode)) {
-        const size_t large = large_workspace_bytes(net.n, tau, mode);
-        return mode != TPF_MODE_FP64 && net.n <= kMaxMidBuses ? std::max(large, mid_workspace_bytes(net.n, tau)) : large;
-    }
+    if (is_tree(mode)) return kQueueBytes;
+    if (uses_large_path(net.n, mode)) return large_workspace_bytes(net.n, tau, mode);
+    if (uses_mid_path(net.n, mode)) return mid_workspace_bytes(net.n, tau);
     return kQueueBytes;
 }
 
@@ -94,7 +93,7 @@ int solve_impl(tpf_network net, const void *S, int32_t dtype, int64_t T, double 
     // column: a start that V_out partly covers is moved into V_out first (a start in V_out itself
     // is read before its column is written).  The per-sweep paths read every start first.
     const size_t bytes = (size_t)T * n * (dtype == TPF_C128 ? 16 : 8);
-    const bool per_sweep = max_iter > 0 && !is_tree(mode) && n > (mode == TPF_MODE_FP64 ? 8 * kMaxSmallTiles : kMaxMidBuses);
+    const bool per_sweep = max_iter > 0 && !is_tree(mode) && uses_large_path(n, mode);
     if (V0 && V0 != V_out && !per_sweep && overlap(V0, V_out, bytes) && !overlap(S, V_out, bytes)) {
         rc = launch_move(V0, V_out, dtype, T * n, st);
         if (rc != TPF_OK) return rc;
@@ -104,7 +103,7 @@ int solve_impl(tpf_network net, const void *S, int32_t dtype, int64_t T, double 
         rc = launch_start_only(n, V0, dtype, T, V_out, iters_out, status_out, st);
     } else if (is_tree(mode)) {
         rc = launch_fpi_tree(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out, st);
-    } else if (mode != TPF_MODE_FP64 && n > 128 && n <= kMaxMidBuses) {
+    } else if (uses_mid_path(n, mode)) {
         rc = launch_fpi_mid(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out, workspace, st);
     } else if (uses_large_path(n, mode)) {
         rc = launch_fpi_large(*net, *dn, mode, S, dtype, T, tol, max_iter, V0, V_out, iters_out, status_out,

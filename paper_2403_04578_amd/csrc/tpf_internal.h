@@ -186,9 +186,13 @@ inline int large64_ksteps(int n) { return (n + 7) / 8 * 2; }
 // Bit pattern of the smallest double x >= 0 with sqrt(x) >= tol, so that x < it exactly when
 // sqrt(x) < tol (sqrt is monotone and correctly rounded).
 unsigned long long square_bound(double tol);
-// The register-resident kernels cover FP64 up to 8 * kMaxSmallTiles PQ buses and the
-// FP32/mixed ones up to 128; larger networks use the large path (FP64, FP32).
-inline bool uses_large_path(int n, int mode) { return mode == TPF_MODE_FP64 ? n > 8 * kMaxSmallTiles : n > 128; }
+// Which kernels a dense mode runs on, for the dispatch and the workspace alike: the
+// register-resident ones (FP64 up to 8 kMaxSmallTiles PQ buses, the FP32 family up to 128), the
+// persistent FP32-family one up to kMaxMidBuses (fpi_mid.hip), the per-sweep ones beyond.
+inline bool uses_mid_path(int n, int mode) { return mode != TPF_MODE_FP64 && n > 128 && n <= kMaxMidBuses; }
+inline bool uses_large_path(int n, int mode) {
+    return n > (mode == TPF_MODE_FP64 ? 8 * kMaxSmallTiles : kMaxMidBuses);
+}
 int launch_start_only(int n, const void *V0, int dtype, int64_t tau, void *V, int32_t *iters,
                       int8_t *status, hipStream_t stream);
 int launch_mismatch_f64(const tpf_network_s &net, const DeviceNet &dn, const void *S, const void *V,
