@@ -19,6 +19,7 @@
 // each column reads and writes only LDS and registers; S, V0 and the result cross HBM
 // once.
 #include <algorithm>
+#include <cmath>
 
 #include "device_math.h"
 #include "tpf_internal.h"
@@ -452,12 +453,16 @@ __global__ __launch_bounds__(kTreeWaves * 64) void fpi_tree32_kernel(
     }
 }
 
+size_t tree32_lds(int np, int levels, int CPW, int ZM) {
+    return (size_t)2 * np * 8 + (size_t)4 * np * 4 + (size_t)(ZM ? ZM + 1 : 0) * np * 4 +
+           (size_t)(ZM == 2 ? 2 : 1) * kTreeWaves * CPW * 2 * np * 4 + (size_t)(4 * np + levels + 2) * 4;
+}
+
 template <typename IO, int CPW, int B, int ZM>
 int launch32_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
                 const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int n = net.n, np = n + 1, levels = dn.tree_levels;
-    const size_t lds = (size_t)2 * np * 8 + (size_t)4 * np * 4 + (size_t)(ZM ? ZM + 1 : 0) * np * 4 +
-                       (size_t)(ZM == 2 ? 2 : 1) * kTreeWaves * CPW * 2 * np * 4 + (size_t)(4 * np + levels + 2) * 4;
+    const int n = net.n, levels = dn.tree_levels;
+    const size_t lds = tree32_lds(n + 1, levels, CPW, ZM);
     if (lds > (size_t)160 * 1024) return fail(TPF_ERR_UNSUPPORTED, "tree operator: network too large for LDS");
     auto k = fpi_tree32_kernel<IO, CPW, B, ZM>;
     if (hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -488,19 +493,30 @@ int launch32_b(const tpf_network_s &net, const DeviceNet &dn, const void *S, int
     return launch32_as<IO, CPW, B, 0>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
 }
 
+// Columns per wavefront and places per lane of a kernel.
+template <int C, int P>
+struct Shape {
+    static constexpr int cols = C, places = P;
+};
+
 // The FP32 form takes 4 columns of 16 lanes up to 128 PQ buses: with half the FP64
 // kernel's registers per position, the wider column group measured fastest there
 // (8 columns of 8 lanes, the FP64 choice, ran the 100-bus year 16 % slower).
+template <typename F>
+int with_shape32(int n, F f) {
+    if (n <= 64) return f(Shape<8, 8>{});
+    if (n <= 128) return f(Shape<4, 8>{});
+    if (n <= 256) return f(Shape<2, 8>{});
+    if (n <= 512) return f(Shape<1, 8>{});
+    if (n <= 1024) return f(Shape<1, 16>{});
+    return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 1,024 PQ buses");
+}
 template <typename IO>
 int launch32_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
                 const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int n = net.n;
-    if (n <= 64) return launch32_b<IO, 8, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 128) return launch32_b<IO, 4, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 256) return launch32_b<IO, 2, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 512) return launch32_b<IO, 1, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 1024) return launch32_b<IO, 1, 16>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 1,024 PQ buses");
+    return with_shape32(net.n, [&](auto s) {
+        return launch32_b<IO, s.cols, s.places>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
+    });
 }
 
 // Three-phase networks: the same passes with three phase nodes per position; a branch
@@ -846,12 +862,16 @@ __global__ __launch_bounds__(kTreeWaves * 64) void fpi_tree3_32_kernel(
     }
 }
 
+size_t tree3_32_lds(int np, int levels, int CPW) {
+    return (size_t)6 * np * 8 + (size_t)24 * np * 4 + (size_t)kTreeWaves * CPW * 6 * np * 4 +
+           (size_t)(4 * np + levels + 2) * 4;
+}
+
 template <typename IO, int CPW, int B>
 int launch3_32_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                   int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int nb = net.n / 3, np = nb + 1, levels = dn.tree_levels;
-    const size_t lds = (size_t)6 * np * 8 + (size_t)24 * np * 4 + (size_t)kTreeWaves * CPW * 6 * np * 4 +
-                       (size_t)(4 * np + levels + 2) * 4;
+    const int nb = net.n / 3, levels = dn.tree_levels;
+    const size_t lds = tree3_32_lds(nb + 1, levels, CPW);
     if (lds > (size_t)160 * 1024) return fail(TPF_ERR_UNSUPPORTED, "tree operator: network too large for LDS");
     auto k = fpi_tree3_32_kernel<IO, CPW, B>;
     if (hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -871,21 +891,30 @@ int launch3_32_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, 
     return TPF_OK;
 }
 
+template <typename F>
+int with_shape3(int nb, F f) {
+    if (nb <= 128) return f(Shape<2, 4>{});
+    if (nb <= 256) return f(Shape<1, 4>{});
+    if (nb <= 512) return f(Shape<1, 8>{});
+    return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 512 three-phase buses");
+}
 template <typename IO>
 int launch3_32_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol,
                   int max_iter, const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int nb = net.n / 3;
-    if (nb <= 128) return launch3_32_as<IO, 2, 4>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (nb <= 256) return launch3_32_as<IO, 1, 4>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (nb <= 512) return launch3_32_as<IO, 1, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 512 three-phase buses");
+    return with_shape3(net.n / 3, [&](auto s) {
+        return launch3_32_as<IO, s.cols, s.places>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
+    });
+}
+
+size_t tree3_lds(int np, int levels, int CPW) {
+    return (size_t)24 * np * 8 + (size_t)kTreeWaves * CPW * 6 * np * 8 + (size_t)(4 * np + levels + 2) * 4;
 }
 
 template <typename IO, int CPW, int B>
 int launch3_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
                const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int nb = net.n / 3, np = nb + 1, levels = dn.tree_levels;
-    const size_t lds = (size_t)24 * np * 8 + (size_t)kTreeWaves * CPW * 6 * np * 8 + (size_t)(4 * np + levels + 2) * 4;
+    const int nb = net.n / 3, levels = dn.tree_levels;
+    const size_t lds = tree3_lds(nb + 1, levels, CPW);
     if (lds > (size_t)160 * 1024) return fail(TPF_ERR_UNSUPPORTED, "tree operator: network too large for LDS");
     auto k = fpi_tree3_kernel<IO, CPW, B>;
     if (hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -911,19 +940,21 @@ int launch3_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int
 template <typename IO>
 int launch3_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
                const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int nb = net.n / 3;
-    if (nb <= 128) return launch3_as<IO, 2, 4>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (nb <= 256) return launch3_as<IO, 1, 4>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (nb <= 512) return launch3_as<IO, 1, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 512 three-phase buses");
+    return with_shape3(net.n / 3, [&](auto s) {
+        return launch3_as<IO, s.cols, s.places>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
+    });
+}
+
+size_t tree_lds(int np, int levels, int CPW, int ZM) {
+    return (size_t)4 * np * 8 + (size_t)(ZM ? ZM + 1 : 0) * np * 8 +
+           (size_t)(ZM == 2 ? 2 : 1) * kTreeWaves * CPW * 2 * np * 8 + (size_t)(4 * np + levels + 2) * 4;
 }
 
 template <typename IO, int CPW, int B, int ZM>
 int launch_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
               const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int n = net.n, np = n + 1, levels = dn.tree_levels;
-    const size_t lds = (size_t)4 * np * 8 + (size_t)(ZM ? ZM + 1 : 0) * np * 8 +
-                       (size_t)(ZM == 2 ? 2 : 1) * kTreeWaves * CPW * 2 * np * 8 + (size_t)(4 * np + levels + 2) * 4;
+    const int n = net.n, levels = dn.tree_levels;
+    const size_t lds = tree_lds(n + 1, levels, CPW, ZM);
     if (lds > (size_t)160 * 1024) return fail(TPF_ERR_UNSUPPORTED, "tree operator: network too large for LDS");
     auto k = fpi_tree_kernel<IO, CPW, B, ZM>;
     if (hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
@@ -962,16 +993,21 @@ int launch_b(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64
 
 // Columns per wavefront: 8 (8 lanes each) up to 128 buses, 2 up to 256, then 1.  (At 99
 // buses: 1.40 ms per year with 8 columns, 1.51 with 4, 2.48 with 1.)
+template <typename F>
+int with_shape64(int n, F f) {
+    if (n <= 64) return f(Shape<8, 8>{});
+    if (n <= 128) return f(Shape<8, 16>{});
+    if (n <= 256) return f(Shape<2, 8>{});
+    if (n <= 512) return f(Shape<1, 8>{});
+    if (n <= 1024) return f(Shape<1, 16>{});
+    return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 1,024 PQ buses");
+}
 template <typename IO>
 int launch_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
               const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int n = net.n;
-    if (n <= 64) return launch_b<IO, 8, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 128) return launch_b<IO, 8, 16>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 256) return launch_b<IO, 2, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 512) return launch_b<IO, 1, 8>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    if (n <= 1024) return launch_b<IO, 1, 16>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
-    return fail(TPF_ERR_UNSUPPORTED, "tree operator: up to 1,024 PQ buses");
+    return with_shape64(net.n, [&](auto s) {
+        return launch_b<IO, s.cols, s.places>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
+    });
 }
 
 // ---- shallow trees
@@ -1276,25 +1312,18 @@ __global__ __launch_bounds__(kTreeWaves * 64) void fpi_tree_rows_kernel(
     }
 }
 
-// Rows of LPC lanes that a network's levels take.
-int level_rows(const tpf_network_s &net, int LPC) {
-    int rows = 0;
-    const int levels = (int)net.tree_level_start.size() - 2;
-    for (int L = 1; L <= levels; ++L)
-        rows += (net.tree_level_start[L + 1] - net.tree_level_start[L] + LPC - 1) / LPC;
-    return rows;
+size_t rows_lds(int slots, int CPW, int PH, size_t real, bool zip) {
+    return (size_t)kTreeWaves * CPW * PH * (slots + 1) * 2 * real + (size_t)(PH * PH + PH) * slots * 2 * real +
+           (real == 4 ? (size_t)PH * slots * 16 : 0) + (zip ? 2 * slots * real : 0);
 }
 
-// Launches the row kernel; TPF_ERR_UNSUPPORTED (nothing launched) when the tree's rows or
-// their LDS do not fit.
+constexpr int log2_lanes(int CPW) { return CPW == 8 ? 0 : CPW == 4 ? 1 : CPW == 2 ? 2 : 3; }  // of 64 / CPW = 8 << k
+
 template <typename IO, typename R, int CPW, int B, int PH, bool ZIP>
 int launch_rows_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
                    const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
-    const int nb = net.n / PH, rows = level_rows(net, 64 / CPW), slots = rows * (64 / CPW);
-    const size_t c2 = 2 * sizeof(R);
-    const size_t lds = (size_t)kTreeWaves * CPW * PH * (slots + 1) * c2 + (size_t)(PH * PH + PH) * slots * c2 +
-                       (sizeof(R) == 4 ? (size_t)PH * slots * 16 : 0) + (ZIP ? (size_t)2 * slots * sizeof(R) : 0);
-    if (rows > B || nb >= 0xffff || lds > (size_t)160 * 1024) return TPF_ERR_UNSUPPORTED;
+    const int nb = net.n / PH, rows = dn.tree_rows[log2_lanes(CPW)];
+    const size_t lds = rows_lds(rows * (64 / CPW), CPW, PH, sizeof(R), ZIP);
     auto k = fpi_tree_rows_kernel<IO, R, CPW, B, PH, ZIP>;
     if (hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return fail(TPF_ERR_DEVICE, "hipFuncSetAttribute failed");
@@ -1310,66 +1339,158 @@ int launch_rows_as(const tpf_network_s &net, const DeviceNet &dn, const void *S,
     return TPF_OK;
 }
 
-// Lanes per column and registers per lane: the fewest padded lanes per column whose state
-// still leaves two wavefronts per SIMD, with rows close to B (a lane's B places are loaded and
-// looped over, used or not).  Measured against the table kernels, us: one phase, 50,000
-// columns, FP64 / FP32: 19 buses 20.7 (28.1) / 17.8 (18.4); 59: 50.1 (67.1) / -; 99 buses,
-// 525,600 columns: 887 (1,349) / 672 (771); 127: 108 (194) / 78 (94); 199: 199 (335) / -;
-// 299: 393 (639) / 269 (273); 399: 614 (794) / 327 (579); 499: 721 (1,091) / 471 (481); 999:
-// 3,695 (4,774) / 1,671 (2,293).  Three phases, 20,000 columns: 39 buses 60 (149) / 44 (64);
-// 79: 153 (270) / 94 (104); 119: 288 (394) / -; 99 buses, 262,800 columns, FP32: 1,024 (1,502).
-// Left to the table kernels (the dashes), which were faster: FP32 with 9 rows of 8 lanes but 6
-// of 16 (59 buses, 40.7 against 38.7), FP32 up to 256 buses with over 10 rows of 16 (159:
-// 137.9 against 120.8), FP64 up to 730 buses with over 12 rows of 64 (699: 2,844 against
-// 2,237; the padded rows leave one workgroup per CU where the tables leave two), three-phase
-// FP32 with over 8 rows of 16 (119: 210 against 180).
-template <typename IO, typename R>
+// ---- which kernel and shape
+//
+// What a pass costs depends on the tree (the rows its levels take and the children of their
+// positions), on the places that a lane holds, and on how many workgroups share a CU, so these
+// are what the choice is made from, with constants fitted to the times of every shape on 85 trees
+// of 5 to 999 buses and 2 to 20 levels (k-ary, evenly filled and bottom-heavy ones), one and three
+// phases, at 500, 6,000 and 50,000 to 200,000 columns and 3 to 6 sweeps: a sweep takes no less
+// than a wavefront's latency (linear in rows, child steps and places; few columns, 3 sweeps), and
+// with more columns than the chip holds its share of the CUs' work (another linear form, divided
+// by the columns of a wavefront and a power of the workgroups per CU).  The forms fit the times
+// within 7 to 18 % rms; against the best shape of each tree the choice loses 0 to 1 % on average
+// at 50,000 columns and more, 1 to 5 % below.  Measured on 86 more trees, time over the table
+// kernels' (FP64, FP32): 0.88 and 0.93 at 50,000 columns (the worst tree 1.02 and 1.13), 0.98 and
+// 1.00 at 6,000, 0.98 and 0.99 at 500.  Cut by bus counts, as measured on k-ary feeders, the
+// choice was up to 4 times slower than the tables on other trees (FP32, 300 buses in 20 levels,
+// 50,000 columns: 2,018 us, now 500).
+struct PassCost {
+    double base, row, step, place;
+    double of(int rows, int steps, double places) const { return base + row * rows + step * steps + place * places; }
+};
+struct TreeCost {
+    PassCost latency, work;  // us per sweep of a wavefront
+    double share;            // workgroups on a CU speed its work up by this power of their number
+};
+constexpr TreeCost kRowsCost[2][2] = {  // [three-phase][FP64]
+    {{{1.43, 0.262, 0.143, 0.132}, {1.02, 0.227, 0.105, 0.021}, 0.75},
+     {{0.83, 0.265, 0.129, 0.139}, {0.78, 0.240, 0.122, 0.038}, 0.80}},
+    {{{2.07, 0.483, 0.150, 0.109}, {0.41, 0.462, 0.208, 0.044}, 0.47},
+     {{2.89, 0.540, 0.158, 0.030}, {1.02, 0.594, 0.249, 0.003}, 0.69}}};
+constexpr TreeCost kTableCost[2][2] = {
+    {{{2.95, 0.134, 0.158, 0.000}, {0.32, 0.108, 0.051, 0.466}, 0.48},
+     {{3.69, 0.071, 0.190, 0.122}, {0.40, 0.164, 0.106, 0.391}, 0.46}},
+    {{{1.98, 0.481, 0.159, 0.524}, {0.69, 0.572, 0.040, 1.389}, 0.62},
+     {{3.91, 0.366, 0.310, 0.925}, {0.62, 0.539, 0.121, 2.045}, 0.34}}};
+
+// Workgroups of a kernel per CU: what its registers allow (asked once per kernel), and its LDS.
+template <auto Kernel>
+int resident(size_t lds) {
+    static const int by_registers = [] {
+        int v = 0;
+        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, Kernel, kTreeWaves * 64, 0) == hipSuccess ? v : 1;
+    }();
+    return std::max(1, std::min(by_registers, (int)((size_t)160 * 1024 / lds)));
+}
+
+// Microseconds per sweep of tau columns.
+double tree_cost(const TreeCost &c, const DeviceNet &dn, int64_t tau, int CPW, double places, int per_cu) {
+    const int k = log2_lanes(CPW);
+    const double wavefronts_per_cu = (double)tau / (kTreeWaves * CPW * (double)num_cus());
+    return std::max(c.latency.of(dn.tree_rows[k], dn.tree_steps[k], places),
+                    c.work.of(dn.tree_rows[k], dn.tree_steps[k], places) * wavefronts_per_cu / std::pow(per_cu, c.share));
+}
+
+// The table kernels' cost for a network without a constant-impedance share; negative when they
+// do not take it.
+template <typename IO, typename R, int PH>
+double table_cost(const tpf_network_s &net, const DeviceNet &dn, int64_t tau) {
+    constexpr bool kF64 = sizeof(R) == 8;
+    const int nb = net.n / PH, np = nb + 1, levels = dn.tree_levels;
+    double cost = -1.0;
+    auto take = [&](auto s, size_t lds, auto per_cu) {
+        if (lds <= (size_t)160 * 1024)
+            cost = tree_cost(kTableCost[PH == 3][kF64], dn, tau, s.cols, nb * s.cols / 64.0, per_cu(lds));
+        return TPF_OK;
+    };
+    if constexpr (PH == 3 && kF64)
+        (void)with_shape3(nb, [&](auto s) {
+            return take(s, tree3_lds(np, levels, s.cols), resident<fpi_tree3_kernel<IO, s.cols, s.places>>);
+        });
+    else if constexpr (PH == 3)
+        (void)with_shape3(nb, [&](auto s) {
+            return take(s, tree3_32_lds(np, levels, s.cols), resident<fpi_tree3_32_kernel<IO, s.cols, s.places>>);
+        });
+    else if constexpr (kF64)
+        (void)with_shape64(nb, [&](auto s) {
+            return take(s, tree_lds(np, levels, s.cols, 0), resident<fpi_tree_kernel<IO, s.cols, s.places, 0>>);
+        });
+    else
+        (void)with_shape32(nb, [&](auto s) {
+            return take(s, tree32_lds(np, levels, s.cols, 0), resident<fpi_tree32_kernel<IO, s.cols, s.places, 0>>);
+        });
+    return cost;
+}
+
+// Launches the row kernel in its best shape; TPF_ERR_UNSUPPORTED (nothing launched) when the
+// tree fits none or the row kernel is not the better one by 5 %, where the model's error would decide.
+template <typename IO, typename R, int PH>
 int launch_rows(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
                 const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
     constexpr bool kF64 = sizeof(R) == 8;
+    const int nb = net.n / PH;
     // (rows are at least the levels; a constant-impedance share needs the tables' G')
-    if (dn.aZ || dn.tree_levels > 20) return TPF_ERR_UNSUPPORTED;
-    const int r8 = level_rows(net, 8), r16 = level_rows(net, 16), r32 = level_rows(net, 32), r64 = level_rows(net, 64);
-#define TPF_ROWS3(C, B) \
-    return launch_rows_as<IO, R, C, B, 3, false>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st)
-#define TPF_ROWS(C, B)                                                                                           \
-    return dn.aP ? launch_rows_as<IO, R, C, B, 1, true>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st) \
-                 : launch_rows_as<IO, R, C, B, 1, false>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st)
-    if (dn.tree_phases == 3) {
-        if (r8 <= 4) TPF_ROWS3(8, 4);
-        if (r16 <= 5) TPF_ROWS3(4, 5);
-        if (r16 <= 8) TPF_ROWS3(4, 8);
-        if constexpr (kF64) {
-            if (r32 <= 8) TPF_ROWS3(2, 8);
+    if (dn.aZ || dn.tree_levels > 20 || nb >= 0xffff) return TPF_ERR_UNSUPPORTED;
+    double best = 0.0;
+    int pick = 0;
+    auto consider = [&](auto s) {
+        const int rows = dn.tree_rows[log2_lanes(s.cols)];
+        const size_t lds = rows_lds(rows * (64 / s.cols), s.cols, PH, sizeof(R), dn.aP != nullptr);
+        if (rows > s.places || lds > (size_t)160 * 1024) return;
+        const double cost = tree_cost(kRowsCost[PH == 3][kF64], dn, tau, s.cols, s.places,
+                                      resident<fpi_tree_rows_kernel<IO, R, s.cols, s.places, PH, false>>(lds));
+        if (!pick || cost < best) best = cost, pick = 100 * s.cols + s.places;
+    };
+    auto launch = [&](auto s) {
+        if constexpr (PH == 1) {
+            if (dn.aP)
+                return launch_rows_as<IO, R, s.cols, s.places, 1, true>(net, dn, S, tau, tol, max_iter, V0, V, iters,
+                                                                        status, st);
         }
-        return TPF_ERR_UNSUPPORTED;
-    }
-    if (r8 <= 4) TPF_ROWS(8, 4);
-    if (r8 <= 8) TPF_ROWS(8, 8);
-    if constexpr (kF64) {
-        if (r8 <= 10) TPF_ROWS(8, 10);
-    } else {
-        if (r16 <= 6) return TPF_ERR_UNSUPPORTED;
-    }
-    if (r16 <= 8) TPF_ROWS(4, 8);
-    if (r16 <= 10) TPF_ROWS(4, 10);
-    // few columns leave wavefronts idle: one each, with the fewest rows to walk (500 columns,
-    // FP64: 199 buses 32.9 to 21.9 us, 299 buses 35.7 to 27.9)
-    if ((kF64 || net.n > 256) && tau < 8 * (int64_t)num_cus() && r64 <= 12) TPF_ROWS(1, 12);
-    if constexpr (kF64) {
-        if (r16 <= 12) TPF_ROWS(4, 12);
-        if (r16 <= 15) TPF_ROWS(4, 15);
-        if (r32 <= 13) TPF_ROWS(2, 13);
-    } else {
-        if (net.n <= 256) return TPF_ERR_UNSUPPORTED;
-        if (r32 <= 13) TPF_ROWS(2, 13);
-        if (r32 <= 16) TPF_ROWS(2, 16);
-    }
-    if (r64 <= 12) TPF_ROWS(1, 12);
-    if (kF64 && net.n <= 730) return TPF_ERR_UNSUPPORTED;
-    TPF_ROWS(1, 20);
-#undef TPF_ROWS
-#undef TPF_ROWS3
+        return launch_rows_as<IO, R, s.cols, s.places, PH, false>(net, dn, S, tau, tol, max_iter, V0, V, iters, status,
+                                                                  st);
+    };
+    auto each = [&](auto f) {  // the shapes built: places so that two wavefronts fit a SIMD or more
+        f(Shape<8, 4>{});
+        if constexpr (PH == 3) {
+            f(Shape<4, 5>{});
+            f(Shape<4, 8>{});
+            if constexpr (kF64) f(Shape<2, 8>{});
+        } else {
+            f(Shape<8, 8>{});
+            f(Shape<4, 8>{});
+            f(Shape<4, 10>{});
+            f(Shape<2, 13>{});
+            f(Shape<1, 12>{});
+            f(Shape<1, 20>{});
+            if constexpr (kF64) {
+                f(Shape<8, 10>{});
+                f(Shape<4, 12>{});
+                f(Shape<4, 15>{});
+            } else {
+                f(Shape<2, 16>{});
+            }
+        }
+    };
+    each(consider);
+    if (!pick) return TPF_ERR_UNSUPPORTED;
+    const double tables = table_cost<IO, R, PH>(net, dn, tau);
+    if (tables >= 0.0 && best >= 0.95 * tables) return TPF_ERR_UNSUPPORTED;
+    int rc = TPF_ERR_UNSUPPORTED;
+    each([&](auto s) {
+        if (pick == 100 * s.cols + s.places) rc = launch(s);
+    });
+    return rc;
+}
+
+// The row kernel for loads of IO and state of R, any number of phases.
+template <typename IO, typename R>
+int launch_rows_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,
+                   const void *V0, void *V, int32_t *iters, int8_t *status, hipStream_t st) {
+    if (dn.tree_phases == 3)
+        return launch_rows<IO, R, 3>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
+    return launch_rows<IO, R, 1>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, st);
 }
 
 }  // namespace
@@ -1382,10 +1503,10 @@ int launch_fpi_tree(const tpf_network_s &net, const DeviceNet &dn, int mode, con
         const bool c128 = dtype == TPF_C128;
         const int rc =
             mode == TPF_MODE_TREE_FP32
-                ? (c128 ? launch_rows<double, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream)
-                        : launch_rows<float, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream))
-                : (c128 ? launch_rows<double, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream)
-                        : launch_rows<float, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream));
+                ? (c128 ? launch_rows_io<double, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream)
+                        : launch_rows_io<float, float>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream))
+                : (c128 ? launch_rows_io<double, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream)
+                        : launch_rows_io<float, double>(net, dn, S, tau, tol, max_iter, V0, V, iters, status, stream));
         if (rc != TPF_ERR_UNSUPPORTED) return rc;
     }
     if (mode == TPF_MODE_TREE_FP32) {

@@ -333,6 +333,15 @@ static int upload(tpf_network_s &net, DeviceNet &dn) {
         if (!h2d(dn.tree_i, ti.data(), ti.size() * 4) || !h2d(dn.tree_z, tz.data(), tz.size() * 8))
             return fail(TPF_ERR_DEVICE, "host-to-device copy failed (tree)");
         dn.tree_levels = levels;
+        for (int k = 0; k < 4; ++k)
+            for (int L = 1; L <= levels; ++L)
+                for (int a = net.tree_level_start[L]; a < net.tree_level_start[L + 1]; a += 8 << k) {
+                    int most = 0;
+                    for (int p = a; p < std::min<int>(a + (8 << k), net.tree_level_start[L + 1]); ++p)
+                        most = std::max<int>(most, net.tree_c1[p] - net.tree_c0[p]);
+                    dn.tree_rows[k] += 1;
+                    dn.tree_steps[k] += (most + 1) / 2;
+                }
         dn.tree_phases = ph;
     }
     // ---- ZIP shares

@@ -95,6 +95,9 @@ struct DeviceNet {
     // the branch impedance (phases x phases complex) then w of its phases, as doubles.
     int tree_levels = 0;
     int tree_phases = 1;
+    // By lanes per column 8 << k: the rows of lanes the levels take, and over these rows half
+    // the most children of a position, rounded up (what a pass walks; fpi_tree.hip).
+    int tree_rows[4] = {0, 0, 0, 0}, tree_steps[4] = {0, 0, 0, 0};
     int32_t *tree_i = nullptr;
     double *tree_z = nullptr;
     double *aI = nullptr, *aP = nullptr;  // [n] each
