@@ -141,10 +141,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g = lane >> 4, j = lane & 15;
     const int wr = (wave >> 1) * 2, wc = (wave & 1) * 2;  // first row group, first column group
-    const bool rows_fast = (size_t)row_blocks * 64 * KB * 16 <= ((size_t)2 << 20);
     for (int t = blockIdx.x; t < ct * row_blocks; t += gridDim.x) {
-        const int c0 = (rows_fast ? t / row_blocks : t % ct) * 64;
-        const int rb = rows_fast ? t % row_blocks : t / ct;
+        const int c0 = (t % ct) * 64, rb = t / ct;
         d4x m1[2][2], m2[2][2], m3[2][2];
 #pragma unroll
         for (int a = 0; a < 2; ++a)
