@@ -85,6 +85,22 @@ def test_any_three_phase_tree(gpu, n, levels, T):
     assert np.abs(V.cpu().numpy()[pick] - oracle.fpi(onet, S[pick], 1e-10, 200).V).max() <= 1e-6
 
 
+@pytest.mark.parametrize("n,levels,phases", [
+    (12, 4, 1), (24, 3, 1), (45, 6, 1), (60, 5, 1), (60, 8, 1), (60, 10, 1), (80, 7, 1), (99, 9, 1), (127, 5, 1),
+    (127, 9, 1), (12, 4, 3), (30, 5, 3), (30, 8, 3), (60, 5, 3), (60, 8, 3), (99, 6, 3)])
+def test_calls_that_fill_the_chip(gpu, n, levels, phases):
+    net, onet, S = _case(n, levels, False, 1_000, phases=phases)
+    T = 60_001
+    Sd = torch.from_numpy(S).to(gpu).repeat(61, 1)[:T].contiguous()
+    pick = np.r_[0:3, 517, T - 4:T]
+    V, it, _ = tpf.solve_timeseries(net, Sd, 0.0, 3, mode="tree_fp64")
+    S = S[pick % 1_000]
+    assert int(it.min()) == 3 and np.abs(V[pick].cpu().numpy() - oracle.fpi(onet, S, 0.0, 3).V).max() <= 1e-12
+    V, _, st = tpf.solve_timeseries(net, Sd, 1e-6, 100, mode="tree_fp32")
+    assert int(st.max()) == tpf.ST_CONVERGED
+    assert np.abs(V[pick].cpu().numpy() - oracle.fpi(onet, S, 1e-10, 200).V).max() <= 1e-6
+
+
 def _ms(gpu, n, levels, heavy, mode):
     net, _, S = _case(n, levels, heavy, 2_000)
     S = torch.from_numpy(S).to(gpu).repeat(25, 1)
