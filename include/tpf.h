@@ -60,8 +60,9 @@ enum { TPF_C64 = 0, TPF_C128 = 1 };
  *   MIXED_BF16  sweeps on BF16 MFMA with FP32 accumulation until the low-precision
  *               iteration stalls, then FP32-accurate sweeps (one full FP32 sweep, then
  *               sweeps on the change of the injections) to the tolerance;
- *   MIXED_FP16  the same with FP16 operands under a per-column power-of-two scale; its
- *               FP32-accurate sweep splits Z and I into FP16 high and low parts.
+ *   MIXED_FP16  the same with FP16 operands under a per-column power-of-two scale; up to
+ *               128 PQ buses its FP32-accurate sweep splits Z and I into FP16 high and low
+ *               parts, beyond it is an FP32 product.
  *   Convergence is only declared on an FP32-accurate iterate.  In FP32 and mixed
  *   modes tol must be >= 5e-7 pu (the FP32 state floor).
  * Network size: these four modes run any n.  Beyond 320 PQ buses they use a per-sweep

@@ -6,7 +6,7 @@
 // As kernels of their own per sweep (fpi_large.hip) these networks moved their state,
 // injections and operands through HBM four times a sweep, waited on three launches per
 // sweep, and queued launches up to max_iter (300 buses, mixed FP16: 8.26 ms for 210,240
-// columns and 0.54 ms for 1,000; here 3.55 and 0.11 ms).  Here S is read and V written once.  The
+// columns and 0.50 ms for 1,000; here 3.20 and 0.11 ms).  Here S is read and V written once.  The
 // iterates, the per-column schedule and the results are those of that path bit for bit
 // (mixed_steps.h); columns of a batch may be at different stages, so a sweep runs the
 // 16-bit product for the 16-column groups that have a column wanting it and the FP32 product
@@ -15,7 +15,8 @@
 // Bound: the FP32 product by the matrix cores (a column needs about one; 57,000 cycles of a
 // batch's 195,000 at 299 buses), the 16-bit products by the operator's way from L2 (0.73 MB
 // per batch and sweep, 11,000 cycles), the injections by vector instructions (8,000 per
-// sweep).  Two workgroups of 16 columns per CU (128 registers, spills) took 3.76 ms.
+// sweep; cycles of a build that took 3.55 ms).  Two workgroups of 16 columns per CU (128
+// registers, spills) took 3.76 ms instead of those.
 #include <type_traits>
 
 #include "mixed_steps.h"
@@ -704,7 +705,7 @@ int launch_as(const tpf_network_s &net, const DeviceNet &dn, const void *S, int6
 }
 
 // Batches of 32 columns share a product's way through the operator (300 buses, 210,240
-// columns: 3.55 ms against 4.39 ms with 16); 16 go to more CUs when the columns do not fill
+// columns: mixed FP16 3.20 ms against 4.01 with 16, FP32 6.61 and 7.02); 16 go to more CUs when the columns do not fill
 // the chip anyway.
 template <int MODE, typename IO>
 int launch_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int64_t tau, double tol, int max_iter,

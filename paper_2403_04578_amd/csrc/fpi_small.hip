@@ -2,20 +2,20 @@
 //
 // Algorithm 1 (Sec. IV-A) evaluates V <- Z conj(S ./ V) + w for every power flow
 // (column) of the reshaped load matrix until the voltage step of that column
-// falls below the tolerance.  Here each wavefront is an independent worker that
-// owns 16 column slots.  Per sweep it
-//   1. forms the current injection conj(S./V) = conj(S) V / |V|^2 (Eq. (3)) of the
-//      slot's buses straight into its MFMA B operand (never stored to memory),
-//   2. multiplies by Z on the 16x16x4 FP64 matrix cores, the complex product as three
-//      real ones, with Z streamed from L2 in fragment order,
-//   3. adds w, measures max_i |V'_i - V_i| per column with lane shuffles, and
-//   4. retires converged columns (writes V, sweep count and status) and refills
+// falls below the tolerance.  Here a workgroup owns 16 column slots, and each of its
+// wavefronts some tiles of 16 buses of all of them.  Per sweep it
+//   1. multiplies the injections (MFMA B operand, in LDS, never stored to memory) by Z on the
+//      16x16x4 FP64 matrix cores, the complex product as three or four real ones, with Z
+//      streamed from L2 in fragment order,
+//   2. adds w, measures max_i |V'_i - V_i| per column with atomics on LDS, and forms the next
+//      injections conj(S./V) = conj(S) V / |V|^2 (Eq. (3)) into the operand's other copy,
+//   3. retires converged columns (writes V, sweep count and status) and refills
 //      their slots from a global atomic column queue, so the 16-wide MFMA tiles
 //      stay full while columns finish after different numbers of sweeps.
 //
 // Register layout.  A tile is 16 buses; the real and imaginary parts of Z are separate
 // operands.  The FP64 MFMA leaves tile row g + 4r of output column j in lane 16g + j,
-// register r, for each of the three products, so a lane combines Re and Im of buses
+// register r, for each of the products, so a lane combines Re and Im of buses
 // 16t + g + 4r of its column by itself.  For k-step 4t + r lane 16g + j must supply
 // I[16t + 4r + g][j], which is exactly the bus it holds in register r of tile t: the
 // epilogue lane writes the operand entry that the same lane position reads.
@@ -43,7 +43,7 @@ __device__ __forceinline__ void st_c(IO *p, double re, double im) {
 }
 
 // One workgroup of NW waves owns 16 column slots; wave w computes the 16-bus tiles
-// t = w' + NW q (w' its rotated role) of all 16 columns.  Per lane and owned tile the slot's
+// t = w + NW q of all 16 columns.  Per lane and owned tile the slot's
 // voltages and loads of buses 16t + g + 4r, r = 0..3, in registers; the injections
 // conj(S./V) of all buses live in LDS as Ib[bus][16 columns] complex values: the lane that
 // holds bus 16t + g + 4r of column j writes row 16t + 4r + g, and k-step kt reads rows

@@ -1019,8 +1019,9 @@ int launch_io(const tpf_network_s &net, const DeviceNet &dn, const void *S, int6
 // injection is formed where the backward pass needs it and V' where the forward pass makes
 // the drop, so that a position costs its children's reads and two writes per sweep.  The
 // kernels above visit a level's positions through the tables (four dependent LDS reads per
-// visit) and serve the trees whose rows do not fit B registers (long chains).  Sums and
-// roundings are those of the kernels above.
+// visit) and serve the trees whose rows do not fit B registers (long chains).  The order of the
+// sums and the roundings are those of the kernels above (FP64: but for a reciprocal in about
+// 2^38, device_math.h).
 //
 // Bound by the chain of LDS round trips, one per row and pass, between which a wavefront
 // waits; reading the next row's operands ahead did not pay (registers cost a wavefront per
@@ -1346,33 +1347,37 @@ int launch_rows_as(const tpf_network_s &net, const DeviceNet &dn, const void *S,
 // are what the choice is made from, with constants fitted to the times of every shape on 85 trees
 // of 5 to 999 buses and 2 to 20 levels (k-ary, evenly filled and bottom-heavy ones), one and three
 // phases, at 500, 6,000 and 50,000 to 200,000 columns and 3 to 6 sweeps: a sweep takes no less
-// than a wavefront's latency (linear in rows, child steps and places; few columns, 3 sweeps), and
+// than a wavefront's latency (linear in rows, child steps, places and levels; few columns, 3 sweeps), and
 // with more columns than the chip holds its share of the CUs' work (another linear form, divided
 // by the columns of a wavefront and a power of the workgroups per CU).  The forms fit the times
 // within 7 to 18 % rms; against the best shape of each tree the choice loses 0 to 1 % on average
-// at 50,000 columns and more, 1 to 5 % below.  Measured on 86 more trees, time over the table
-// kernels' (FP64, FP32): 0.88 and 0.93 at 50,000 columns (the worst tree 1.02 and 1.13), 0.98 and
-// 1.00 at 6,000, 0.98 and 0.99 at 500.  Cut by bus counts, as measured on k-ary feeders, the
-// choice was up to 4 times slower than the tables on other trees (FP32, 300 buses in 20 levels,
-// 50,000 columns: 2,018 us, now 500).
+// at 50,000 columns and more, 1 to 4 % below.  Measured on 86 more trees, time over the table
+// kernels' (FP64, FP32): 0.90 and 0.95 at 50,000 columns (the worst tree 1.03 and 1.25), 0.98 and
+// 1.01 at 6,000 and at 500; on k-ary feeders of 199 to 999 buses the times of the rule before are
+// kept, but for FP32 at 799 and 999 buses and up to 500 columns (99 and 110 us, 91 and 99
+// before: a row kernel that starts later pays off over nine sweeps).  Cut by bus counts, as measured
+// on k-ary feeders, the choice was up to 4 times slower than the tables on other trees (FP32,
+// 300 buses in 20 levels, 50,000 columns: 2,018 us, now 500).
 struct PassCost {
     double base, row, step, place;
     double of(int rows, int steps, double places) const { return base + row * rows + step * steps + place * places; }
 };
 struct TreeCost {
-    PassCost latency, work;  // us per sweep of a wavefront
-    double share;            // workgroups on a CU speed its work up by this power of their number
+    PassCost latency;  // us per sweep of a wavefront, and a level's share of it
+    double level;
+    PassCost work;
+    double share;  // workgroups on a CU speed its work up by this power of their number
 };
 constexpr TreeCost kRowsCost[2][2] = {  // [three-phase][FP64]
-    {{{1.43, 0.262, 0.143, 0.132}, {1.02, 0.227, 0.105, 0.021}, 0.75},
-     {{0.83, 0.265, 0.129, 0.139}, {0.78, 0.240, 0.122, 0.038}, 0.80}},
-    {{{2.07, 0.483, 0.150, 0.109}, {0.41, 0.462, 0.208, 0.044}, 0.47},
-     {{2.89, 0.540, 0.158, 0.030}, {1.02, 0.594, 0.249, 0.003}, 0.69}}};
+    {{{1.38, 0.180, 0.146, 0.131}, 0.096, {1.02, 0.227, 0.105, 0.021}, 0.75},
+     {{0.78, 0.155, 0.136, 0.137}, 0.124, {0.78, 0.240, 0.122, 0.038}, 0.80}},
+    {{{1.77, 0.519, 0.134, 0.141}, 0.000, {0.41, 0.461, 0.209, 0.043}, 0.47},
+     {{2.83, 0.547, 0.156, 0.035}, 0.000, {0.95, 0.593, 0.247, 0.014}, 0.68}}};
 constexpr TreeCost kTableCost[2][2] = {
-    {{{2.95, 0.134, 0.158, 0.000}, {0.32, 0.108, 0.051, 0.466}, 0.48},
-     {{3.69, 0.071, 0.190, 0.122}, {0.40, 0.164, 0.106, 0.391}, 0.46}},
-    {{{1.98, 0.481, 0.159, 0.524}, {0.69, 0.572, 0.040, 1.389}, 0.62},
-     {{3.91, 0.366, 0.310, 0.925}, {0.62, 0.539, 0.121, 2.045}, 0.34}}};
+    {{{3.12, 0.076, 0.163, 0.000}, 0.041, {0.32, 0.107, 0.051, 0.466}, 0.48},
+     {{3.62, 0.085, 0.188, 0.113}, 0.000, {0.40, 0.164, 0.106, 0.391}, 0.46}},
+    {{{1.97, 0.425, 0.156, 0.547}, 0.058, {0.69, 0.572, 0.040, 1.389}, 0.62},
+     {{3.58, 0.426, 0.279, 1.040}, 0.000, {0.62, 0.539, 0.121, 2.045}, 0.34}}};
 
 // Workgroups of a kernel per CU: what its registers allow (asked once per kernel), and its LDS.
 template <auto Kernel>
@@ -1388,7 +1393,7 @@ int resident(size_t lds) {
 double tree_cost(const TreeCost &c, const DeviceNet &dn, int64_t tau, int CPW, double places, int per_cu) {
     const int k = log2_lanes(CPW);
     const double wavefronts_per_cu = (double)tau / (kTreeWaves * CPW * (double)num_cus());
-    return std::max(c.latency.of(dn.tree_rows[k], dn.tree_steps[k], places),
+    return std::max(c.latency.of(dn.tree_rows[k], dn.tree_steps[k], places) + c.level * dn.tree_levels,
                     c.work.of(dn.tree_rows[k], dn.tree_steps[k], places) * wavefronts_per_cu / std::pow(per_cu, c.share));
 }
 
