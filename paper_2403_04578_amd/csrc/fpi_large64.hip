@@ -338,22 +338,30 @@ __global__ __launch_bounds__(256) void gemm64_direct_kernel(
     }
 }
 
-// The same for the fewest columns: a workgroup of three wavefronts per 16 x 16 tile, one of the
-// sums each, so that a sweep takes about one chain of KT products (64 cycles each).  Bound by the
-// latency of the operands, which the three wavefronts stage through LDS for one another in
-// chunks of kChunk k-steps, requested two chunks ahead of their products.
-constexpr int kChunk = 12;
+// The same for the fewest columns: a workgroup per 16 x 16 tile, a wavefront for each of the
+// three sums, so that a sweep takes about one chain of KT products (64 cycles each), and
+// kLoaders more that bring the operands: they request them kSets chunks of kChunk k-steps before
+// they write them to LDS, real and imaginary parts and what the third product takes in planes
+// of their own, so that a product reads the 1 KB it uses.  Three buffers: while the sums are at
+// chunk c and read on into c + 1, chunk c + 2 is written.  A sweep of one column at 999 buses:
+// 22 us with the three wavefronts bringing the operands themselves, as with one loader; 17 with
+// four (LDS writes and sums each take about as long as the chain, 6.7 us); 8 loaders 20, chunks of 12
+// and more chunks requested ahead 17.
+constexpr int kChunk = 8, kLoaders = 4, kSets = 2;
 
 template <bool THREE, typename IO>
-__global__ __launch_bounds__(192) void gemm64_sums_kernel(
+__global__ __launch_bounds__(64 * (3 + kLoaders)) void gemm64_sums_kernel(
     const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
     const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
     const IO *__restrict__ S, const ZipShares zs, double *__restrict__ x, unsigned long long *__restrict__ dmax) {
-    constexpr int kOwn = kChunk / 3;  // k-steps of a chunk that a wavefront stages
-    constexpr int kAhead = 4;         // k-steps between a read from LDS and its product
+    constexpr int kPlanes = THREE ? 6 : 4;  // Zr, Zi, Ir, Ii (and Zr - Zi, Ir - Ii)
+    constexpr int kAhead = 4;               // k-steps between a read from LDS and its product
+    constexpr int kOwn = kChunk / kLoaders;  // k-steps of a chunk that a loader brings
     const int nact = *na;
     const int ct = (nact + 15) / 16;
-    __shared__ d2x stage[2][kChunk][2][64];  // [buffer][k-step][Z, I][lane]
+    const int chunks = (KT + kChunk - 1) / kChunk;
+    const int turns = (chunks + 2 + kSets - 1) / kSets * kSets;  // chunks written: two are ahead
+    __shared__ double stage[3][kChunk][kPlanes][64];  // [buffer][k-step][plane][lane]
     __shared__ double part[3][4][64];
     __shared__ unsigned long long red[16];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -364,76 +372,94 @@ __global__ __launch_bounds__(192) void gemm64_sums_kernel(
         if (tid < 16) red[tid] = 0ull;
         const bool live = c0 + j < nact;
         const long long c = act[live ? c0 + j : nact - 1];
-        const d2x *Ap = A + (size_t)rt * KT * 64 + lane;
-        const d2x *Bp = B + c * KB + g;
-        d2x ra[2][kOwn], rb[2][kOwn];
-        auto fetch = [&](int u, int k0) __attribute__((always_inline)) {  // chunk that starts at k-step k0
+        auto bring = [&] {
+            const int own = kOwn * (wave - 3);
+            const d2x *Ap = A + (size_t)rt * KT * 64 + lane;
+            const d2x *Bp = B + c * KB + g;
+            d2x ra[kSets][kOwn], rb[kSets][kOwn];
+            auto fetch = [&](int u, int chunk) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < kOwn; ++i) {
-                const int kt = k0 + kOwn * wave + i, k = kt < KT ? kt : KT - 1;  // past the end: unused
-                ra[u][i] = Ap[(size_t)k * 64];
-                rb[u][i] = Bp[4 * k];
+                for (int i = 0; i < kOwn; ++i) {
+                    const int kt = chunk * kChunk + own + i, k = kt < KT ? kt : KT - 1;
+                    ra[u][i] = Ap[(size_t)k * 64];
+                    rb[u][i] = Bp[4 * k];
+                }
+            };
+            auto put = [&](int u, int chunk, int buffer) __attribute__((always_inline)) {
+                if ((chunk + 1) * kChunk > KT)  // products past the end add nothing
+#pragma unroll
+                    for (int i = 0; i < kOwn; ++i)
+                        if (chunk * kChunk + own + i >= KT) ra[u][i] = rb[u][i] = d2x{0.0, 0.0};
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i) {
+                    const d2x z = ra[u][i], q = rb[u][i];
+                    double(*s)[64] = stage[buffer][own + i];
+                    s[0][lane] = z.x, s[1][lane] = z.y;
+                    s[2][lane] = q.x, s[3][lane] = q.y;
+                    if constexpr (THREE) s[4][lane] = z.x - z.y, s[5][lane] = q.x - q.y;
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < kSets; ++u) {
+                fetch(u, u);
+                __builtin_amdgcn_sched_barrier(0);
             }
-        };
-        auto put = [&](int u) __attribute__((always_inline)) {
+            int buffer = 0;  // of chunk k + u
+            for (int k = 0; k < turns; k += kSets) {
 #pragma unroll
-            for (int i = 0; i < kOwn; ++i) {
-                stage[u][kOwn * wave + i][0][lane] = ra[u][i];
-                stage[u][kOwn * wave + i][1][lane] = rb[u][i];
+                for (int u = 0; u < kSets; ++u) {
+                    put(u, k + u, buffer);
+                    __builtin_amdgcn_sched_barrier(0);
+                    fetch(u, k + u + kSets);
+                    __builtin_amdgcn_sched_barrier(0);
+                    lds_barrier();
+                    buffer = buffer == 2 ? 0 : buffer + 1;
+                }
             }
         };
         auto sum = [&](auto which) __attribute__((always_inline)) {
             constexpr int P = decltype(which)::value;
+            constexpr bool kBoth = P == 2 && !THREE;  // the third sum of four products
+            constexpr int kZ = P == 2 ? (THREE ? 4 : 0) : P, kI = P == 2 ? (THREE ? 5 : 3) : 2 + P;
             d4x m = d4x{0, 0, 0, 0};
-            d2x z[kChunk], i[kChunk];
-            auto read = [&](int u, int k) __attribute__((always_inline)) {
-                z[k] = stage[u][k][0][lane];
-                i[k] = stage[u][k][1][lane];
+            double z[kChunk], i[kChunk], z2[kChunk], i2[kChunk];
+            auto read = [&](int buffer, int k) __attribute__((always_inline)) {
+                z[k] = stage[buffer][k][kZ][lane];
+                i[k] = stage[buffer][k][kI][lane];
+                if constexpr (kBoth) z2[k] = stage[buffer][k][1][lane], i2[k] = stage[buffer][k][2][lane];
             };
-            auto step = [&](int k) __attribute__((always_inline)) {
-                m = P == 0   ? mma64(z[k].x, i[k].x, m)
-                    : P == 1 ? mma64(z[k].y, i[k].y, m)
-                             : third<THREE>(z[k], i[k], z[k].x - z[k].y, i[k].x - i[k].y, m);
-            };
-            fetch(0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(1, kChunk);
-            put(0);
             lds_barrier();
-            for (int k0 = 0; k0 < KT; k0 += 2 * kChunk) {
+            lds_barrier();  // chunks 0 and 1 are there
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {  // buffer u: the chunk at k0 + u kChunk
-                    const int k1 = k0 + u * kChunk;
-                    fetch(u, k1 + 2 * kChunk);
+            for (int k = 0; k < kAhead; ++k) read(0, k);
+            int buffer = 0;
+            for (int chunk = 0; chunk < chunks; ++chunk) {
+                const int next = buffer == 2 ? 0 : buffer + 1;
+#pragma unroll
+                for (int k = 0; k < kChunk; ++k) {
+                    if (k + kAhead < kChunk)
+                        read(buffer, k + kAhead);
+                    else
+                        read(next, k + kAhead - kChunk);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (k1 + kChunk <= KT) {
-#pragma unroll
-                        for (int k = 0; k < kAhead; ++k) read(u, k);
-#pragma unroll
-                        for (int k = 0; k < kChunk; ++k) {
-                            if (k + kAhead < kChunk) read(u, k + kAhead);
-                            __builtin_amdgcn_sched_barrier(0);
-                            step(k);
-                        }
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < kChunk; ++k)
-                            if (k1 + k < KT) read(u, k), step(k);
-                    }
-                    put(u ^ 1);  // its last readers passed the previous barrier
-                    lds_barrier();
+                    m = mma64(z[k], i[k], m);
+                    if constexpr (kBoth) m = mma64(z2[k], i2[k], m);
                 }
+                lds_barrier();
+                buffer = next;
             }
+            for (int k = chunks + 2; k < turns; ++k) lds_barrier();
 #pragma unroll
             for (int r = 0; r < 4; ++r) part[P][r][lane] = m[r];
         };
+        if (wave >= 3) bring();
         if (wave == 0) sum(std::integral_constant<int, 0>{});
         if (wave == 1) sum(std::integral_constant<int, 1>{});
         if (wave == 2) sum(std::integral_constant<int, 2>{});
         __syncthreads();  // the sums visible, red clear
         double e = 0.0, poison = 0.0;
-        for (int r = wave; r < 4; r += 3) {
-            const int bus = 16 * rt + g + 4 * r;
+        if (wave < 4) {
+            const int r = wave, bus = 16 * rt + g + 4 * r;
             if (live && bus < n) {
                 const double p1 = part[0][r][lane], p2 = part[1][r][lane], p3 = part[2][r][lane];
                 update64<IO>(p1 - p2, imaginary<THREE>(p1, p2, p3), w[bus], c, bus, n, KB, S, zs,
@@ -567,11 +593,11 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     // the device has already posted that none is left (all_retired).
     // Shape by the tiles a batch has (the results do not depend on it): staged 64 x 64 tiles once
     // each CU gets six of them, the direct ones from three quarters of a 64 x 64 tile per CU,
-    // 32 x 32 below, and single tiles by three wavefronts up to two per CU.  Per solve, us, at
-    // 999 buses (sums / direct 32 / direct 64 / staged): 1 column 313 / 461 / 1,226 / 1,525;
-    // 128: 529 / 636 / 1,396 / 1,745; 256: 916 / 649 / 1,411 / 1,764; 1,000: - / 1,750 / 1,430 /
-    // 1,795; 4,096: - / 5,732 / 4,144 / 4,339; 8,192: - / - / 7,899 / 7,769.  At 349 buses: 256:
-    // 161 / 172 / 346 / 484; 2,000: - / 386 / 383 / 491; 8,000: - / 1,183 / 941 / 1,009.
+    // 32 x 32 below, and single tiles up to two per CU.  Per solve, us, at 999 buses (sums / direct
+    // 32 / direct 64 / staged): 1 column 264 / 447 / 1,206 / 1,525; 128: 451 / 601 / 1,383 / 1,745;
+    // 256: 845 / 659 / 1,402 / 1,764; 1,000: - / 1,750 / 1,430 / 1,795; 4,096: - / 5,732 / 4,144 /
+    // 4,339; 8,192: - / - / 7,899 / 7,769.  At 349 buses: 256: 155 / 172 / 346 / 484; 2,000: - /
+    // 386 / 383 / 491; 8,000: - / 1,183 / 941 / 1,009.
     const int64_t cus = num_cus();
     auto tiles = [&](int edge) { return (int64_t)((n + edge - 1) / edge) * ((tau + edge - 1) / edge); };
     const int shape = tiles(64) >= 6 * cus ? 3 : 4 * tiles(64) >= 3 * cus ? 2 : tiles(16) > 2 * cus ? 1 : 0;
@@ -581,7 +607,7 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
                       : shape == 2 ? gemm64_direct_kernel<THREE, 2, IO>
                       : shape == 1 ? gemm64_direct_kernel<THREE, 1, IO>
                                    : gemm64_sums_kernel<THREE, IO>;
-    const int threads = shape == 0 ? 192 : 256;
+    const int threads = shape == 0 ? 64 * (3 + kLoaders) : 256;
     const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(edge));
     const int cpb = apart ? finish_chunk(n) : 256;
     const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + cpb - 1) / cpb);
