@@ -1419,11 +1419,15 @@ double table_cost(const tpf_network_s &net, const DeviceNet &dn, int64_t tau) {
         });
     else if constexpr (kF64)
         (void)with_shape64(nb, [&](auto s) {
-            return take(s, tree_lds(np, levels, s.cols, 0), resident<fpi_tree_kernel<IO, s.cols, s.places, 0>>);
+            return take(s, tree_lds(np, levels, s.cols, dn.aP ? 1 : 0),
+                        dn.aP ? resident<fpi_tree_kernel<IO, s.cols, s.places, 1>>
+                              : resident<fpi_tree_kernel<IO, s.cols, s.places, 0>>);
         });
     else
         (void)with_shape32(nb, [&](auto s) {
-            return take(s, tree32_lds(np, levels, s.cols, 0), resident<fpi_tree32_kernel<IO, s.cols, s.places, 0>>);
+            return take(s, tree32_lds(np, levels, s.cols, dn.aP ? 1 : 0),
+                        dn.aP ? resident<fpi_tree32_kernel<IO, s.cols, s.places, 1>>
+                              : resident<fpi_tree32_kernel<IO, s.cols, s.places, 0>>);
         });
     return cost;
 }
