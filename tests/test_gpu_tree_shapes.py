@@ -72,6 +72,25 @@ def test_any_tree(gpu, n, levels, T, heavy):
     assert np.abs(V.cpu().numpy()[pick] - oracle.fpi(onet, S[pick], 1e-10, 200).V).max() <= 1e-6
 
 
+@pytest.mark.parametrize("zip_loads", [False, True])
+@pytest.mark.parametrize("n,levels", TREES)
+def test_a_column_alone_and_among_others(gpu, n, levels, zip_loads):
+    """The kernel depends on the number of columns, the bits do not."""
+    net, _, S = _case(n, levels, True, 3_001)
+    if zip_loads:
+        rng = np.random.default_rng(n)
+        ai = rng.uniform(0, 0.6, n)
+        frm, to = _tree(n, levels, True), np.arange(1, n + 1, dtype=np.int32)
+        r = rng.uniform(0.002, 0.006, n) * (20 / max(n, 20))
+        net = tpf.Network(n + 1, frm, to, r, r * rng.uniform(0.5, 2.0, n), alpha_i=ai, alpha_p=1 - ai)
+    S = torch.from_numpy(S).to(gpu)
+    for mode in ("tree_fp64", "tree_fp32"):
+        few, it, _ = tpf.solve_timeseries(net, S[:9].contiguous(), 1e-6, 100, mode=mode)
+        for X in (S, S.repeat(max(1, 6_000 // n), 1)):
+            V, its, _ = tpf.solve_timeseries(net, X, 1e-6, 100, mode=mode)
+            assert torch.equal(V[:9], few) and torch.equal(its[:9], it)
+
+
 @pytest.mark.parametrize("T", [9, 3_001])
 @pytest.mark.parametrize("n,levels", [(5, 2), (5, 5), (12, 8), (30, 5), (30, 12), (60, 6), (99, 4), (127, 7), (250, 10)])
 def test_any_three_phase_tree(gpu, n, levels, T):
