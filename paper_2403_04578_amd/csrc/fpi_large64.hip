@@ -228,57 +228,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
     }
 }
 
-// The same sweep for batches that leave a CU fewer than six such workgroups: the operands
-// straight from L2 through a register ring (no LDS and no barrier in the loop).  Every element's
-// three sums run over the k-steps in the order of gemm64_kernel, so a column has the same bits
-// whichever kernel its batch picks; splitting the k-steps among wavefronts is faster for a few
-// columns (192 against 313 us for one at 999 buses) but adds the terms in another order.
-// Four wavefronts, 2 x 2, with TW x TW tiles each; TW = 1 is bound by the operands' way through L1
-// (43 bytes per cycle and CU), TW = 2 halves that.
-template <bool THREE, int TW, typename IO>
+// The same sweep for batches that leave a CU fewer than six such workgroups, as 32 x 32, 64 x 32
+// or 64 x 64 blocks: the operands straight from L2 through a register ring (no LDS and no barrier
+// in the loop).  Every element's three sums run over the k-steps in the order of gemm64_kernel, so
+// a column has the same bits whichever kernel its batch picks; splitting the k-steps among
+// wavefronts is faster for a few columns (197 against 264 us for one at 999 buses) but adds the
+// terms in another order.  Four wavefronts, 2 x 2, with TR x TC tiles each; 1 x 1 is bound by the
+// operands' way through L1 (43 bytes per cycle and CU), 2 x 1 takes three quarters of it and 2 x 2
+// half.
+template <bool THREE, int TR, int TC, typename IO>
 __global__ __launch_bounds__(256) void gemm64_direct_kernel(
     const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
     const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
     const IO *__restrict__ S, const ZipShares zs, double *__restrict__ x, unsigned long long *__restrict__ dmax) {
-    constexpr int E = 2 * TW;  // tiles per side of a workgroup's block
-    constexpr int kRing = TW == 1 ? 6 : 3;
+    constexpr int kCols = 32 * TC;  // of a workgroup's block
+    constexpr int kRing = TR + TC == 2 ? 6 : TR + TC == 3 ? 4 : 3;
     const int nact = *na;
-    const int ct = (nact + 16 * E - 1) / (16 * E);
-    __shared__ unsigned long long red[16 * E];
+    const int ct = (nact + kCols - 1) / kCols;
+    __shared__ unsigned long long red[kCols];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, j = lane & 15;
     for (int t = blockIdx.x; t < ct * row_blocks; t += gridDim.x) {
-        const int cb = t / row_blocks * 16 * E;              // the block's first column,
-        const int c0 = cb + 16 * TW * (wave & 1);            // the wavefront's,
-        const int rt = t % row_blocks * E + TW * (wave >> 1);  // and its first row tile
-        if (tid < 16 * E) red[tid] = 0ull;
-        const d2x *Ap[TW], *Bp[TW];
+        const int cb = t / row_blocks * kCols;                      // the block's first column,
+        const int c0 = cb + 16 * TC * (wave & 1);                   // the wavefront's,
+        const int rt = t % row_blocks * 2 * TR + TR * (wave >> 1);  // and its first row tile
+        if (tid < kCols) red[tid] = 0ull;
+        const d2x *Ap[TR], *Bp[TC];
 #pragma unroll
-        for (int a = 0; a < TW; ++a) Ap[a] = A + (size_t)(rt + a) * KT * 64 + lane;
+        for (int a = 0; a < TR; ++a) Ap[a] = A + (size_t)(rt + a) * KT * 64 + lane;
 #pragma unroll
-        for (int b = 0; b < TW; ++b) {
+        for (int b = 0; b < TC; ++b) {
             const int slot = c0 + 16 * b + j;
             Bp[b] = B + act[slot < nact ? slot : nact - 1] * KB + g;
         }
-        d4x m1[TW][TW], m2[TW][TW], m3[TW][TW];
+        d4x m1[TR][TC], m2[TR][TC], m3[TR][TC];
 #pragma unroll
-        for (int a = 0; a < TW; ++a)
+        for (int a = 0; a < TR; ++a)
 #pragma unroll
-            for (int b = 0; b < TW; ++b) m1[a][b] = m2[a][b] = m3[a][b] = d4x{0, 0, 0, 0};
-        d2x ra[kRing][TW], rb[kRing][TW];
+            for (int b = 0; b < TC; ++b) m1[a][b] = m2[a][b] = m3[a][b] = d4x{0, 0, 0, 0};
+        d2x ra[kRing][TR], rb[kRing][TC];
         auto fetch = [&](int u, int kt) __attribute__((always_inline)) {
             const int k = kt < KT ? kt : KT - 1;  // past the end: a step already read
 #pragma unroll
-            for (int a = 0; a < TW; ++a) ra[u][a] = Ap[a][(size_t)k * 64];
+            for (int a = 0; a < TR; ++a) ra[u][a] = Ap[a][(size_t)k * 64];
 #pragma unroll
-            for (int b = 0; b < TW; ++b) rb[u][b] = Bp[b][4 * k];
+            for (int b = 0; b < TC; ++b) rb[u][b] = Bp[b][4 * k];
         };
         auto step = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-            for (int a = 0; a < TW; ++a)
+            for (int a = 0; a < TR; ++a)
 #pragma unroll
-                for (int b = 0; b < TW; ++b) {
+                for (int b = 0; b < TC; ++b) {
                     const d2x z = ra[u][a], i = rb[u][b];
                     m1[a][b] = mma64(z.x, i.x, m1[a][b]);
                     m2[a][b] = mma64(z.y, i.y, m2[a][b]);
@@ -305,13 +306,13 @@ __global__ __launch_bounds__(256) void gemm64_direct_kernel(
             if (kt + u < KT) step(u);
         __syncthreads();  // red clear
 #pragma unroll
-        for (int b = 0; b < TW; ++b) {
+        for (int b = 0; b < TC; ++b) {
             const int slot = c0 + 16 * b + j;
             const bool live = slot < nact;
             const long long c = act[live ? slot : nact - 1];
             double e = 0.0, poison = 0.0;
 #pragma unroll
-            for (int a = 0; a < TW; ++a) {
+            for (int a = 0; a < TR; ++a) {
                 const int bus0 = 16 * (rt + a) + g;
                 d2x old[4];
                 double sr[4], si[4];
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(256) void gemm64_direct_kernel(
                 atomicMax(red + slot - cb, poison == 0.0 ? (unsigned long long)__double_as_longlong(e) : ~0ull);
         }
         __syncthreads();
-        if (tid < 16 * E && cb + tid < nact) atomicMax(dmax + act[cb + tid], red[tid]);
+        if (tid < kCols && cb + tid < nact) atomicMax(dmax + act[cb + tid], red[tid]);
         __syncthreads();  // red is reused
     }
 }
@@ -591,24 +592,35 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     // stay on the device (three of them in rotation: read, appended, cleared) and the
     // kernels of a sweep with no active column exit at once.  Queueing stops early when
     // the device has already posted that none is left (all_retired).
-    // Shape by the tiles a batch has (the results do not depend on it): staged 64 x 64 tiles once
-    // each CU gets six of them, the direct ones from three quarters of a 64 x 64 tile per CU,
-    // 32 x 32 below, and single tiles up to two per CU.  Per solve, us, at 999 buses (sums / direct
-    // 32 / direct 64 / staged): 1 column 264 / 447 / 1,206 / 1,525; 128: 451 / 601 / 1,383 / 1,745;
-    // 256: 845 / 659 / 1,402 / 1,764; 1,000: - / 1,750 / 1,430 / 1,795; 4,096: - / 5,732 / 4,144 /
-    // 4,339; 8,192: - / - / 7,899 / 7,769.  At 349 buses: 256: 155 / 172 / 346 / 484; 2,000: - /
-    // 386 / 383 / 491; 8,000: - / 1,183 / 941 / 1,009.
+    // Shape by the tiles a batch has (the results do not depend on it).  Single tiles up to two
+    // per CU, 32 x 32 up to one, staged 64 x 64 from six; between them 64 x 32 straight from L2, or
+    // 64 x 64 where those do not save half a round of the chip and the rounds are three or more (a
+    // round of 64 x 32 at 999 buses takes 445 us and 445 more per solve, of 64 x 64 840 and 560).
+    // Per solve, us, at 999 buses (sums / 32 x 32 / 64 x 32 / 64 x 64 / staged): 1 column 264 / 447 /
+    // - / 1,206 / 1,525; 128: 451 / 601 / - / 1,383 / 1,745; 256: 845 / 659 / 885 / 1,390 / -; 500: 1,325
+    // / 1,094 / 915 / 1,402 / 1,763; 1,000: - / 1,740 / 1,356 / 1,426 / 1,795; 2,000: - / 3,043 / 2,238
+    // / 2,250 / 2,575; 4,000: - / 5,733 / 4,166 / 4,137 / 4,356; 8,192: - / - / - / 7,899 / 7,769.  At 349
+    // buses: 256: 155 / 184 / 238 / 399 / -; 1,000: - / 308 / 260 / 415 / -; 3,000: - / 647 / 576 / 704 /
+    // -; 5,000: - / 881 / 746 / 721 / 882.
     const int64_t cus = num_cus();
-    auto tiles = [&](int edge) { return (int64_t)((n + edge - 1) / edge) * ((tau + edge - 1) / edge); };
-    const int shape = tiles(64) >= 6 * cus ? 3 : 4 * tiles(64) >= 3 * cus ? 2 : tiles(16) > 2 * cus ? 1 : 0;
-    const int edge = shape >= 2 ? 64 : shape == 1 ? 32 : 16;
-    const int row_blocks = (n + edge - 1) / edge;
-    const auto gemm = shape == 3   ? gemm64_kernel<THREE, IO>
-                      : shape == 2 ? gemm64_direct_kernel<THREE, 2, IO>
-                      : shape == 1 ? gemm64_direct_kernel<THREE, 1, IO>
+    auto tiles = [&](int rows, int columns) {
+        return (int64_t)((n + rows - 1) / rows) * ((tau + columns - 1) / columns);
+    };
+    auto rounds = [&](int columns) { return (tiles(64, columns) + cus - 1) / cus; };
+    const int shape = tiles(64, 64) >= 6 * cus                            ? 4
+                      : tiles(16, 16) <= 2 * cus                          ? 0
+                      : tiles(32, 32) <= cus                              ? 1
+                      : rounds(32) < 2 * rounds(64) || rounds(64) < 3     ? 2
+                                                                          : 3;
+    const int rows = shape >= 2 ? 64 : shape == 1 ? 32 : 16, columns = shape >= 3 ? 64 : shape >= 1 ? 32 : 16;
+    const int row_blocks = (n + rows - 1) / rows;
+    const auto gemm = shape == 4   ? gemm64_kernel<THREE, IO>
+                      : shape == 3 ? gemm64_direct_kernel<THREE, 2, 2, IO>
+                      : shape == 2 ? gemm64_direct_kernel<THREE, 2, 1, IO>
+                      : shape == 1 ? gemm64_direct_kernel<THREE, 1, 1, IO>
                                    : gemm64_sums_kernel<THREE, IO>;
     const int threads = shape == 0 ? 64 * (3 + kLoaders) : 256;
-    const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(edge));
+    const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(rows, columns));
     const int cpb = apart ? finish_chunk(n) : 256;
     const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + cpb - 1) / cpb);
     const unsigned long long thr = square_bound(tol);
