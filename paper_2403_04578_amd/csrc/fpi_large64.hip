@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
 // or 64 x 64 blocks: the operands straight from L2 through a register ring (no LDS and no barrier
 // in the loop).  Every element's three sums run over the k-steps in the order of gemm64_kernel, so
 // a column has the same bits whichever kernel its batch picks; splitting the k-steps among
-// wavefronts is faster for a few columns (197 against 264 us for one at 999 buses) but adds the
+// wavefronts is faster for a few columns (197 against 235 us for one at 999 buses) but adds the
 // terms in another order.  Four wavefronts, 2 x 2, with TR x TC tiles each; 1 x 1 is bound by the
 // operands' way through L1 (43 bytes per cycle and CU), 2 x 1 takes three quarters of it and 2 x 2
 // half.
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256) void gemm64_direct_kernel(
     }
 }
 
-// The same for the fewest columns: a workgroup per 16 x 16 tile, a wavefront for each of the
+// The same for few columns: a workgroup per 16 x 16 tile, a wavefront for each of the
 // three sums, so that a sweep takes about one chain of KT products (64 cycles each), and
 // kLoaders more that bring the operands: they request them kSets chunks of kChunk k-steps before
 // they write them to LDS, real and imaginary parts and what the third product takes in planes
@@ -475,6 +475,88 @@ __global__ __launch_bounds__(64 * (3 + kLoaders)) void gemm64_sums_kernel(
     }
 }
 
+constexpr int kXcds = 8;  // workgroups are dealt to the chip's eight dies in turn
+
+// The same for a handful of columns: a wavefront per 16 buses x 4 columns, whose 4 x 4 x 4 products
+// (four blocks of four buses, the operator's fragments as they are) take 24 cycles instead of 64
+// and round alike: both are chains of FMAs over their k values.  No LDS and no barrier in the
+// loop.  Bound by issue, three products per k-step (72 cycles), with a ring deep enough for the
+// way to L2.  One column of 999 buses: 14.6 us a sweep, 17 by the kernel above.  A tile's column
+// groups go to one die.
+template <bool THREE, typename IO>
+__global__ __launch_bounds__(64) void gemm64_few_kernel(
+    const d2x *__restrict__ A, int KT, const d2x *__restrict__ B, d2x *__restrict__ Bn, int KB,
+    const long long *__restrict__ act, const int *__restrict__ na, int row_blocks, const d2x *__restrict__ w, int n,
+    const IO *__restrict__ S, const ZipShares zs, double *__restrict__ x, unsigned long long *__restrict__ dmax) {
+    constexpr int kRing = 20;
+    const int nact = *na;
+    const int lane = threadIdx.x, j = lane & 3;
+    const int spread = (row_blocks + kXcds - 1) / kXcds * kXcds;
+    __shared__ unsigned long long red[4];
+    for (int t = blockIdx.x; t < (nact + 3) / 4 * spread; t += gridDim.x) {
+        const int c0 = t / spread * 4, rt = t % spread;
+        if (rt >= row_blocks) continue;
+        if (lane < 4) red[lane] = 0ull;
+        const bool live = c0 + j < nact;
+        const long long c = act[live ? c0 + j : nact - 1];
+        const int bus = 16 * rt + 4 * (lane >> 2 & 3) + (lane >> 4);  // of the lane's result
+        const bool mine = live && bus < n;
+        d2x wv = d2x{0.0, 0.0}, old = wv;
+        double sr = 0.0, si = 0.0;
+        if (mine) {
+            wv = w[bus];
+            old = reinterpret_cast<const d2x *>(x)[c * n + bus];
+            sr = (double)S[2 * (c * n + bus)], si = (double)S[2 * (c * n + bus) + 1];
+        }
+        const d2x *Ap = A + (size_t)rt * KT * 64 + lane;
+        const d2x *Bp = B + c * KB + (lane >> 4);
+        double m1 = 0.0, m2 = 0.0, m3 = 0.0;
+        d2x ra[kRing], rb[kRing];
+        auto fetch = [&](int u, int kt) __attribute__((always_inline)) {
+            const int k = kt < KT ? kt : KT - 1;  // past the end: a step already read
+            ra[u] = Ap[(size_t)k * 64];
+            rb[u] = Bp[4 * k];
+        };
+        auto step = [&](int u) __attribute__((always_inline)) {
+            const d2x z = ra[u], i = rb[u];
+            m1 = __builtin_amdgcn_mfma_f64_4x4x4f64(z.x, i.x, m1, 0, 0, 0);
+            m2 = __builtin_amdgcn_mfma_f64_4x4x4f64(z.y, i.y, m2, 0, 0, 0);
+            if constexpr (THREE) {
+                m3 = __builtin_amdgcn_mfma_f64_4x4x4f64(z.x - z.y, i.x - i.y, m3, 0, 0, 0);
+            } else {
+                m3 = __builtin_amdgcn_mfma_f64_4x4x4f64(z.x, i.y, m3, 0, 0, 0);
+                m3 = __builtin_amdgcn_mfma_f64_4x4x4f64(z.y, i.x, m3, 0, 0, 0);
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < kRing; ++u) {
+            fetch(u, u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        int kt = 0;
+        for (; kt + kRing <= KT; kt += kRing) {
+#pragma unroll
+            for (int u = 0; u < kRing; ++u) {
+                step(u);
+                fetch(u, kt + u + kRing);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kRing; ++u)
+            if (kt + u < KT) step(u);
+        double e = 0.0, poison = 0.0;
+        if (mine)
+            update64<IO>(m1 - m2, imaginary<THREE>(m1, m2, m3), wv, c, bus, n, KB, S, zs, old, sr, si, x, Bn, e,
+                         poison);
+        __syncthreads();  // red clear
+        if (live) atomicMax(red + j, poison == 0.0 ? (unsigned long long)__double_as_longlong(e) : ~0ull);
+        __syncthreads();
+        if (lane < 4 && c0 + lane < nact) atomicMax(dmax + act[c0 + lane], red[lane]);
+        __syncthreads();  // red is reused
+    }
+}
+
 // Chunks of cpb <= 256 active columns, one thread each: sweep count, stopping rule (thr: the bit
 // pattern of the smallest |dV|^2 whose root is not below the tolerance), retirement and the
 // staying columns' places in the next list.  Where the state is kept `apart` from the
@@ -592,35 +674,42 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     // stay on the device (three of them in rotation: read, appended, cleared) and the
     // kernels of a sweep with no active column exit at once.  Queueing stops early when
     // the device has already posted that none is left (all_retired).
-    // Shape by the tiles a batch has (the results do not depend on it).  Single tiles up to two
-    // per CU, 32 x 32 up to one, staged 64 x 64 from six; between them 64 x 32 straight from L2, or
-    // 64 x 64 where those do not save half a round of the chip and the rounds are three or more (a
-    // round of 64 x 32 at 999 buses takes 445 us and 445 more per solve, of 64 x 64 840 and 560).
-    // Per solve, us, at 999 buses (sums / 32 x 32 / 64 x 32 / 64 x 64 / staged): 1 column 264 / 447 /
-    // - / 1,206 / 1,525; 128: 451 / 601 / - / 1,383 / 1,745; 256: 845 / 659 / 885 / 1,390 / -; 500: 1,325
-    // / 1,094 / 915 / 1,402 / 1,763; 1,000: - / 1,740 / 1,356 / 1,426 / 1,795; 2,000: - / 3,043 / 2,238
-    // / 2,250 / 2,575; 4,000: - / 5,733 / 4,166 / 4,137 / 4,356; 8,192: - / - / - / 7,899 / 7,769.  At 349
-    // buses: 256: 155 / 184 / 238 / 399 / -; 1,000: - / 308 / 260 / 415 / -; 3,000: - / 647 / 576 / 704 /
-    // -; 5,000: - / 881 / 746 / 721 / 882.
+    // Shape by the tiles a batch has (the results do not depend on it).  16 buses x 4 columns up to
+    // one per CU, 16 x 16 up to two, 32 x 32 up to one, staged 64 x 64 from six; between them 64 x 32
+    // straight from L2, or 64 x 64 where those do not save half a round of the chip and the rounds
+    // are three or more (a round of 64 x 32 at 999 buses takes 445 us and 445 more per solve, of
+    // 64 x 64 840 and 560).
+    // Per solve, us, at 999 buses (16 x 4 / 16 x 16 / 32 x 32 / 64 x 32 / 64 x 64 / staged): 1 column
+    // 235 / 269 / 447 / - / 1,206 / 1,525; 16: 242 / 282; 32: 348 / 300 / 597; 128: 1,075 / 451 / 601 / - /
+    // 1,383 / 1,745; 256: - / 845 / 659 / 885 / 1,390; 500: - / 1,325 / 1,094 / 915 / 1,402 / 1,763; 1,000: -
+    // / - / 1,740 / 1,356 / 1,426 / 1,795; 2,000: - / - / 3,043 / 2,238 / 2,250 / 2,575; 4,000: - / - / 5,733 /
+    // 4,166 / 4,137 / 4,356; 8,192: 7,899 / 7,769 (64 x 64, staged).  At 349 buses: 32: 92 / 104 / 176;
+    // 64: 117 / 111 / 169; 256: - / 155 / 184 / 238 / 399; 1,000: - / - / 308 / 260 / 415; 3,000: - / - /
+    // 647 / 576 / 704; 5,000: - / - / 881 / 746 / 721 / 882.
     const int64_t cus = num_cus();
     auto tiles = [&](int rows, int columns) {
         return (int64_t)((n + rows - 1) / rows) * ((tau + columns - 1) / columns);
     };
     auto rounds = [&](int columns) { return (tiles(64, columns) + cus - 1) / cus; };
-    const int shape = tiles(64, 64) >= 6 * cus                            ? 4
-                      : tiles(16, 16) <= 2 * cus                          ? 0
-                      : tiles(32, 32) <= cus                              ? 1
-                      : rounds(32) < 2 * rounds(64) || rounds(64) < 3     ? 2
-                                                                          : 3;
-    const int rows = shape >= 2 ? 64 : shape == 1 ? 32 : 16, columns = shape >= 3 ? 64 : shape >= 1 ? 32 : 16;
+    const int shape = tiles(64, 64) >= 6 * cus                        ? 5
+                      : tiles(16, 4) <= cus                           ? 0
+                      : tiles(16, 16) <= 2 * cus                      ? 1
+                      : tiles(32, 32) <= cus                          ? 2
+                      : rounds(32) < 2 * rounds(64) || rounds(64) < 3 ? 3
+                                                                      : 4;
+    const int rows = shape >= 3 ? 64 : shape == 2 ? 32 : 16;
+    const int columns = shape >= 4 ? 64 : shape >= 2 ? 32 : shape == 1 ? 16 : 4;
     const int row_blocks = (n + rows - 1) / rows;
-    const auto gemm = shape == 4   ? gemm64_kernel<THREE, IO>
-                      : shape == 3 ? gemm64_direct_kernel<THREE, 2, 2, IO>
-                      : shape == 2 ? gemm64_direct_kernel<THREE, 2, 1, IO>
-                      : shape == 1 ? gemm64_direct_kernel<THREE, 1, 1, IO>
-                                   : gemm64_sums_kernel<THREE, IO>;
-    const int threads = shape == 0 ? 64 * (3 + kLoaders) : 256;
-    const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, tiles(rows, columns));
+    const auto gemm = shape == 5   ? gemm64_kernel<THREE, IO>
+                      : shape == 4 ? gemm64_direct_kernel<THREE, 2, 2, IO>
+                      : shape == 3 ? gemm64_direct_kernel<THREE, 2, 1, IO>
+                      : shape == 2 ? gemm64_direct_kernel<THREE, 1, 1, IO>
+                      : shape == 1 ? gemm64_sums_kernel<THREE, IO>
+                                   : gemm64_few_kernel<THREE, IO>;
+    const int threads = shape == 0 ? 64 : shape == 1 ? 64 * (3 + kLoaders) : 256;
+    const int64_t blocks =
+        shape == 0 ? (row_blocks + kXcds - 1) / kXcds * kXcds * ((tau + 3) / 4) : tiles(rows, columns);
+    const unsigned g_mm = (unsigned)gemm_grid((const void *)gemm, threads, blocks);
     const int cpb = apart ? finish_chunk(n) : 256;
     const unsigned g_fin = (unsigned)std::min<int64_t>(kFinishGrid, (tau + cpb - 1) / cpb);
     const unsigned long long thr = square_bound(tol);
