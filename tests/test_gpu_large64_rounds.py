@@ -31,3 +31,13 @@ def test_every_shape(gpu, n, ratio):
     pick = np.r_[0:3, T - 2:T]
     ref = oracle.fpi(oracle.build_network(n + 1, f.frm, f.to, f.r, x), S[pick], 0.0, 3).V
     assert np.abs(want[0].cpu().numpy()[pick] - ref).max() <= 1e-12
+
+
+def test_operator_beyond_the_cache(gpu):
+    f = W.make_feeder(3_601, load_scale=0.02)
+    net = tpf.Network.from_feeder(f)
+    Sd = torch.from_numpy(W.profile_minute_year(f, steps=500, seed=8)).to(gpu)
+    want = tpf.solve_timeseries(net, Sd, 0.0, 2, mode="fp64")
+    for m in (300, 64, 20, 1):
+        for a, b in zip(want, tpf.solve_timeseries(net, Sd[:m].contiguous(), 0.0, 2, mode="fp64")):
+            assert torch.equal(a[:m], b), m
