@@ -676,8 +676,8 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     // the device has already posted that none is left (all_retired).
     // Shape by the tiles a batch has (the results do not depend on it).  16 buses x 4 columns up to
     // one per CU, 16 x 16 up to two, 32 x 32 up to one, staged 64 x 64 from six; between them 64 x 32
-    // straight from L2, or 64 x 64 where those do not save half a round of the chip and the rounds
-    // are three or more (a round of 64 x 32 at 999 buses takes 445 us and 445 more per solve, of
+    // straight from L2, or 64 x 64 where those do not save half a turn of the chip and the turns
+    // are three or more (a turn of 64 x 32 at 999 buses takes 445 us and 445 more per solve, of
     // 64 x 64 840 and 560), and 64 x 64 when an operator beyond the 256 MB cache would be streamed more
     // than three times (4,999 buses, 500 columns: 11.1 ms by 64 x 32, 10.0).
     // Per solve, us, at 999 buses (16 x 4 / 16 x 16 / 32 x 32 / 64 x 32 / 64 x 64 / staged): 1 column
@@ -691,13 +691,13 @@ static int run_large64(const tpf_network_s &net, const DeviceNet &dn, const void
     auto tiles = [&](int rows, int columns) {
         return (int64_t)((n + rows - 1) / rows) * ((tau + columns - 1) / columns);
     };
-    const int64_t rounds = (tiles(64, 32) + cus - 1) / cus, twice = (tiles(64, 64) + cus - 1) / cus * 2;
+    const int64_t turns = (tiles(64, 32) + cus - 1) / cus, twice = (tiles(64, 64) + cus - 1) / cus * 2;
     const bool cached = (size_t)16 * n * n <= ((size_t)192 << 20);
     const int shape = tiles(64, 64) >= 6 * cus                                         ? 5
                       : tiles(16, 4) <= cus                                            ? 0
                       : tiles(16, 16) <= 2 * cus                                       ? 1
                       : tiles(32, 32) <= cus                                           ? 2
-                      : (rounds < twice || twice < 6) && (rounds <= 3 || cached)       ? 3
+                      : (turns < twice || twice < 6) && (turns <= 3 || cached)         ? 3
                                                                                        : 4;
     const int rows = shape >= 3 ? 64 : shape == 2 ? 32 : 16;
     const int columns = shape >= 4 ? 64 : shape >= 2 ? 32 : shape == 1 ? 16 : 4;
